@@ -185,13 +185,17 @@ typedef enum ucl_tile_scheduler { UCL_SCHED_DEFAULT = 0, UCL_SCHED_PERSISTENT = 
  * the first UCL_WORKSPACE_COUNTER_BYTES to be zero when the call starts: clear them once with
  * ucl_workspace_init(); every call leaves them zero again.  Calls that share a workspace must not
  * overlap in time.  Without a split, workspace is ignored.
- * scheduler is a ucl_tile_scheduler; STREAM_K uses the workspace in the same way (zeroed counters, left zero). */
+ * scheduler is a ucl_tile_scheduler; STREAM_K uses the workspace in the same way (zeroed counters, left zero).
+ * k_groups: groups of four wavefronts that share a tile inside one workgroup, each multiplying its own part of K
+ * (their sums meet in LDS in group order; no workspace).  With no tile named the library chooses.  With a tile
+ * named, 0 takes the kernel of that shape without K groups if one is built, else the one with; n > 1 takes the
+ * one built with n groups (ucl_variant_k_groups()), 1 the one without. */
 typedef struct ucl_tuning {
     int32_t tile_m, tile_n, tile_k, stages, raster;
     int32_t iterator;
     int32_t split_k_mode, split_k_slices;
     int32_t scheduler;
-    int32_t reserved;
+    int32_t k_groups;
     void *workspace;
     int64_t workspace_bytes;
 } ucl_tuning;
@@ -407,6 +411,7 @@ typedef struct ucl_variant_info {
 } ucl_variant_info;
 int32_t ucl_num_variants(void);
 ucl_status ucl_variant(int32_t i, ucl_variant_info *out);
+int32_t ucl_variant_k_groups(int32_t i);   /* K groups variant i is built with (1: none; 0: no such variant) */
 
 const char *ucl_status_string(ucl_status s);
 const char *ucl_last_error(void);   /* thread-local; valid until the next call on this thread */

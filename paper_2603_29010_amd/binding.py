@@ -40,7 +40,7 @@ class _Tuning(C.Structure):
     _fields_ = [("tile_m", C.c_int32), ("tile_n", C.c_int32), ("tile_k", C.c_int32),
                 ("stages", C.c_int32), ("raster", C.c_int32), ("iterator", C.c_int32),
                 ("split_k_mode", C.c_int32), ("split_k_slices", C.c_int32), ("scheduler", C.c_int32),
-                ("reserved", C.c_int32), ("workspace", C.c_void_p), ("workspace_bytes", C.c_int64)]
+                ("k_groups", C.c_int32), ("workspace", C.c_void_p), ("workspace_bytes", C.c_int64)]
 
 
 SPLIT_K_MODES = {"none": 0, "serial": 1, "parallel": 2}
@@ -128,6 +128,8 @@ def _load():
         lib.ucl_tile_map.argtypes = [i32, C.POINTER(i32), i32, i32, i32, C.POINTER(i32), C.POINTER(i32),
                                      C.POINTER(i32)]
         lib.ucl_num_variants.restype = i32
+        lib.ucl_variant_k_groups.restype = i32
+        lib.ucl_variant_k_groups.argtypes = [i32]
         lib.ucl_variant.restype = C.c_int
         lib.ucl_variant.argtypes = [i32, C.POINTER(_VariantInfo)]
         lib.ucl_status_string.restype = C.c_char_p
@@ -182,10 +184,10 @@ class Tuning:
     """split_k: "none" | "serial" | "parallel" (or the enum value); workspace: device address."""
 
     def __init__(self, tile_m=0, tile_n=0, tile_k=0, stages=0, raster=0, iterator=0, split_k="none", slices=0,
-                 scheduler="default", workspace=0, workspace_bytes=0):
+                 scheduler="default", workspace=0, workspace_bytes=0, k_groups=0):
         mode = SPLIT_K_MODES[split_k] if isinstance(split_k, str) else int(split_k)
         sched = SCHEDULERS[scheduler] if isinstance(scheduler, str) else int(scheduler)
-        self.c = _Tuning(tile_m, tile_n, tile_k, stages, raster, iterator, mode, slices, sched, 0,
+        self.c = _Tuning(tile_m, tile_n, tile_k, stages, raster, iterator, mode, slices, sched, k_groups,
                          workspace or None, workspace_bytes)
 
     def ref(self):
@@ -324,6 +326,7 @@ def ucl_variant(i):
     _check(_load().ucl_variant(i, C.byref(v)))
     d = {k: getattr(v, k) for k, _ in _VariantInfo._fields_}
     d["mode"], d["f16"], d["la"], d["lb"] = v.op_class, int(v.dt_in == DTYPES["f16"]), v.a_path, v.b_path
+    d["k_groups"] = int(_load().ucl_variant_k_groups(i))
     d["dt"] = {code: name for name, code in DTYPES.items()}[v.dt_in]
     return d
 

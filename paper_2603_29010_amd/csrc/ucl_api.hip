@@ -38,7 +38,7 @@ ucl_status fail(ucl_status st, const char *fmt, ...) {
 const std::vector<VariantDesc> &all_variants() {
     static const std::vector<VariantDesc> v = [] {
         std::vector<VariantDesc> out;
-        for (VariantList l : {variants_gemm_kk_bf16_a(), variants_gemm_kk_bf16_b(), variants_gemm_kk_bf16_c(), variants_gemm_kk_bf16_d(), variants_gemm_kk_f16_a(), variants_gemm_kk_f16_b(), variants_gemm_mn_bf16(), variants_gemm_mn_f16(), variants_grouped_a(), variants_grouped_b(), variants_conv_a(), variants_conv_b(), variants_conv_f16(), variants_conv_halo(), variants_gemm_kn_bf16(), variants_gemm_kn_f16(), variants_gemm_mx_bf16(), variants_gemm_mx_f16(), variants_grouped_kn(), variants_conv_dgrad(), variants_conv_dgrad_halo(), variants_conv_wgrad(), variants_gemm_kk_fp8(), variants_persistent(), variants_grouped_fp8_e4m3(), variants_grouped_fp8_e5m2(), variants_streamk()})
+        for (VariantList l : {variants_gemm_kk_bf16_a(), variants_gemm_kk_bf16_b(), variants_gemm_kk_bf16_c(), variants_gemm_kk_bf16_d(), variants_gemm_kk_f16_a(), variants_gemm_kk_f16_b(), variants_gemm_mn_bf16(), variants_gemm_mn_f16(), variants_grouped_a(), variants_grouped_b(), variants_conv_a(), variants_conv_b(), variants_conv_f16(), variants_conv_halo(), variants_gemm_kn_bf16(), variants_gemm_kn_f16(), variants_gemm_mx_bf16(), variants_gemm_mx_f16(), variants_grouped_kn(), variants_conv_dgrad(), variants_conv_dgrad_halo(), variants_conv_wgrad(), variants_gemm_kk_fp8(), variants_persistent(), variants_grouped_fp8_e4m3(), variants_grouped_fp8_e5m2(), variants_streamk(), variants_kgroups_kk(), variants_kgroups_mn(), variants_kgroups_conv(), variants_kgroups_conv_grad()})
             for (int i = 0; i < l.n; ++i) out.push_back(l.v[i]);
         return out;
     }();
@@ -119,6 +119,7 @@ constexpr int64_t kMaxWideLd = 1ll << 21;
 // Workgroups of a variant that fit on one CU: 512 registers per lane and SIMD (the kernels are built
 // with a budget by tile area), 160 KB of LDS.
 int workgroups_per_cu(const VariantDesc &v) {
+    if (v.k_groups > 1) return v.wgs_per_cu;          // (their stage buffers take most of a CU's LDS: one)
     const int64_t area = (int64_t)v.tile_m * v.tile_n;
     const int by_regs = area >= 256 * 256 ? 1 : area >= 256 * 128 ? 2 : area >= 128 * 128 ? 3 : 4;
     const int by_lds = v.lds_bytes > 0 ? kLdsBytesPerCU / v.lds_bytes : 8;
@@ -213,11 +214,19 @@ double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_t
     double main = copy_bytes / ((resident ? 16.0e12 : 10.0e12) * busy);
     const double mfma = flops / (relative_rate(v) * 1.38e15 * busy);
     if (mfma > main) main = mfma;
-    const double chain = rounds * (kps / (double)v.tile_k) * (resident ? 0.8e-6 : 1.5e-6) / (v.stages > 1 ? v.stages - 1 : 1);
+    const double chain = rounds * (kps / (double)v.tile_k) * (resident ? 0.8e-6 : 1.5e-6) / (v.stages > 1 ? v.stages - 1 : 1) / v.k_groups;
     if (chain > main) main = chain;
     const double tile_bytes = (double)v.tile_m * v.tile_n * 4.0;
     if (tune->split_k_mode == UCL_SPLIT_K_PARALLEL) return main + 6.0e-6 + wgs * tile_bytes / 1.0e12;
     return main + 3.0e-6 + slices * tile_bytes / (v.tile_m * v.tile_n >= 128 * 128 ? 15.0e9 : 28.0e9);
+}
+
+// Workspace a split-K launch of variant v needs.
+int64_t split_bytes(const Launch &L, const VariantDesc &v, const ucl_tuning *tune) {
+    const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
+    int slices = 1, kps = 0;
+    split_slices(L, tune->split_k_slices, tiles, split_fill(L, v, tune), slices, kps);
+    return slices <= 1 ? 0 : UCL_WORKSPACE_COUNTER_BYTES + (int64_t)slices * tiles * v.tile_m * v.tile_n * 4;
 }
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
@@ -239,13 +248,27 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         if (explicit_tune) {
             if (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.stages != tune->stages || v.tile_k != tune->tile_k)
                 continue;
-            // of several kernels with the named shape: the resident-patch one, else a direct-copy one, else the first
+            if (tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
+            // of several kernels with the named shape: the resident-patch one, else one without K groups (unless named),
+            // else a direct-copy one, else the first
             if (v.la == 3) return &v;
+            if (best && best->k_groups != v.k_groups) {
+                if (v.k_groups < best->k_groups) best = &v;
+                continue;
+            }
             const bool direct = v.la == 5 || v.lb == 4;
             if (!best || (direct && !(best->la == 5 || best->lb == 4))) best = &v;
             continue;
         }
+        if (tune && tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
         const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4);
+        // Split-K and K groups: only the weight gradient, whose gathered operand leaves a workgroup waiting, gains from
+        // both at once; and only in a workspace that holds the partial tiles of the kernel chosen (a caller's workspace
+        // that served the kernels without K groups goes on serving).
+        if (split && v.k_groups > 1) {
+            if (L.mode != 4) continue;
+            if (tune->workspace && split_bytes(L, v, tune) > tune->workspace_bytes) continue;
+        }
         const double t = split ? estimate_split_seconds(v, L, tune) : estimate_seconds(v, L);
         if (!best || t < best_t) { best_t = t; best = &v; }
     }
@@ -1198,6 +1221,7 @@ ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out) {
     memset(out, 0, sizeof(*out));
     out->tile_m = v->tile_m; out->tile_n = v->tile_n; out->tile_k = v->tile_k; out->stages = v->stages;
     out->raster = default_raster(*v, L);
+    out->k_groups = v->k_groups;
     out->iterator = v->la == 3 ? UCL_ITER_FIXED_STRIDE_DILATION : v->la == 2 ? UCL_ITER_ANALYTIC : UCL_ITER_DEFAULT;
     return UCL_OK;
 }
@@ -1270,6 +1294,11 @@ ucl_status ucl_variant(int32_t i, ucl_variant_info *out) {
     out->patch_channels = v.patch_c;
     out->scheduler = v.persistent == 2 ? UCL_SCHED_STREAM_K : v.persistent ? UCL_SCHED_PERSISTENT : UCL_SCHED_DEFAULT;
     return UCL_OK;
+}
+
+int32_t ucl_variant_k_groups(int32_t i) {
+    const auto &vs = all_variants();
+    return i < 0 || i >= (int)vs.size() ? 0 : vs[i].k_groups;
 }
 
 const char *ucl_status_string(ucl_status s) {

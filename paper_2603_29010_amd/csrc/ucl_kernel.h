@@ -344,7 +344,8 @@ __device__ __forceinline__ void apply_step(float (&v)[8], const EpiStepDev &s, c
 
 template <int TM_, int TN_, int TK_, int STAGES_, int DT_ /*inputs: 0 bf16, 1 fp16, 2 fp8 e4m3, 3 fp8 e5m2*/, int MODE_ /*0 gemm+batched, 1 grouped, 2 conv fprop, 3 conv dgrad, 4 conv wgrad*/,
           int LA_ /*OperandLayout of A*/, int LB_ /*OperandLayout of B*/, int SCHED_ = 0 /*tile scheduler: 0 default, 1 persistent, 2 stream-K*/,
-          int PATCH_C_ = 0 /*kHalo: channels per pixel of the tensor the patch holds, 64 or 128 (0: 64 for fprop, 128 for dgrad)*/>
+          int PATCH_C_ = 0 /*kHalo: channels per pixel of the tensor the patch holds, 64 or 128 (0: 64 for fprop, 128 for dgrad)*/,
+          int KG_ = 1 /*wave groups of a workgroup that share the tile, each taking a part of K*/>
 struct KernelCfg {
     static constexpr int TM = TM_, TN = TN_, TK = TK_, STAGES = STAGES_, MODE = MODE_, LA = LA_, LB = LB_;
     static constexpr int SCHED = SCHED_;
@@ -355,6 +356,17 @@ struct KernelCfg {
     static constexpr int CPR = TK / 8;                            // 16-byte chunks per LDS row
     static constexpr int ROW_BYTES = TK * 2;
     static_assert(TK == 32 || TK == 64, "k-tile of 32 or 64 elements");
+    // K groups: KG times four waves work on one tile, each four on their own part of K with stage buffers of their own;
+    // their accumulators meet in LDS before the epilogue, group 0 first (a fixed order).  For problems with fewer
+    // tiles than the chip has CU slots: what such a launch lacks is operand bytes in flight and waves to hide the
+    // LDS latency behind, and KG groups have KG times as many of both.
+    // Measured, before -> after (64x64x64x4 with two groups unless noted): 1000x1001x1992 fp16 33.2 -> 20.2 us,
+    // 16x4096x4096 18.2 -> 14.5 us, A^T B 4096x1024x8192 in fp32 127 -> 60 us (128x128x32x4, two groups; without them
+    // 71 us: 1.15 PFLOP/s, what 128x128 tiles reach at ~16 TB/s of L2 -> LDS copies).  Four groups of 64x64x32x4 were slower
+    // than two of 64x64x64x4 on every shape tried (20.6 against 24.3 us on the first): half-line copies.
+    static constexpr int KG = KG_, THREADS = kThreads * KG_;
+    static_assert(KG_ == 1 || ((KG_ == 2 || KG_ == 4) && SCHED_ == 0 && LA_ != kHalo && LA_ != kMNContig && LB_ != kMNContig),
+                  "K groups are built into the pipelined and the two-buffer loops");
     static constexpr int DT = DT_;
     static_assert(DT_ >= 0 && DT_ <= 3, "input type code");
     static_assert(DT_ < 2 || (LA_ == kKContig && LB_ == kKContig), "8-bit inputs: both operands contiguous along K");
@@ -381,7 +393,9 @@ struct KernelCfg {
     // epilogue staging: per wave 32 rows x (WTN + 4) fp32 (16 bytes of padding per row)
     static constexpr int EPI_LD = TN / 2 + 4;
     static constexpr int EPI_BYTES = 4 * 32 * EPI_LD * 4;
-    static constexpr int LDS_BYTES = PIPE_BYTES + PATCH_BYTES > EPI_BYTES ? PIPE_BYTES + PATCH_BYTES : EPI_BYTES;
+    static constexpr int MEET_BYTES = (KG - 1) * TM * TN * 4;     // accumulators of the groups behind the first
+    static constexpr int WORK_BYTES = KG * PIPE_BYTES + PATCH_BYTES > MEET_BYTES ? KG * PIPE_BYTES + PATCH_BYTES : MEET_BYTES;
+    static constexpr int LDS_BYTES = WORK_BYTES > EPI_BYTES ? WORK_BYTES : EPI_BYTES;
     static constexpr int A_ITERS = HALO ? 0 : TM * CPR / kThreads;   // 16-byte chunks per thread per stage
     static constexpr int B_ITERS = TN * CPR / kThreads;
     static constexpr int ROWS_PER_ITER = kThreads / CPR;          // rows covered by one 256-thread copy
@@ -390,7 +404,9 @@ struct KernelCfg {
     // Register budget: smaller tiles are built to let several workgroups share a CU (512 registers per
     // lane and SIMD, accumulators included), so that one workgroup's loads and stores overlap another's
     // MFMAs -- that is what the short-K, bandwidth-bound problems need.
-    static constexpr int MIN_WAVES = TM * TN >= 256 * 256 ? 1 : TM * TN >= 256 * 128 ? 2 : TM * TN >= 128 * 128 ? 3 : 4;
+    // (K groups: as many waves per SIMD as the workgroups that fit into LDS bring along, four at most)
+    static constexpr int MIN_WAVES = KG > 1 ? (2 * LDS_BYTES <= kLdsBytesPerCU && 2 * KG <= 4 ? 2 * KG : KG)
+                                     : TM * TN >= 256 * 256 ? 1 : TM * TN >= 256 * 128 ? 2 : TM * TN >= 128 * 128 ? 3 : 4;
     using Groups = typename std::conditional<MODE == 1, GroupTable, NoGroupTable>::type;
 };
 
@@ -471,7 +487,7 @@ constexpr int bshare(int mi, int mblocks, int n) {
 }
 
 template <class Cfg>
-__global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(const KParams p_arg, const typename Cfg::Groups gt) {
+__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(const KParams p_arg, const typename Cfg::Groups gt) {
     constexpr int TM = Cfg::TM, TN = Cfg::TN, TK = Cfg::TK, STAGES = Cfg::STAGES;
     constexpr int MI = Cfg::MI, NI = Cfg::NI, MODE = Cfg::MODE, LA = Cfg::LA, LB = Cfg::LB;
     constexpr int A_ITERS = Cfg::A_ITERS, B_ITERS = Cfg::B_ITERS;
@@ -517,6 +533,13 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
     // (persistent kernels: everything derived from the thread index is worked out again for every tile,
     // or the compiler keeps all of it in registers across the whole loop and runs out of them)
     if constexpr (Cfg::PERSIST) asm volatile("" : "+v"(tid_));
+    // K groups: `tid` and `wave` count inside the group, `kg` is the group; its stage buffers start at kg_lds
+    int kg = 0, kg_lds = 0;
+    if constexpr (Cfg::KG > 1) {
+        kg = __builtin_amdgcn_readfirstlane(tid_ >> 8);
+        kg_lds = kg * Cfg::PIPE_BYTES;
+        tid_ &= kThreads - 1;
+    }
     const int tid = tid_;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -588,9 +611,20 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
         Ab += (int64_t)kb * (LA == kKContig ? 1 : p.lda) * 2;
         Bb += (int64_t)kb * (LB == kKContig ? 1 : p.ldb) * 2;
     }
+    // K groups: whole k-tiles [kg * KT, (kg + 1) * KT) of the workgroup's K range.  Every group runs KT k-tiles (the
+    // barriers count on it); what a late group has too many of is copied from out-of-range addresses, i.e. zeros.
+    int kg_first = 0;                                  // first k of the group within the workgroup's range
+    int KT = (k_len + TK - 1) / TK;
+    if constexpr (Cfg::KG > 1) {
+        KT = (KT + Cfg::KG - 1) / Cfg::KG;
+        kg_first = kg * KT * TK;
+        k_len = k_len - kg_first < KT * TK ? k_len - kg_first : KT * TK;
+        if (k_len < 0) k_len = 0;
+        if (LA != kIm2col) Ab += (int64_t)kg_first * (LA == kKContig ? 1 : p.lda) * 2;
+        if (!(LB == kNDirect && (MODE == 3 || MODE == 4))) Bb += (int64_t)kg_first * (LB == kKContig ? 1 : p.ldb) * 2;
+    }
     const int K = k_len;
     const int Kr = K > 0 ? K : 1;                      // rows of k a directly copied operand's resource covers (K = 0: see above)
-    const int KT = (K + TK - 1) / TK;
     const bool k_tail = (K % TK) != 0;
 
     // ---- loader set-up -----------------------------------------------------------------------
@@ -648,8 +682,8 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
                 a_off[i] = (uint32_t)(((nb * p.cH + a_h0[i]) * p.cW + a_w0[i]) * p.cC * 2);
             }
         }
-        a_ci = l_kc % p.cC;
-        const int tap = l_kc / p.cC;
+        a_ci = (kg_first + l_kc) % p.cC;
+        const int tap = (kg_first + l_kc) / p.cC;
         a_r = tap / p.cS;
         a_s = tap % p.cS;
     }
@@ -684,12 +718,12 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
             const int row = i * RPIB + nd_row;
             const int chunk = (tid % CPRB) ^ nd_swz(row);
             b_off[i] = (uint32_t)(chunk * 16);
-            g_b[i] = row / p.cC;
-            g_a[i] = row - g_b[i] * p.cC;
+            g_b[i] = (kg_first + row) / p.cC;
+            g_a[i] = kg_first + row - g_b[i] * p.cC;
         }
     } else if constexpr (LB == kNDirect && MODE == 4) {
         b_rsrc = buffer_rsrc(Bb, (uint32_t)p.b_bytes);
-        const int kb = p.split_k > 1 && p.split_phase != 2 ? slice * p.k_per_slice : 0;
+        const int kb = (p.split_k > 1 && p.split_phase != 2 ? slice * p.k_per_slice : 0) + kg_first;
 #pragma unroll
         for (int i = 0; i < B_ITERS; ++i) {
             const int row = i * RPIB + nd_row;
@@ -841,7 +875,7 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
     auto issue_part = [&](auto check_k_, auto part_, int kt, int buf) __attribute__((always_inline)) {
         constexpr bool CHECK_K = decltype(check_k_)::value;
         constexpr int PART = decltype(part_)::value;
-        char *sA = smem + buf * Cfg::STAGE_BYTES;
+        char *sA = smem + kg_lds + buf * Cfg::STAGE_BYTES;
         char *sB = sA + Cfg::A_BYTES;
         const int k0 = kt * TK;
         const bool kok = !CHECK_K || (k0 + l_kc < K);
@@ -939,7 +973,7 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
     auto issue_one = [&](auto check_k_, auto idx_, int kt, int buf) __attribute__((always_inline)) {
         constexpr bool CHECK_K = decltype(check_k_)::value;
         constexpr int IDX = decltype(idx_)::value;
-        char *sA = smem + buf * Cfg::STAGE_BYTES;
+        char *sA = smem + kg_lds + buf * Cfg::STAGE_BYTES;
         char *sB = sA + Cfg::A_BYTES;
         const int k0 = kt * TK;
         const bool kok = !CHECK_K || (k0 + l_kc < K);
@@ -1056,8 +1090,8 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
     // byte offset of this lane's fragment chunk inside its LDS row for k-step 0 (chunk f_kg XOR
     // swz(row)); k-step kk XORs it with kk*64 (chunk index 4kk + f_kg)
     const int f_x = (f_kg ^ lds_swz<CPR>(f_row)) << 4;
-    const int a_frag_base = (wm * Cfg::WTM + f_row) * ROW_BYTES;
-    const int b_frag_base = Cfg::A_BYTES + (wn * Cfg::WTN + f_row) * ROW_BYTES;
+    const int a_frag_base = kg_lds + (wm * Cfg::WTM + f_row) * ROW_BYTES;
+    const int b_frag_base = kg_lds + Cfg::A_BYTES + (wn * Cfg::WTN + f_row) * ROW_BYTES;
     auto frag = [&](const char *sbase, int base, int blk, int kk) __attribute__((always_inline)) {
         return *(const u32x4_t *)(sbase + base + blk * 16 * ROW_BYTES + (f_x ^ (kk << 6)));
     };
@@ -1074,7 +1108,7 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
         static_for<NI>([&](auto ni_) {
             constexpr int ni = decltype(ni_)::value;
             const int chunk = (wn * Cfg::WTN + ni * 16) / 8 + ((l & 3) >> 1);
-            nd_addr[ni] = Cfg::A_BYTES + (8 * g + (l >> 2)) * (TN * 2) + ((chunk ^ xr) << 4) + (l & 1) * 8;
+            nd_addr[ni] = kg_lds + Cfg::A_BYTES + (8 * g + (l >> 2)) * (TN * 2) + ((chunk ^ xr) << 4) + (l & 1) * 8;
         });
     }
     auto fragB = [&](const char *sbase, auto blk_, int kk) __attribute__((always_inline)) {
@@ -1103,7 +1137,7 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
         const int l = lane & 15, g = lane >> 4;
         const int xr = (((l >> 2) << 1) | (g << 3)) & (TM / 8 - 1);
         const int chunk = (wm * Cfg::WTM) / 8 + ((l & 3) >> 1);
-        md_addr = (8 * g + (l >> 2)) * (TM * 2) + ((chunk ^ xr) << 4) + (l & 1) * 8;
+        md_addr = kg_lds + (8 * g + (l >> 2)) * (TM * 2) + ((chunk ^ xr) << 4) + (l & 1) * 8;
     }
     auto fragA = [&](const char *sbase, int blk, int kk) __attribute__((always_inline)) {
         if constexpr (LA == kMDirect) {
@@ -1276,7 +1310,7 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
         pipeline_barrier<DMA_PER_TILE>();
         static_for<RA - 1>([&](auto i) { ar[i] = fragA(smem, i, 0); });
         static_for<NI>([&](auto ni) { bq[0][ni] = fragB(smem, ni, 0); });
-        const int KT_full = k_tail ? KT - 1 : KT;
+        const int KT_full = Cfg::KG > 1 ? K / TK : k_tail ? KT - 1 : KT;
         int kt = 0;
         auto ktile2 = [&](auto check_, auto cur_) __attribute__((always_inline)) {
             const int cur = cur_;
@@ -1447,7 +1481,8 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
         static_for<RA - 1>([&](auto i) { ar[i] = fragA(smem, i, 0); });
         static_for<NI>([&](auto ni) { bq[0][ni] = fragB(smem, ni, 0); });
 
-        const int KT_full = k_tail ? KT - 1 : KT;                  // complete k-tiles: loads skip the K-tail test
+        // complete k-tiles: loads skip the K-tail test (K groups: a late group has fewer than KT)
+        const int KT_full = Cfg::KG > 1 ? K / TK : k_tail ? KT - 1 : KT;
         const int KTP = (KT + TPU - 1) / TPU * TPU;
         int kt = 0;
         // steady state, unrolled over the ring of stage buffers (and over the B set parity)
@@ -1485,6 +1520,29 @@ __global__ __launch_bounds__(kThreads, Cfg::MIN_WAVES) void ucl_tile_kernel(cons
     // by the matrix pipeline: keep the required distance to their first reader by hand.
     asm volatile("s_nop 15");
     asm volatile("s_nop 15");
+
+    // ---- K groups: the accumulators meet in LDS -----------------------------------------------------
+    // Groups 1 .. KG-1 leave theirs register by register, one 128-bit write per accumulator and thread; group 0 adds
+    // them to its own in group order and goes on alone.
+    if constexpr (Cfg::KG > 1) {
+        // (the copies past the end of K are still in flight: they must land before their buffers are reused)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __syncthreads();
+        if (kg > 0) {
+            char *mine = smem + (kg - 1) * (TM * TN * 4) + tid * 16;
+            static_for<MI>([&](auto mi) {
+                static_for<NI>([&](auto ni) { *(f32x4_t *)(mine + (mi * NI + ni) * (kThreads * 16)) = acc[mi][ni]; });
+            });
+        }
+        __syncthreads();
+        if (kg > 0) return;                            // (waves that have ended are not waited for at barriers)
+        static_for<Cfg::KG - 1>([&](auto g) {
+            const char *other = smem + g * (TM * TN * 4) + tid * 16;
+            static_for<MI>([&](auto mi) {
+                static_for<NI>([&](auto ni) { acc[mi][ni] += *(const f32x4_t *)(other + (mi * NI + ni) * (kThreads * 16)); });
+            });
+        });
+    }
 
     // ---- split-K: partial tiles through the workspace ---------------------------------------------
     // Slice s of tile t keeps its fp32 accumulators at partial[(s * tiles + t)][register][thread], one

@@ -8,10 +8,10 @@ namespace ucl {
 template <class Cfg>
 hipError_t launch_cfg(const KParams &p, const GroupTable *gt, int grid, hipStream_t stream) {
     if constexpr (Cfg::MODE == 1) {
-        hipLaunchKernelGGL(ucl_tile_kernel<Cfg>, dim3(grid), dim3(kThreads), 0, stream, p, *gt);
+        hipLaunchKernelGGL(ucl_tile_kernel<Cfg>, dim3(grid), dim3(Cfg::THREADS), 0, stream, p, *gt);
     } else {
         (void)gt;
-        hipLaunchKernelGGL(ucl_tile_kernel<Cfg>, dim3(grid), dim3(kThreads), 0, stream, p, NoGroupTable{});
+        hipLaunchKernelGGL(ucl_tile_kernel<Cfg>, dim3(grid), dim3(Cfg::THREADS), 0, stream, p, NoGroupTable{});
     }
     return hipGetLastError();
 }
@@ -22,7 +22,7 @@ template <class Cfg>
 int resident_cfg() {
     static const int cached = [] {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ucl_tile_kernel<Cfg>, kThreads, 0) != hipSuccess || n < 1) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ucl_tile_kernel<Cfg>, Cfg::THREADS, 0) != hipSuccess || n < 1) {
             (void)hipGetLastError();
             n = 1;
         }
@@ -34,7 +34,7 @@ int resident_cfg() {
 template <class Cfg>
 constexpr VariantDesc describe() {
     return VariantDesc{Cfg::TM, Cfg::TN, Cfg::TK, Cfg::STAGES, Cfg::DT, Cfg::MODE, Cfg::LA, Cfg::LB,
-                       Cfg::LDS_BYTES, Cfg::SCHED, Cfg::MIN_WAVES, Cfg::HALO ? Cfg::PATCH_C : 0, &launch_cfg<Cfg>, &resident_cfg<Cfg>};
+                       Cfg::LDS_BYTES, Cfg::SCHED, Cfg::KG > 1 ? Cfg::MIN_WAVES / Cfg::KG : Cfg::MIN_WAVES, Cfg::KG, Cfg::HALO ? Cfg::PATCH_C : 0, &launch_cfg<Cfg>, &resident_cfg<Cfg>};
 }
 
 }  // namespace ucl

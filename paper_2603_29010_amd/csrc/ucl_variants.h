@@ -14,6 +14,7 @@ struct VariantDesc {
     int persistent;     // tile scheduler the kernel is built for: 0 one workgroup per tile, 1 persistent (grid = CU slots, workgroups
                         // walk the tile order), 2 stream-K (grid = CU slots, workgroups take equal runs of (tile, k range) iterations)
     int wgs_per_cu;     // workgroups of the kernel a CU is meant to hold (register budget it was built with)
+    int k_groups;       // wave groups of a workgroup that share a tile, each taking a part of K (1: none)
     int patch_c;        // resident-patch kernels: channels per pixel of the tensor the patch holds (64 or 128), else 0
     hipError_t (*launch)(const KParams &p, const GroupTable *gt, int grid, hipStream_t stream);
     int (*resident)();          // workgroups one CU holds at a time (queried from the runtime)
@@ -52,5 +53,9 @@ VariantList variants_gemm_kk_fp8();
 VariantList variants_conv_dgrad();
 VariantList variants_conv_dgrad_halo();
 VariantList variants_conv_wgrad();
+VariantList variants_kgroups_kk();
+VariantList variants_kgroups_mn();
+VariantList variants_kgroups_conv();
+VariantList variants_kgroups_conv_grad();
 
 }  // namespace ucl
