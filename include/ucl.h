@@ -30,9 +30,9 @@
  *     one of their two strides is 1 and the other a multiple of 8, and K (for
  *     K-contiguous operands) or M / N (for operands contiguous along M / N) is
  *     a multiple of 8.  D and the epilogue's tensor operands may have any N and
- *     any strides; they are accessed with 128-bit loads / stores when base and
- *     row starts are 16-byte aligned (leading and batch strides multiples of 8
- *     for 16-bit types, of 4 for fp32), element by element otherwise.  In
+ *     any strides; they are accessed with 128-bit loads / stores, fastest when
+ *     base and row starts are 16-byte aligned (leading and batch strides
+ *     multiples of 8 for 16-bit types, of 4 for fp32).  In
  *     ucl_grouped_gemm the per-group pointers live on the device, where the
  *     host cannot inspect them: every one of them must be 16-byte aligned,
  *     except those of vectors indexed by m (PER_ROW_SCALE, COL_BROADCAST),
