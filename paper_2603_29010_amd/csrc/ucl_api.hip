@@ -79,6 +79,7 @@ struct Launch {
     const int64_t *M_g = nullptr;
     int64_t max_Mg = 0, sum_Mg = 0;
     int patch_c = 0;              // conv: the problem fits the resident-patch kernels built for pixels of this many channels (0: none)
+    int64_t cN = 0, cH = 0, cW = 0, str_h = 1, str_w = 1;    // conv dgrad: images, extents of the activations, strides
     bool ndirect_ok = false;      // B contiguous along N and small enough for 32-bit byte offsets: direct-copy kernels apply
     bool mdirect_ok = false;      // the same for A contiguous along M
 };
@@ -110,7 +111,16 @@ int64_t count_tiles(const Launch &L, int tm, int tn) {
         for (int g = 0; g < L.groups; ++g) t += (L.M_g[g] + tm - 1) / tm * tiles_n;
         return t;
     }
+    // (stride 1: the same as the general form)
+    if (L.mode == 3) return dgrad_tile_rows(L.cN, L.cH, L.cW, L.str_h, L.str_w, tm) * tiles_n;
     return L.batch * ((L.M + tm - 1) / tm) * tiles_n;
+}
+
+// Launch description of a data gradient: extents for the tile count, and the mean depth over the residue classes of a
+// strided convolution (every tap meets one class in stride_h * stride_w).
+void dgrad_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t stride_h, int64_t stride_w) {
+    L.cN = N; L.cH = H; L.cW = W; L.str_h = stride_h; L.str_w = stride_w;
+    if (stride_h * stride_w > 1) L.K = (L.K + stride_h * stride_w - 1) / (stride_h * stride_w);
 }
 
 // The wide epilogue path addresses a wave's row panel (up to 128 rows) with 32-bit byte offsets.
@@ -673,7 +683,7 @@ ucl_status run(const Launch &L, KParams &kp, const ucl_tuning *tune, void *strea
     } else {
         kp.tiles_m = (int32_t)((L.M + v->tile_m - 1) / v->tile_m);
         kp.tiles_per_batch = kp.tiles_m * kp.tiles_n;
-        total = (int64_t)kp.tiles_per_batch * L.batch;
+        total = L.mode == 3 ? count_tiles(L, v->tile_m, v->tile_n) : (int64_t)kp.tiles_per_batch * L.batch;
     }
     if (total >= (1ll << 31)) return fail(UCL_ERR_UNSUPPORTED, "problem needs %lld tiles; the grid is limited to 2^31-1", (long long)total);
     SplitPlan sp;
@@ -964,8 +974,10 @@ ucl_status launch_from_problem(const ucl_problem *p, Launch &L) {
     L.dtD = p->dt_out;
     if (L.mode == 2)
         L.patch_c = conv_patch_channels(p->cW, p->cC, p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
-    if (L.mode == 3)
+    if (L.mode == 3) {
         L.patch_c = conv_patch_channels(p->cW, p->cKout, p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
+        dgrad_launch(L, p->cN, p->cH, p->cW, p->stride_h, p->stride_w);
+    }
     if (L.mode == 1)
         for (int g = 0; g < L.groups; ++g) L.sum_Mg += L.M_g[g];
     return UCL_OK;
@@ -1133,8 +1145,12 @@ ucl_status ucl_conv2d_dgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     Launch L;
     L.mode = 3; L.M = M; L.N = C; L.K = Kg; L.la = 2; L.lb = 1; L.ndirect_ok = true; L.dt = dt_code(dtDy); L.dtD = dtDx;
     L.patch_c = conv_patch_channels(W, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
+    dgrad_launch(L, N, H, W, stride_h, stride_w);
     KParams kp;
     memset(&kp, 0, sizeof(kp));
+    // (the tiles that take longest start first)
+    kp.dg_reverse = dgrad_taps((int)stride_h - 1, (int)pad_h, (int)dil_h, (int)stride_h, (int)R).count >
+                    dgrad_taps(0, (int)pad_h, (int)dil_h, (int)stride_h, (int)R).count;
     if (ucl_status st = check_epilogue(epi, L, kp)) return st;
     kp.A = dy; kp.B = w; kp.D = dx;
     kp.a_bytes = N * P * Q * Kout * 2;

@@ -585,6 +585,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         t = xcd_remap(pc.tile, p.total_tiles);
         sk_k0 = pc.k0;
         sk_k1 = pc.k1;
+    } else if constexpr (MODE == 3 && LA == kIm2col) {
+        t = p.dg_reverse ? p.total_tiles - 1 - wg_id : wg_id;        // (dealt to the XCDs class by class, below)
     } else {
         t = xcd_remap(wg_id, p.total_tiles);
     }
@@ -593,6 +595,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     const char *Ab = (const char *)p.A;
     const char *Bb = (const char *)p.B;
     char *Db = (char *)p.D;
+    DgradClass dg{0, 0, 1, 1, 1, 0};                             // gathered data gradient: residue class and its taps
+    DgradTaps dg_h{0, 1, 1, 0, 0}, dg_w{0, 1, 1, 0, 0};
     if constexpr (MODE == 1) {
         group = find_group(gt.tile_start, p.groups, t);
         t -= gt.tile_start[group];
@@ -605,6 +609,12 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         Ab = uniform_ptr((const char *)p.A_g[group]);
         Bb = uniform_ptr((const char *)p.B_g[group]);
         Db = (char *)uniform_ptr((const char *)p.D_g[group]);
+    } else if constexpr (MODE == 3 && LA == kIm2col) {
+        dg = dgrad_class(t, p.M / (p.cP * p.cQ), p.cP, p.cQ, p.str_h, p.str_w, TM, p.tiles_n);
+        Mloc = p.M / (p.cP * p.cQ) * dg.Hc * dg.Wc;
+        band_raster(xcd_remap(dg.t, dg.tiles_m * p.tiles_n), dg.tiles_m, p.tiles_n, p.raster, tm, tn);
+        dg_h = dgrad_taps(dg.rh, p.pad_h, p.dil_h, p.str_h, p.K / (p.cS * p.cC));
+        dg_w = dgrad_taps(dg.rw, p.pad_w, p.dil_w, p.str_w, p.cS);
     } else {
         batch = t / p.tiles_per_batch;
         t -= batch * p.tiles_per_batch;
@@ -614,6 +624,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     }
     const int m0 = tm * TM, n0 = tn * TN;
     int k_len = p.K;
+    if constexpr (MODE == 3 && LA == kIm2col) k_len = dg_h.count * dg_w.count * p.cC;
     if constexpr ((MODE == 0 || MODE == 4) && !Cfg::PERSIST) {
         if (p.split_k > 1 || p.split_phase == 2) {
             // this slice's K range (a multiple of 64 long, so operand rows stay 16-byte aligned)
@@ -685,16 +696,17 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         for (int i = 0; i < A_ITERS; ++i) {
             int row = m0 + i * RPI + l_row;
             row = row < Mloc ? row : Mloc - 1;
-            const int q = row % p.cQ;
-            const int pq = row / p.cQ;
-            const int pp = pq % p.cP;
-            const int nb = pq / p.cP;
+            const int row_w = MODE == 3 ? dg.Wc : p.cQ, row_h = MODE == 3 ? dg.Hc : p.cP;
+            const int pq = row / row_w;
+            const int q = row - pq * row_w;
+            const int nb = pq / row_h;
+            const int pp = pq - nb * row_h;
             if constexpr (MODE == 3) {
-                // data gradient: the row is an INPUT pixel (h, w) = (pp, q); tap (r, s) pairs it with the
-                // gradient pixel ((h + pad - r*dil) / stride, ...) where that division is exact.  The
-                // gathered tensor is dy: "image" extents cH x cW = P x Q, cC = its channels.
-                a_h0[i] = pp + p.pad_h;
-                a_w0[i] = q + p.pad_w;
+                // data gradient: the row is pixel (pp, q) of the residue class; tap number (j, l) of the class pairs
+                // it with the gradient pixel (pp + q0_h - j dq_h, q + q0_w - l dq_w).  The gathered tensor is dy:
+                // "image" extents cH x cW = P x Q, cC = its channels.
+                a_h0[i] = pp + dg_h.q0;
+                a_w0[i] = q + dg_w.q0;
                 a_off[i] = (uint32_t)(nb * p.cH * p.cW * p.cC * 2);
             } else {
                 a_h0[i] = pp * p.str_h - p.pad_h;
@@ -705,8 +717,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         }
         a_ci = (kg_first + l_kc) % p.cC;
         const int tap = (kg_first + l_kc) / p.cC;
-        a_r = tap / p.cS;
-        a_s = tap % p.cS;
+        const int taps_w = MODE == 3 ? (dg_w.count > 0 ? dg_w.count : 1) : p.cS;
+        a_r = tap / taps_w;
+        a_s = tap % taps_w;
     }
     if constexpr (LB == kKContig) {
         const int rows = p.N - n0 < TN ? p.N - n0 : TN;
@@ -724,13 +737,13 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     const int nd_row = tid / CPRB;
     // Per-slot state of the two gathered forms of such a B stage.
     // MODE 3 (data gradient): GEMM row k = (r*S + s)*Ko + ko of B is filter row w[ko, r, s, :]: the slot
-    // keeps (ko, tap) of its row and steps ko by TK per k-tile.
+    // keeps (ko, tap) of its row and steps ko by TK per k-tile (gathered A: through the taps of its residue class).
     // MODE 4 (weight gradient): GEMM row k is output pixel (n, p, q), GEMM column (r, s, c): the slot's 8
     // columns are 8 channels of ONE tap (C is a multiple of 8), fixed for the whole loop; its pixel
     // steps by TK per k-tile.  Every slot reads x[n, p*stride - pad + r*dil, q*stride - pad + s*dil, c..c+7].
     constexpr bool kBGather = LB == kNDirect && (MODE == 3 || MODE == 4);
     int g_a[kBGather ? B_ITERS : 1], g_b[kBGather ? B_ITERS : 1];          // MODE 3: ko, tap   MODE 4: q, p
-    int g_dh[MODE == 4 && kBGather ? B_ITERS : 1], g_dw[MODE == 4 && kBGather ? B_ITERS : 1];
+    int g_dh[kBGather ? B_ITERS : 1], g_dw[MODE == 4 && kBGather ? B_ITERS : 1];      // (MODE 3: g_dh = tap number along w)
     uint32_t g_img[MODE == 4 && kBGather ? B_ITERS : 1];                   // byte offset of the slot's image
     if constexpr (LB == kNDirect && MODE == 3) {
         b_rsrc = buffer_rsrc(Bb + (int64_t)n0 * 2, (uint32_t)(p.b_bytes - (int64_t)n0 * 2));
@@ -739,8 +752,15 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
             const int row = i * RPIB + nd_row;
             const int chunk = (tid % CPRB) ^ nd_swz(row);
             b_off[i] = (uint32_t)(chunk * 16);
-            g_b[i] = (kg_first + row) / p.cC;
-            g_a[i] = kg_first + row - g_b[i] * p.cC;
+            const int tap = (kg_first + row) / p.cC;
+            g_a[i] = kg_first + row - tap * p.cC;
+            if constexpr (LA == kIm2col) {
+                const int j = tap / (dg_w.count > 0 ? dg_w.count : 1);
+                g_dh[i] = tap - j * dg_w.count;
+                g_b[i] = (dg_h.r0 + j * dg_h.step) * p.cS + dg_w.r0 + g_dh[i] * dg_w.step;
+            } else {
+                g_b[i] = tap;
+            }
         }
     } else if constexpr (LB == kNDirect && MODE == 4) {
         b_rsrc = buffer_rsrc(Bb, (uint32_t)p.b_bytes);
@@ -779,7 +799,15 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         if constexpr (kBGather && MODE == 3) {
             if (kok) off = (uint32_t)((g_a[i] * (int)p.ldb + g_b[i] * p.N) * 2) + b_off[i];
             g_a[i] += TK;
-            while (g_a[i] >= p.cC) { g_a[i] -= p.cC; ++g_b[i]; }
+            while (g_a[i] >= p.cC) {
+                g_a[i] -= p.cC;
+                if constexpr (LA == kIm2col) {
+                    g_b[i] += dg_w.step;
+                    if (++g_dh[i] == dg_w.count) { g_dh[i] = 0; g_b[i] += dg_h.step * p.cS - dg_w.count * dg_w.step; }
+                } else {
+                    ++g_b[i];
+                }
+            }
         } else if constexpr (kBGather && MODE == 4) {
             const int h = g_b[i] * p.str_h + g_dh[i], w = g_a[i] * p.str_w + g_dw[i];
             if (kok && (unsigned)h < (unsigned)p.cH && (unsigned)w < (unsigned)p.cW)
@@ -796,12 +824,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     auto a_gather_off = [&](auto i_, bool kok) __attribute__((always_inline)) -> uint32_t {
         constexpr int i = decltype(i_)::value;
         if constexpr (LA == kIm2col && MODE == 3) {
-            const int th = a_h0[i] - a_r * p.dil_h, tw = a_w0[i] - a_s * p.dil_w;
-            int hh = th, ww = tw;
-            bool ok = kok && th >= 0 && tw >= 0;
-            if (p.str_h != 1) { hh = th / p.str_h; ok = ok && hh * p.str_h == th; }
-            if (p.str_w != 1) { ww = tw / p.str_w; ok = ok && ww * p.str_w == tw; }
-            ok = ok && hh < p.cH && ww < p.cW;
+            const int hh = a_h0[i] - a_r * dg_h.dq, ww = a_w0[i] - a_s * dg_w.dq;
+            const bool ok = kok && (unsigned)hh < (unsigned)p.cH && (unsigned)ww < (unsigned)p.cW;
             return ok ? a_off[i] + (uint32_t)(((hh * p.cW + ww) * p.cC + a_ci) * 2) : kOobOffset;
         } else {
             return kOobOffset;
@@ -941,7 +965,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
             a_ci += TK;
             while (a_ci >= p.cC) {
                 a_ci -= p.cC;
-                if (++a_s == p.cS) { a_s = 0; ++a_r; }
+                if (++a_s == (MODE == 3 ? dg_w.count : p.cS)) { a_s = 0; ++a_r; }
             }
         } else {   // A contiguous along M: element (m, k) at k*lda + m
 #pragma unroll
@@ -1024,7 +1048,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
                     a_ci += TK;
                     while (a_ci >= p.cC) {
                         a_ci -= p.cC;
-                        if (++a_s == p.cS) { a_s = 0; ++a_r; }
+                        if (++a_s == (MODE == 3 ? dg_w.count : p.cS)) { a_s = 0; ++a_r; }
                     }
                 }
             }
@@ -1834,6 +1858,17 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         }
     };
     const int64_t d_batch_off = MODE == 1 ? 0 : (int64_t)batch * p.d_bs;
+    // Row of the output that row m of the (sub)problem is: itself, but for the residue classes of a strided data gradient.
+    const bool rows_scattered = MODE == 3 && LA == kIm2col && (p.str_h != 1 || p.str_w != 1);
+    auto out_row = [&](int m) __attribute__((always_inline)) -> int {
+        if constexpr (MODE == 3 && LA == kIm2col) {
+            if (rows_scattered) {
+                const int pq = m / dg.Wc, nb = pq / dg.Hc;
+                return (nb * p.cP + dg.rh + (pq - nb * dg.Hc) * p.str_h) * p.cQ + dg.rw + (m - pq * dg.Wc) * p.str_w;
+            }
+        }
+        return m;
+    };
 
     // ---- fused form: act(alpha * acc + bias[n] + beta * R[m,n]) as straight-line code ---------------
     // All block / pass loops of the epilogue are REAL loops: their bodies are re-executed from the
@@ -1855,7 +1890,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
             if (f.has_res) {
                 static_for<GRP>([&](auto u) {
                     const int m = m_blk + (pg + u) * RPP + e_row;
-                    res[u] = load8(res_base, f.res_dt & 0xff, (int64_t)m * f.res_ld,
+                    res[u] = load8(res_base, f.res_dt & 0xff, (int64_t)out_row(m) * f.res_ld,
                                    m < Mloc ? n_left : 0);
                 });
             }
@@ -1874,7 +1909,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = act_f32<ACT>(v[e], f.act_p0, f.act_p1);
-                store8(Db, dtD, d_batch_off + (int64_t)m * p.ldd + c.n, v, m < Mloc ? n_left : 0);
+                store8(Db, dtD, d_batch_off + (int64_t)out_row(m) * p.ldd + c.n, v, m < Mloc ? n_left : 0);
             });
         }
     };
@@ -2063,7 +2098,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
 
     if (f.enabled) {
         // uniform per wave: all 8-column groups of the wave exist and every access may be 128-bit
-        const bool fast_ok = dvec && (n0 + wn * WTN + WTN <= p.N) && (!f.has_res || (f.res_dt & 0x100)) &&
+        const bool fast_ok = dvec && !rows_scattered && (n0 + wn * WTN + WTN <= p.N) && (!f.has_res || (f.res_dt & 0x100)) &&
                              (!f.has_bias || (f.bias_dt & 0x100));
 #pragma unroll
         for (int e = 0; e < 8; ++e) bias8[e] = 0.f;
@@ -2203,13 +2238,13 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
                     const int nv = m < Mloc ? n_left : 0;
                     static_for<kMaxMat>([&](auto j) {
                         if (j < n_mat)
-                            mat[u][j] = load8(mat_base[j], mat_dt[j] & 0xff, (int64_t)m * mat_ld[j], nv);
+                            mat[u][j] = load8(mat_base[j], mat_dt[j] & 0xff, (int64_t)out_row(m) * mat_ld[j], nv);
                     });
                 });
                 static_for<GRP_I>([&](auto u) {
                     const int row = (pg + u) * RPP + e_row;
                     const int m = m_blk + row;
-                    c.m = m;
+                    c.m = out_row(m);
                     c.nvalid = m < Mloc ? n_left : 0;
                     float v[8];
                     staged_row(row, v);
@@ -2227,7 +2262,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
                         });
                         apply_step(v, get_step(s), c, pre, has_pre);
                     }
-                    store8(Db, dtD, d_batch_off + (int64_t)m * p.ldd + c.n, v, c.nvalid);
+                    store8(Db, dtD, d_batch_off + c.m * p.ldd + c.n, v, c.nvalid);
                 });
             }
         }
