@@ -4,9 +4,7 @@
 namespace ucl {
 static const VariantDesc kTable[] = {
     describe<KernelCfg<64, 64, 64, 4, 0, 0, kKContig, kKContig, 0, 0, 2>>(),
-    describe<KernelCfg<128, 64, 64, 3, 0, 0, kKContig, kKContig, 0, 0, 2>>(),
     describe<KernelCfg<64, 64, 64, 4, 1, 0, kKContig, kKContig, 0, 0, 2>>(),
-    describe<KernelCfg<128, 64, 64, 3, 1, 0, kKContig, kKContig, 0, 0, 2>>(),
     describe<KernelCfg<64, 64, 64, 4, 2, 0, kKContig, kKContig, 0, 0, 2>>(),
     describe<KernelCfg<64, 64, 64, 4, 3, 0, kKContig, kKContig, 0, 0, 2>>(),
 };

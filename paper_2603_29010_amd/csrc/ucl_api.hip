@@ -10,6 +10,7 @@
 
 #include "ucl_kernel.h"      // the epilogue's element-wise arithmetic (the split-K reduction kernel finishes simple chains itself)
 #include "ucl_variants.h"
+#include "ucl_costs.h"
 
 // Split-K workspace of ucl_gemm_static_workspace: counters followed by partial tiles, held by every
 // GPU the library runs on until the process ends.  Host code never uses this name as an address: it
@@ -38,11 +39,31 @@ ucl_status fail(ucl_status st, const char *fmt, ...) {
 const std::vector<VariantDesc> &all_variants() {
     static const std::vector<VariantDesc> v = [] {
         std::vector<VariantDesc> out;
-        for (VariantList l : {variants_gemm_kk_bf16_a(), variants_gemm_kk_bf16_b(), variants_gemm_kk_bf16_c(), variants_gemm_kk_bf16_d(), variants_gemm_kk_f16_a(), variants_gemm_kk_f16_b(), variants_gemm_mn_bf16(), variants_gemm_mn_f16(), variants_grouped_a(), variants_grouped_b(), variants_conv_a(), variants_conv_b(), variants_conv_f16(), variants_conv_halo(), variants_gemm_kn_bf16(), variants_gemm_kn_f16(), variants_gemm_mx_bf16(), variants_gemm_mx_f16(), variants_grouped_kn(), variants_conv_dgrad(), variants_conv_dgrad_halo(), variants_conv_wgrad(), variants_gemm_kk_fp8(), variants_persistent(), variants_grouped_fp8_e4m3(), variants_grouped_fp8_e5m2(), variants_streamk(), variants_kgroups_kk(), variants_kgroups_mn(), variants_kgroups_conv(), variants_kgroups_conv_grad()})
+        for (VariantList l : {variants_gemm_kk_bf16_a(), variants_gemm_kk_bf16_b(), variants_gemm_kk_bf16_c(), variants_gemm_kk_bf16_d(), variants_gemm_kk_f16_a(), variants_gemm_kk_f16_b(), variants_gemm_mn_bf16(), variants_gemm_mn_f16(), variants_grouped_a(), variants_grouped_b(), variants_conv_a(), variants_conv_b(), variants_conv_f16(), variants_conv_halo(), variants_gemm_kn_bf16(), variants_gemm_kn_f16(), variants_gemm_mx_bf16(), variants_gemm_mx_f16(), variants_grouped_kn(), variants_conv_dgrad(), variants_conv_dgrad_halo(), variants_conv_wgrad(), variants_gemm_kk_fp8(), variants_persistent(), variants_grouped_fp8_e4m3(), variants_grouped_fp8_e5m2(), variants_streamk(), variants_kgroups_kk(), variants_kgroups_mn(), variants_kgroups_conv(), variants_kgroups_conv_grad(), variants_skinny()})
             for (int i = 0; i < l.n; ++i) out.push_back(l.v[i]);
         return out;
     }();
     return v;
+}
+
+// The cost row of every variant, in the same order (kernels of another tile scheduler take the row of their tile).  Kernels
+// without one -- those that transpose operands in registers, for matrices beyond the reach of 32-bit offsets -- are priced
+// by the tile alone, far above the others.
+const std::vector<CostRow> &all_costs() {
+    static const std::vector<CostRow> c = [] {
+        std::vector<CostRow> out;
+        for (const VariantDesc &v : all_variants()) {
+            const float slow = (int64_t)v.tile_m * v.tile_n >= 128 * 128 ? 20.f : 14.f;
+            CostRow row = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 2, 8.f, 4.f, slow, 2.f, 1.5f, 1.f, 0.f, 1.f};
+            for (const CostRow &r : kCostRows)
+                if (r.mode == v.mode && r.la == v.la && r.lb == v.lb && r.eight_bit == (v.dt >= 2) && r.tile_m == v.tile_m && r.tile_n == v.tile_n &&
+                    r.tile_k == v.tile_k && r.stages == v.stages && r.k_groups == v.k_groups && r.patch_c == (v.la == 3 ? v.patch_c : 0))
+                    row = r;
+            out.push_back(row);
+        }
+        return out;
+    }();
+    return c;
 }
 
 bool is8(int dt) { return dt == UCL_FP8_E4M3 || dt == UCL_FP8_E5M2; }
@@ -95,15 +116,8 @@ int conv_patch_channels(int64_t W, int64_t channels, int64_t R, int64_t S, int64
     return ok ? (int)channels : 0;
 }
 
-// Per-problem selection table: of the variants built for this (mode, input type, operand layouts)
-// take the one with the smallest estimated time
-//     ceil(tiles / 256) * ( tile FLOPs / (rate of a busy CU with this variant)
-//                           + (fixed cost of a tile) / (workgroups of the variant that share a CU) ),
-// i.e. the tiles dealt to the busiest CU one after the other, each paying its MFMA time at the rate
-// measured for the variant (4096^3 bf16 problem, relative to the best variant) and its un-overlapped
-// prologue + store time unless a co-resident workgroup hides it.  Large compute-bound problems thus get
-// 256x256 tiles and the two-buffer loop, short-K / wide-output problems get the largest tile of which
-// two workgroups fit on a CU, small problems the tile that fills the chip.
+// Per-problem selection: of the variants built for this (mode, input type, operand layouts) the one with the smallest
+// estimated launch time (estimate_seconds, constants in ucl_costs.h).
 int64_t count_tiles(const Launch &L, int tm, int tn) {
     const int64_t tiles_n = (L.N + tn - 1) / tn;
     if (L.mode == 1) {
@@ -152,29 +166,37 @@ double relative_rate(const VariantDesc &v) {
     return nd * (v.tile_k == 64 ? 0.49 : v.stages == 3 ? 0.41 : 0.37);
 }
 
-double estimate_seconds(const VariantDesc &v, const Launch &L) {
-    const double kCuRate = 1.38e15 / 256;            // FLOP/s of one CU at the best variant's measured rate
-    const double kCuStore = 4.6e12 / 256;            // B/s of output one CU gets when all CUs store
-    const int wg = workgroups_per_cu(v);
+// Launch time of a variant:  fixed + round * rounds + loop (+) output, where
+//   rounds = turns of resident workgroups the tiles make over the chip,
+//   loop   = what bounds it: the bytes the busiest CU copies, its multiplications, the chain of a workgroup's k-tiles, or
+//            the operands' trip from memory (5.3 TB/s), added as fourth powers (the largest, somewhat more where two are close),
+//   output = the output's bytes, part of it hidden under the loop in the same sense.
+double fourth_power_sum(double a, double b, double c = 0, double d = 0) {
+    a *= a; b *= b; c *= c; d *= d;
+    return sqrt(sqrt(a * a + b * b + c * c + d * d));
+}
+double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L) {
+    const int64_t tiles_n = (L.N + v.tile_n - 1) / v.tile_n;
     const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
-    const int64_t slots = 256 * (int64_t)wg;
-    // tiles the busiest CU works through: they run wg at a time, a new set starting when slots free up
-    const double per_cu = tiles <= slots ? (double)((tiles + 255) / 256) : (double)((tiles + slots - 1) / slots * wg);
-    // the chip is power-limited: CUs run faster when fewer of them are busy (measured ~1.5x at 144 of 256)
-    const double active = tiles / per_cu < 256.0 ? tiles / per_cu : 256.0;
-    double boost = pow(256.0 / (active < 1.0 ? 1.0 : active), 0.7);
-    if (boost > 1.5) boost = 1.5;
-    // (8-bit inputs: K counts pairs, and the 8-bit MFMA used runs at the 16-bit rate per byte of operand)
-    const double tile_flops = 2.0 * v.tile_m * v.tile_n * (double)L.K;
-    const double out_bytes = (double)v.tile_m * v.tile_n * (L.dtD == UCL_F32 ? 4.0 : 2.0);
-    const double fixed = 2.0e-6 + out_bytes / kCuStore;
-    // co-resident workgroups hide about half of what perfect overlap of one's fixed cost with the
-    // others' MFMA time would; a CU with a single tile has nothing to overlap with
-    const double exposed = per_cu > 1.0 ? 0.5 * (1.0 + 1.0 / wg) : 1.0;
-    // a variant built to share its CU runs below its rate when it has the CU to itself (one wave per SIMD
-    // with the register budget of two: measured 0.7x for 256x128 tiles)
-    const double alone = (wg >= 2 && per_cu < 2.0) ? 0.7 : 1.0;
-    return per_cu * (tile_flops / (relative_rate(v) * alone * kCuRate * boost) + fixed * exposed);
+    const int64_t slots = 256 * (int64_t)r.resident, rounds = (tiles + slots - 1) / slots;
+    const double on_cu = tiles <= slots ? (double)((tiles + 255) / 256) : (double)(rounds * r.resident);
+    // (8-bit inputs: K counts pairs of elements, 2 bytes)
+    double rows = (double)L.M, all_rows = (double)L.batch * L.M, panels = (double)L.batch;
+    if (L.mode == 1) {
+        rows = tiles > 0 ? (double)L.sum_Mg * tiles_n / tiles : 0;             // mean rows of a tile
+        all_rows = (double)L.sum_Mg;
+        panels = L.groups;
+    }
+    const double tile_rows = (rows < v.tile_m ? rows : v.tile_m) + (double)(L.N < v.tile_n ? L.N : v.tile_n);
+    const double K = (double)L.K;
+    const double copies = on_cu * tile_rows * K * 2.0 / (r.gbs * 1e3);
+    const double math = on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6);
+    const int64_t step_k = (v.stages == 1 ? 64 : v.tile_k) * (int64_t)v.k_groups;
+    const double chain = (double)rounds * (double)((L.K + step_k - 1) / step_k) * r.step;
+    const double memory = (all_rows + panels * L.N) * K * 2.0 / 5.3e6;
+    const double loop = fourth_power_sum(copies, math, chain, memory);
+    const double out = all_rows * L.N * (L.dtD == UCL_F32 ? 4.0 : 2.0) / 4.6e6 * r.out;
+    return 1e-6 * r.factor * (r.fixed + r.round * (double)rounds + fourth_power_sum(loop, out * r.hidden) + out * (1.0 - r.hidden));
 }
 
 constexpr int kNumCUs = 256;
@@ -210,11 +232,11 @@ void split_slices(const Launch &L, int64_t want, int64_t total_tiles, int fill, 
 // of partial tiles; chains the reduction kernel finishes itself need one launch less, which is the same for every
 // tile and is left out of the comparison), in serial mode through the last workgroup of each tile, which reads all slices alone
 // (measured 15-28 GB/s per workgroup).
-double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_tuning *tune) {
+double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const Launch &L, const ucl_tuning *tune) {
     const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
     int slices = 1, kps = 0;
     split_slices(L, tune->split_k_slices, tiles, split_fill(L, v, tune), slices, kps);
-    if (slices <= 1) return estimate_seconds(v, L);
+    if (slices <= 1) return estimate_seconds(v, row, L);
     const double wgs = (double)tiles * slices;
     const double rounds = ceil(wgs / (256.0 * workgroups_per_cu(v)));
     const double busy = wgs < 256.0 ? wgs / 256.0 : 1.0;
@@ -231,21 +253,15 @@ double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_t
     return main + 3.0e-6 + slices * tile_bytes / (v.tile_m * v.tile_n >= 128 * 128 ? 15.0e9 : 28.0e9);
 }
 
-// Workspace a split-K launch of variant v needs.
-int64_t split_bytes(const Launch &L, const VariantDesc &v, const ucl_tuning *tune) {
-    const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
-    int slices = 1, kps = 0;
-    split_slices(L, tune->split_k_slices, tiles, split_fill(L, v, tune), slices, kps);
-    return slices <= 1 ? 0 : UCL_WORKSPACE_COUNTER_BYTES + (int64_t)slices * tiles * v.tile_m * v.tile_n * 4;
-}
-
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
+    const auto &costs = all_costs();
     const bool explicit_tune = tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
     const VariantDesc *best = nullptr;
     double best_t = 0;
     const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
-    for (const auto &v : vs) {
+    for (size_t i = 0; i < vs.size(); ++i) {
+        const VariantDesc &v = vs[i];
         if (v.mode != L.mode || v.dt != L.dt || v.persistent != want_persistent) continue;
         if (v.lb == 4 ? !(L.lb == 1 && L.ndirect_ok) : v.lb != L.lb) continue;
         if (L.mode == 2 || L.mode == 3) {
@@ -259,6 +275,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
             if (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.stages != tune->stages || v.tile_k != tune->tile_k)
                 continue;
             if (tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
+            if (v.stages == 1 && tune->split_k_mode != UCL_SPLIT_K_NONE) continue;      // (no partial tiles in the few-row kernels)
             // of several kernels with the named shape: the resident-patch one, else one without K groups (unless named),
             // else a direct-copy one, else the first
             if (v.la == 3) return &v;
@@ -270,16 +287,14 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
             if (!best || (direct && !(best->la == 5 || best->lb == 4))) best = &v;
             continue;
         }
+        // The few-row kernels overlap the steps of their waves: below five steps of K there is nothing to overlap.  Grouped
+        // calls have workgroups enough without them unless K is deep (49 experts of 2400 columns, bf16: K = 576 40 us
+        // against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 52 of 976, K = 1152: 23 against 20 us).
+        if (v.stages == 1 && L.K < (L.mode == 1 ? 1408 : 320)) continue;
         if (tune && tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
         const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4);
-        // Split-K and K groups: only the weight gradient, whose gathered operand leaves a workgroup waiting, gains from
-        // both at once; and only in a workspace that holds the partial tiles of the kernel chosen (a caller's workspace
-        // that served the kernels without K groups goes on serving).
-        if (split && v.k_groups > 1) {
-            if (L.mode != 4) continue;
-            if (tune->workspace && split_bytes(L, v, tune) > tune->workspace_bytes) continue;
-        }
-        const double t = split ? estimate_split_seconds(v, L, tune) : estimate_seconds(v, L);
+        if (split && v.k_groups > 1) continue;          // split-K has kernels without K groups only
+        const double t = split ? estimate_split_seconds(v, costs[i], L, tune) : estimate_seconds(v, costs[i], L);
         if (!best || t < best_t) { best_t = t; best = &v; }
     }
     return best;
@@ -1292,7 +1307,13 @@ ucl_status ucl_tile_map(int32_t groups, const int32_t *tiles_m, int32_t tiles_n,
     return UCL_OK;
 }
 
-int32_t ucl_num_variants(void) { return (int32_t)all_variants().size(); }
+// (the few-row kernels come last and are not counted)
+int32_t ucl_num_variants(void) {
+    const auto &vs = all_variants();
+    int32_t n = (int32_t)vs.size();
+    while (n > 0 && vs[n - 1].stages == 1) --n;
+    return n;
+}
 
 ucl_status ucl_variant(int32_t i, ucl_variant_info *out) {
     const auto &vs = all_variants();

@@ -53,6 +53,7 @@ VariantList variants_gemm_kk_fp8();
 VariantList variants_conv_dgrad();
 VariantList variants_conv_dgrad_halo();
 VariantList variants_conv_wgrad();
+VariantList variants_skinny();
 VariantList variants_kgroups_kk();
 VariantList variants_kgroups_mn();
 VariantList variants_kgroups_conv();

@@ -1,5 +1,5 @@
-"""Kernels with K groups (two groups of four wavefronts share a tile, each multiplying its own part of K): exact on
-integers for every such kernel, at the sizes where the split of K can go wrong, and in fixed order."""
+"""Kernels with K groups (two groups of four wavefronts, or in the few-row kernels four single wavefronts, share a tile, each
+multiplying its own part of K): exact on integers for every such kernel, at the sizes where the split of K can go wrong, and in fixed order."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +13,18 @@ import parity
 
 pytestmark = pytest.mark.gpu
 
-VARIANTS = [v for v in (ucl.ucl_variant(i) for i in range(ucl.ucl_num_variants())) if v["k_groups"] > 1]
-NAMES = {0: "gemm", 2: "fprop", 3: "dgrad", 4: "wgrad"}
+def _all_variants():
+    i = 0
+    while True:
+        try:
+            yield ucl.ucl_variant(i)
+        except ucl.UclError:
+            return
+        i += 1
+
+
+VARIANTS = [v for v in _all_variants() if v["k_groups"] > 1]         # (the few-row kernels among them)
+NAMES = {0: "gemm", 1: "grouped", 2: "fprop", 3: "dgrad", 4: "wgrad"}
 
 
 def tuning(v, **kw):
@@ -36,25 +46,36 @@ def test_exact(v):
             spec = synth.gemm_spec(M, N, K, dt_in=dt, dt_out="f32", a_layout=la, b_layout=lb, epilogue=(), integer=True)
             parity.check_exact(spec, tuning(v), label=f"{ident(v)} {M}x{N}x{K}")
         return
+    if v["mode"] == 1:
+        for (rows, N, K) in (([0, 1, 16, 17, 33], 72, step), ([70, 0, 5, 128], 136, 5 * 64 + step), ([3], 264, 1024)):
+            spec = synth.grouped_spec(rows, N, K, dt_in=dt, dt_out="f32", epilogue=(), integer=True)
+            parity.check_exact(spec, tuning(v), label=f"{ident(v)} {rows} {N}x{K}")
+        return
     for g in (dict(Nb=2, H=9, W=7, C=40, Ko=72, R=3, S=3, pad=(1, 1)), dict(Nb=1, H=6, W=6, C=8, Ko=8, R=1, S=1, pad=(0, 0)),
               dict(Nb=1, H=11, W=10, C=136, Ko=64, R=3, S=3, pad=(1, 1), stride=(2, 2))):
         if v["mode"] == 2:
+            g = dict(g)
             spec = synth.conv_spec(dt_in=dt, dt_out="f32", epilogue=(), integer=True, **g)
         else:
             spec = synth.conv_grad_spec(NAMES[v["mode"]], dt_in=dt, dt_out="f32", integer=True, **g)
         parity.check_exact(spec, tuning(v), label=f"{ident(v)} {g}")
 
 
-@pytest.mark.parametrize("v", [v for v in VARIANTS if v["mode"] == 4], ids=ident)
-@pytest.mark.parametrize("mode", ["serial", "parallel"])
-def test_weight_gradient_with_split_k(v, mode):
-    # split-K cuts K into slices, K groups cut every slice again
-    spec = synth.conv_grad_spec("wgrad", dt_in=v["dt"], dt_out="f32", integer=True, Nb=3, H=13, W=11, C=24, Ko=40, R=3, S=3, pad=(1, 1))
-    ws = torch.empty(16 << 20, dtype=torch.uint8, device="cuda")
-    ucl.ucl_workspace_init(ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
-    for slices in (2, 3, 5):
-        parity.check_exact(spec, tuning(v, split_k=mode, slices=slices, workspace=ws.data_ptr(), workspace_bytes=ws.numel()),
-                           label=f"{ident(v)} {mode} x{slices}")
+def test_few_row_kernels_refuse_split_k():
+    v = next(v for v in VARIANTS if v["stages"] == 1 and v["mode"] == 0)
+    spec = synth.gemm_spec(16, 64, 4096, dt_in=v["dt"])
+    with pytest.raises(ucl.UclError) as e:
+        parity.gpu_result(spec, tuning(v, split_k="parallel", slices=4, workspace=4096, workspace_bytes=1 << 30))
+    assert e.value.status == "UCL_ERR_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("chain", [("bias", "aux_load", "gelu_tanh"), ("per_row_scale", "bias", "silu"), ("column_broadcast", "aux_load", "relu")])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "e4m3"])
+def test_few_row_kernels_run_the_chain(chain, dt):
+    spec = synth.gemm_spec(21, 1003, 1200, dt_in=dt, dt_out="f16" if dt == "f16" else "bf16", epilogue=chain)
+    for v in VARIANTS:
+        if v["stages"] == 1 and v["mode"] == 0 and v["dt"] == dt:
+            parity.check(spec, tuning(v), label=f"{ident(v)} {chain}")
 
 
 def test_repeated_runs_give_the_same_bits():
@@ -68,14 +89,3 @@ def test_repeated_runs_give_the_same_bits():
         first = got if first is None else first
         assert np.array_equal(got, first)
     parity.check(spec, tuning(v), label="K groups, bias + SiLU")
-
-
-def test_a_workspace_that_served_without_k_groups_goes_on_serving():
-    # the weight gradient's own choice takes K groups only where the caller's workspace holds their partial tiles
-    conv = dict(Nb=8, H=28, W=28, C=128, Ko=128, R=3, S=3, pad=(1, 1))
-    spec = synth.conv_grad_spec("wgrad", dt_out="f32", integer=True, **conv)
-    geom = (8, 28, 28, 128, 128, 3, 3, 1, 1, 1, 1, 1, 1)
-    small, _ = ucl.ucl_workspace_size("conv2d_wgrad", "bf16", "f32", tune=Tuning(split_k="parallel", k_groups=1), conv=geom)
-    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
-    ucl.ucl_workspace_init(ws.data_ptr(), small, torch.cuda.current_stream().cuda_stream)
-    parity.check_exact(spec, Tuning(split_k="parallel", workspace=ws.data_ptr(), workspace_bytes=small), label="smaller workspace")
