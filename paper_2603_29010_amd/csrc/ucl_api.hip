@@ -253,12 +253,77 @@ double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const La
     return main + 3.0e-6 + slices * tile_bytes / (v.tile_m * v.tile_n >= 128 * 128 ? 15.0e9 : 28.0e9);
 }
 
+// Weight gradient: kernel and slices of a parallel split-K call that leaves the slices to the library, chosen together.
+// Its K (output pixels) is deep, its output small: what decides is how many k-tiles a workgroup chains (0.33 us each of the
+// 64x64x32 kernel, whose four workgroups per CU hide the gathered operand best) against the bytes of partial tiles.
+// Measured against one or two workgroups per CU of the tile the general split model liked (440 geometries): 13 % in the
+// geometric mean; 64 <- 1152 columns over 117978 pixels 82 -> 43 us, 256 <- 576 over 4312 pixels 25.6 -> 16.0 us.
+struct WgradChoice {
+    const VariantDesc *v = nullptr;
+    int slices = 1, k_per_slice = 0;
+};
+double estimate_wgrad_seconds(const VariantDesc &v, const CostRow &r, const Launch &L, int slices, int64_t k_per_slice) {
+    const int64_t wgs = L.batch * ((L.M + v.tile_m - 1) / v.tile_m) * ((L.N + v.tile_n - 1) / v.tile_n) * slices;
+    const int64_t slots = 256 * (int64_t)r.resident, rounds = (wgs + slots - 1) / slots;
+    const double on_cu = wgs <= slots ? (double)((wgs + 255) / 256) : (double)(rounds * r.resident);
+    const double tile_rows = (double)(L.M < v.tile_m ? L.M : v.tile_m) + (double)(L.N < v.tile_n ? L.N : v.tile_n), K = (double)k_per_slice;
+    const double loop = fourth_power_sum(on_cu * tile_rows * K * 2.0 / (r.gbs * 1e3), on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6),
+                                         (double)rounds * (double)((k_per_slice + v.tile_k - 1) / v.tile_k) * r.step);
+    double t = r.fixed + r.round * (double)rounds + loop;
+    if (slices > 1) {
+        SplitCostRow s = {0, 0, 0, 0, 2.f, 2.4f};
+        for (const SplitCostRow &c : kWgradSplitRows)
+            if (c.tile_m == v.tile_m && c.tile_n == v.tile_n && c.tile_k == v.tile_k && c.stages == v.stages) s = c;
+        t += s.fixed + (double)wgs * v.tile_m * v.tile_n * 4.0 / (s.tbs * 1e6);
+    }
+    return 1e-6 * t;
+}
+WgradChoice choose_wgrad_split(const Launch &L, const ucl_tuning *tune) {
+    const bool named = tune->tile_m || tune->tile_n || tune->tile_k || tune->stages;
+    const int64_t kt = (L.K + 63) / 64;
+    WgradChoice best;
+    double best_t = 0;
+    for (size_t i = 0; i < all_variants().size(); ++i) {
+        const VariantDesc &v = all_variants()[i];
+        if (v.mode != 4 || v.dt != L.dt || v.persistent) continue;
+        if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
+        const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
+        // no split, a few slices, and what fills the chip with one to eight workgroups per CU
+        const int64_t fills[] = {1, 2 * tiles, 4 * tiles, 256, 512, 768, 1024, 1536, 2048};
+        for (int64_t fill : fills) {
+            int64_t want = (fill + tiles - 1) / tiles;
+            if (want > kt / 2) want = kt / 2;
+            if (want < 1) want = 1;
+            int slices = 1, kps = 0;
+            split_slices(L, want, tiles, 0, slices, kps);
+            const double t = estimate_wgrad_seconds(v, all_costs()[i], L, slices, slices > 1 ? kps : L.K);
+            if (!best.v || t < best_t) {
+                best_t = t;
+                best.v = &v;
+                best.slices = slices;
+                best.k_per_slice = kps;
+            }
+        }
+    }
+    if (!best.v) return best;
+    // A caller's workspace that holds the partial tiles of the general rule, but not these, goes on serving that rule.
+    const int64_t tiles = count_tiles(L, best.v->tile_m, best.v->tile_n);
+    const int64_t bytes = best.slices <= 1 ? 0 : UCL_WORKSPACE_COUNTER_BYTES + (int64_t)best.slices * tiles * best.v->tile_m * best.v->tile_n * 4;
+    if (tune->workspace && bytes > tune->workspace_bytes) best.v = nullptr;
+    return best;
+}
+bool wgrad_split_left_open(const Launch &L, const ucl_tuning *tune) {
+    return L.mode == 4 && tune && tune->split_k_mode == UCL_SPLIT_K_PARALLEL && tune->split_k_slices == 0 && tune->scheduler == UCL_SCHED_DEFAULT;
+}
+
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
     const auto &costs = all_costs();
     const bool explicit_tune = tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
     const VariantDesc *best = nullptr;
     double best_t = 0;
+    if (!explicit_tune && wgrad_split_left_open(L, tune))
+        if (const VariantDesc *v = choose_wgrad_split(L, tune).v) return v;
     const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
     for (size_t i = 0; i < vs.size(); ++i) {
         const VariantDesc &v = vs[i];
@@ -294,7 +359,8 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         if (tune && tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
         const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4);
         if (split && v.k_groups > 1) continue;          // split-K has kernels without K groups only
-        const double t = split ? estimate_split_seconds(v, costs[i], L, tune) : estimate_seconds(v, costs[i], L);
+        const double t = split ? estimate_split_seconds(v, costs[i], L, tune)
+                         : L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         if (!best || t < best_t) { best_t = t; best = &v; }
     }
     return best;
@@ -639,7 +705,14 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
     if (L.mode != 0 && L.mode != 4) return fail(UCL_ERR_UNSUPPORTED, "split-K is built for gemm, batched_gemm and conv2d_wgrad");
     if (tune->scheduler == UCL_SCHED_PERSISTENT)
         return fail(UCL_ERR_UNSUPPORTED, "split-K and the persistent scheduler cannot be combined");
-    split_slices(L, tune->split_k_slices, total_tiles, split_fill(L, v, tune), sp.slices, sp.k_per_slice);
+    WgradChoice w;
+    if (wgrad_split_left_open(L, tune)) w = choose_wgrad_split(L, tune);
+    if (w.v == &v) {
+        sp.slices = w.slices;
+        sp.k_per_slice = w.k_per_slice;
+    } else {
+        split_slices(L, tune->split_k_slices, total_tiles, split_fill(L, v, tune), sp.slices, sp.k_per_slice);
+    }
     if (sp.slices <= 1) { sp = SplitPlan(); return UCL_OK; }
     if (total_tiles > UCL_SPLIT_K_MAX_TILES)
         return fail(UCL_ERR_UNSUPPORTED, "split-K serves at most %d output tiles (this problem has %lld)", UCL_SPLIT_K_MAX_TILES, (long long)total_tiles);
