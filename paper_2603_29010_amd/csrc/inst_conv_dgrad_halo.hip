@@ -9,6 +9,8 @@ static const VariantDesc kTable[] = {
     describe<KernelCfg<256, 64, 32, 4, 0, 3, kHalo, kNDirect, 0, 64>>(),
     describe<KernelCfg<256, 128, 32, 4, 0, 3, kHalo, kNDirect, 0, 64>>(),
     describe<KernelCfg<256, 64, 32, 4, 1, 3, kHalo, kNDirect, 0, 64>>(),
+    describe<KernelCfg<128, 64, 32, 4, 1, 3, kHalo, kNDirect>>(),
+    describe<KernelCfg<256, 128, 32, 4, 1, 3, kHalo, kNDirect, 0, 64>>(),
 };
 VariantList variants_conv_dgrad_halo() { return {kTable, (int)(sizeof(kTable) / sizeof(kTable[0]))}; }
 }  // namespace ucl

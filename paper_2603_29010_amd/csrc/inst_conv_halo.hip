@@ -8,6 +8,7 @@ static const VariantDesc kTable[] = {
     describe<KernelCfg<256, 128, 32, 4, 0, 2, kHalo, kKContig, 0, 128>>(),
     describe<KernelCfg<128, 64, 32, 4, 0, 2, kHalo, kKContig, 0, 128>>(),
     describe<KernelCfg<256, 128, 32, 4, 1, 2, kHalo, kKContig, 0, 128>>(),
+    describe<KernelCfg<128, 64, 32, 4, 1, 2, kHalo, kKContig, 0, 128>>(),
 };
 VariantList variants_conv_halo() { return {kTable, (int)(sizeof(kTable) / sizeof(kTable[0]))}; }
 }  // namespace ucl

@@ -6,6 +6,12 @@ static const VariantDesc kTable[] = {
     describe<KernelCfg<64, 64, 32, 3, 1, 0, kMDirect, kKContig>>(),
     describe<KernelCfg<256, 256, 64, 2, 1, 0, kMDirect, kNDirect>>(),
     describe<KernelCfg<64, 64, 32, 3, 1, 0, kMDirect, kNDirect>>(),
+    describe<KernelCfg<128, 128, 32, 4, 1, 0, kMDirect, kKContig>>(),
+    describe<KernelCfg<128, 128, 64, 2, 1, 0, kMDirect, kKContig>>(),
+    describe<KernelCfg<64, 64, 64, 4, 1, 0, kMDirect, kKContig>>(),
+    describe<KernelCfg<128, 128, 32, 4, 1, 0, kMDirect, kNDirect>>(),
+    describe<KernelCfg<128, 128, 64, 2, 1, 0, kMDirect, kNDirect>>(),
+    describe<KernelCfg<64, 64, 64, 4, 1, 0, kMDirect, kNDirect>>(),
 };
 VariantList variants_gemm_mx_f16() { return {kTable, (int)(sizeof(kTable) / sizeof(kTable[0]))}; }
 }  // namespace ucl
