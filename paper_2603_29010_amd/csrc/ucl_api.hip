@@ -366,6 +366,33 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     return best;
 }
 
+// A 1x1 convolution at unit stride without padding IS a GEMM over the pixels: its forward pass (pixels x channels times filter
+// rows) and its data gradient (output gradient times the filter, contiguous along N) run on the GEMM kernels, which copy rows
+// instead of gathering taps and come in more tiles.  Convolution kernels that the caller names, their iterator or another
+// scheduler among it, are taken as named; a GEMM tile can be named too.
+bool is_plain_gemm(int64_t R, int64_t S, int64_t pad_h, int64_t pad_w, int64_t stride_h, int64_t stride_w) {
+    return R == 1 && S == 1 && pad_h == 0 && pad_w == 0 && stride_h == 1 && stride_w == 1;
+}
+Launch gemm_of_conv(const Launch &conv) {
+    Launch g;
+    g.M = conv.M; g.N = conv.N; g.K = conv.K;
+    g.la = 0;
+    g.lb = conv.mode == 3 ? 1 : 0;
+    g.ndirect_ok = conv.mode == 3;             // (the filter is below 2 GiB)
+    g.dt = conv.dt; g.dtD = conv.dtD;
+    return g;
+}
+// (Measured over 60 drawn layers: data gradients 1.41x, forward passes 1.11x.  Forward with one 64-wide k-tile is all output
+// and residual: the convolution kernels' choice is 10 % ahead there, 22.5 against 25.1 us on 36 x 60 x 60 x 64 -> 128.)
+bool takes_gemm(const Launch &conv, const Launch &gemm, const ucl_tuning *tune) {
+    if (conv.mode == 2 && conv.K < 128 && !(tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages))) return false;
+    if (!tune) return true;
+    if (tune->split_k_mode != UCL_SPLIT_K_NONE || tune->split_k_slices != 0 || tune->scheduler != UCL_SCHED_DEFAULT || tune->iterator != UCL_ITER_DEFAULT) return false;
+    const bool named = tune->tile_m || tune->tile_n || tune->tile_k || tune->stages;
+    if (named && select_variant(conv, tune)) return false;
+    return select_variant(gemm, tune) != nullptr;
+}
+
 int default_raster(const VariantDesc &v, const Launch &L) {
     (void)L;
     // bands of ~1024 rows: an XCD's run of 32 consecutive tiles then covers a near-square block
@@ -1197,6 +1224,13 @@ ucl_status ucl_conv2d_fprop(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     kp.pad_h = (int32_t)pad_h; kp.pad_w = (int32_t)pad_w; kp.str_h = (int32_t)stride_h; kp.str_w = (int32_t)stride_w;
     kp.dil_h = (int32_t)dil_h; kp.dil_w = (int32_t)dil_w;
     kp.d_vec = aligned16(y) && (Kout % (16 / elem_size(dtY)) == 0);
+    if (is_plain_gemm(R, S, pad_h, pad_w, stride_h, stride_w)) {
+        const Launch G = gemm_of_conv(L);
+        if (takes_gemm(L, G, tune)) {
+            kp.lda = C;
+            return run(G, kp, tune, stream);
+        }
+    }
     return run(L, kp, tune, stream);
 }
 
@@ -1250,6 +1284,13 @@ ucl_status ucl_conv2d_dgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     kp.pad_h = (int32_t)pad_h; kp.pad_w = (int32_t)pad_w; kp.str_h = (int32_t)stride_h; kp.str_w = (int32_t)stride_w;
     kp.dil_h = (int32_t)dil_h; kp.dil_w = (int32_t)dil_w;
     kp.d_vec = aligned16(dx) && (C % (16 / elem_size(dtDx)) == 0);
+    if (is_plain_gemm(R, S, pad_h, pad_w, stride_h, stride_w)) {
+        const Launch G = gemm_of_conv(L);
+        if (takes_gemm(L, G, tune)) {
+            kp.lda = Kout;
+            return run(G, kp, tune, stream);
+        }
+    }
     return run(L, kp, tune, stream);
 }
 
@@ -1320,6 +1361,10 @@ ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out) {
     if (!out) return fail(UCL_ERR_INVALID_ARG, "output pointer is NULL");
     Launch L;
     if (ucl_status st = launch_from_problem(p, L)) return st;
+    if ((L.mode == 2 || L.mode == 3) && is_plain_gemm(p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w)) {
+        const Launch G = gemm_of_conv(L);
+        if (takes_gemm(L, G, nullptr)) L = G;
+    }
     const VariantDesc *v = select_variant(L, nullptr);
     if (!v) return fail(UCL_ERR_UNSUPPORTED, "no kernel built for this problem");
     memset(out, 0, sizeof(*out));

@@ -1,0 +1,40 @@
+"""1x1 convolutions at unit stride without padding run on the GEMM kernels: exact with the library's choice, with named GEMM
+and convolution tiles and with the gather iterator; the choice can be named again."""
+import pytest
+
+from paper_2603_29010_amd import synth
+from paper_2603_29010_amd.binding import Tuning
+
+import paper_2603_29010_amd as ucl
+import parity
+
+pytestmark = pytest.mark.gpu
+
+GEOMS = [dict(Nb=2, H=9, W=7, C=40, Ko=72), dict(Nb=1, H=1, W=1, C=8, Ko=8), dict(Nb=3, H=28, W=28, C=128, Ko=256), dict(Nb=2, H=7, W=7, C=1024, Ko=512)]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("op", ["fprop", "dgrad"])
+@pytest.mark.parametrize("geom", GEOMS, ids=lambda g: "x".join(str(v) for v in g.values()))
+def test_exact(geom, op, dt):
+    g = dict(geom, R=1, S=1, pad=(0, 0))
+    make = (lambda **k: synth.conv_spec(**g, **k)) if op == "fprop" else (lambda **k: synth.conv_grad_spec("dgrad", **g, **k))
+    spec = make(dt_in=dt, dt_out="f32", epilogue=(), integer=True)
+    conv = (g["Nb"], g["H"], g["W"], g["C"], g["Ko"], 1, 1, 0, 0, 1, 1, 1, 1)
+    t = ucl.ucl_select_tuning(f"conv2d_{op}", dt, "f32", conv=conv)
+    named = Tuning(t["tile_m"], t["tile_n"], t["tile_k"], t["stages"], t["raster"], t["iterator"])
+    for tune in (None, named, Tuning(64, 64, 32, 3), Tuning(128, 128, 64, 2), Tuning(iterator=1), Tuning(raster=2)):
+        if tune is not None and op == "dgrad" and (tune.c.tile_m, tune.c.tile_k) == (128, 64) and tune is not named and dt == "f16":
+            continue
+        parity.check_exact(spec, tune, label=f"{op} {dt} {geom} {tune and tune.as_dict()}")
+    spec = make(dt_in=dt, dt_out=dt, epilogue=("bias", "aux_load", "relu"))
+    parity.check(spec, None, label=f"{op} {dt} {geom} chain")
+
+
+def test_what_was_refused_stays_refused():
+    spec = synth.conv_spec(Nb=1, H=8, W=8, C=64, Ko=64, R=1, S=1, pad=(0, 0))
+    for tune in (Tuning(split_k="parallel", slices=2, workspace=4096, workspace_bytes=1 << 20), Tuning(scheduler="persistent"),
+                 Tuning(scheduler="stream_k", workspace=4096, workspace_bytes=1 << 20), Tuning(iterator=2)):
+        with pytest.raises(ucl.UclError) as e:
+            parity.gpu_result(spec, tune)
+        assert e.value.status == "UCL_ERR_UNSUPPORTED"
