@@ -1199,7 +1199,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     // The compiler does not count asm LDS reads, so with kMDirect a row block waits for its A fragment
     // itself: lgkmcnt(W).  The fragment was requested RA - 1 row blocks earlier and LDS reads return in
     // order, so it has arrived once at most W reads are outstanding, W being a number of reads known
-    // to have been issued after it (2: the two transpose reads of the previous row block's request).
+    // to have been issued after it (2: the two transpose reads of the previous row block's request).  A ring of two
+    // requests it in the row block just before, behind which only that row block's B fragments follow: none of them if
+    // that was the last row block of a k-step.
     auto a_ready = [&](auto w_) __attribute__((always_inline)) {
         constexpr int W = decltype(w_)::value;
         if constexpr (LA == kMDirect && W >= 0) __builtin_amdgcn_s_waitcnt((0xF) | (0x3 << 14) | (0x7 << 4) | (W << 8));
@@ -1300,6 +1302,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         static_assert(KSTEPS == 2, "the two-buffer loop is written for k-tiles of two k-steps");
         constexpr int RA = MI % 4 == 0 ? 4 : 2;
         static_assert(MI % RA == 0, "ring slots must line up across k-tiles");
+        static_assert(LA != kMDirect || RA == 4, "the waits of a_ready below count on two requests behind a fragment");
         u32x4_t ar[RA], af[MI], bq[2][NI];
         // the side instructions of a row block go out one (or their even share) behind each MFMA
         auto row_block = [&](auto mi_, const u32x4_t &a, auto pb_, auto ns_, auto w_, auto &&side) __attribute__((always_inline)) {
@@ -1494,7 +1497,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
                 // accumulator, which is what the row-major store wants.  The side instructions go
                 // out one (or their even share) behind each MFMA, so that none of the gaps between
                 // two MFMAs grows longer than the MFMA itself.
-                a_ready(std::integral_constant<int, 2>{});
+                constexpr int b_behind = mi == 0 ? 0 : bshare(mi, MI, NI) - bshare(mi - 1, MI, NI);
+                a_ready(std::integral_constant<int, (RA > 2 || b_behind >= 2 ? 2 : b_behind)>{});
                 static_for<NI>([&](auto ni_) {
                     constexpr int ni = decltype(ni_)::value;
                     mfma16<Cfg::DT>(acc[mi][ni], bq[PB][ni], ar[mi % RA]);
