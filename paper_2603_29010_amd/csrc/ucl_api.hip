@@ -94,6 +94,7 @@ struct Launch {
     int mode = 0;                 // 0 gemm / batched, 1 grouped, 2 conv fprop, 3 conv dgrad, 4 conv wgrad
     int64_t batch = 1, M = 0, N = 0, K = 0;
     int la = 0, lb = 0;           // operand layouts
+    int64_t lda = 0, ldb = 0;     // leading strides (0 where only sizes are known)
     int dt = 0;                   // input type code of the kernels: 0 bf16, 1 fp16, 2 fp8 e4m3, 3 fp8 e5m2
     int dtD = 0;
     int groups = 0;
@@ -258,7 +259,7 @@ double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const La
 // 64x64x32 kernel, whose four workgroups per CU hide the gathered operand best) against the bytes of partial tiles.
 // Measured against one or two workgroups per CU of the tile the general split model liked (440 geometries): 13 % in the
 // geometric mean; 64 <- 1152 columns over 117978 pixels 82 -> 43 us, 256 <- 576 over 4312 pixels 25.6 -> 16.0 us.
-struct WgradChoice {
+struct SplitChoice {
     const VariantDesc *v = nullptr;
     int slices = 1, k_per_slice = 0;
 };
@@ -278,14 +279,57 @@ double estimate_wgrad_seconds(const VariantDesc &v, const CostRow &r, const Laun
     }
     return 1e-6 * t;
 }
-WgradChoice choose_wgrad_split(const Launch &L, const ucl_tuning *tune) {
+// Operand panels are addressed with 32-bit byte offsets inside range-checked buffer resources.
+bool panel_fits(int64_t rows, int64_t ld, int64_t K) { return (rows * ld + K) * 2 < (1ll << 31); }
+bool panels_fit(const VariantDesc &v, const Launch &L) {
+    return (v.la != 0 || panel_fits(v.tile_m, L.lda, L.K)) && (v.lb != 0 || panel_fits(v.tile_n, L.ldb, L.K));
+}
+
+const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune);
+
+// GEMM, both 16-bit operands contiguous along K: the same, for the two kernels that were the fastest or next to it in 310 problems
+// (32..768 rows and columns, K 2048..65536; tiles of 64x64 nearly always, of 128x128 where there are 20 and more).  Constants
+// fitted to every power of two of slices: launches, GB/s copied per CU, us per k-tile of a chain, TB/s of partial tiles and
+// of operands, us that each slice adds to the reduction's chain of loads.
+struct GemmSplitRow {
+    int tile;
+    double fixed, gbs, tflops, step, partial_tbs, operand_tbs, slice;
+};
+constexpr GemmSplitRow kGemmSplitRows[] = {{64, 10.46, 90.7, 20.0, 0.207, 2.24, 5.10, 0.022}, {128, 13.24, 81.4, 20.0, 0.640, 3.07, 5.63, 0.017}};
+bool has_gemm_split_row(const VariantDesc &v) {
+    return v.mode == 0 && v.la == 0 && v.lb == 0 && v.k_groups == 1 && v.tile_k == 64 &&
+           ((v.tile_m == 64 && v.tile_n == 64 && v.stages == 4) || (v.tile_m == 128 && v.tile_n == 128 && v.stages == 2));
+}
+double estimate_gemm_split_seconds(const VariantDesc &v, const Launch &L, int slices, int64_t k_per_slice) {
+    const GemmSplitRow &r = kGemmSplitRows[v.tile_m == 64 ? 0 : 1];
+    const int64_t wgs = count_tiles(L, v.tile_m, v.tile_n) * slices, resident = 2;
+    const int64_t slots = 256 * resident, rounds = (wgs + slots - 1) / slots;
+    const double on_cu = wgs <= slots ? (double)((wgs + 255) / 256) : (double)(rounds * resident);
+    const double tile_rows = (double)(L.M < v.tile_m ? L.M : v.tile_m) + (double)(L.N < v.tile_n ? L.N : v.tile_n), K = (double)k_per_slice;
+    const double loop = fourth_power_sum(on_cu * tile_rows * K * 2.0 / (r.gbs * 1e3), on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6),
+                                         (double)rounds * (double)((k_per_slice + 63) / 64) * r.step,
+                                         (double)(L.M + L.N) * (double)L.K * 2.0 / (r.operand_tbs * 1e6));
+    return 1e-6 * (r.fixed + loop + (double)wgs * v.tile_m * v.tile_n * 4.0 / (r.partial_tbs * 1e6) + r.slice * slices);
+}
+
+// Parallel split-K calls whose slices the library chooses together with the kernel
+bool split_left_open(const Launch &L, const ucl_tuning *tune) {
+    if (!tune || tune->split_k_mode != UCL_SPLIT_K_PARALLEL || tune->split_k_slices != 0 || tune->scheduler != UCL_SCHED_DEFAULT) return false;
+    if (L.mode == 4) return true;
+    // (fp32 outputs keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
+    // 4.4e-7 on 464 x 393 x 19848; a 16-bit output's error is the same to six digits either way)
+    return L.mode == 0 && L.dtD != UCL_F32 && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 &&
+           !(tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
+}
+SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const bool named = tune->tile_m || tune->tile_n || tune->tile_k || tune->stages;
     const int64_t kt = (L.K + 63) / 64;
-    WgradChoice best;
+    SplitChoice best;
     double best_t = 0;
     for (size_t i = 0; i < all_variants().size(); ++i) {
         const VariantDesc &v = all_variants()[i];
-        if (v.mode != 4 || v.dt != L.dt || v.persistent) continue;
+        if (v.mode != L.mode || v.dt != L.dt || v.persistent) continue;
+        if (L.mode == 0 && !(has_gemm_split_row(v) && panels_fit(v, L))) continue;
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
         // no split, a few slices, and what fills the chip with one to eight workgroups per CU
@@ -294,15 +338,29 @@ WgradChoice choose_wgrad_split(const Launch &L, const ucl_tuning *tune) {
             int64_t want = (fill + tiles - 1) / tiles;
             if (want > kt / 2) want = kt / 2;
             if (want < 1) want = 1;
+            // (more slices than 64 were not measured for a GEMM)
+            if (L.mode == 0 && want > 64) want = 64;
             int slices = 1, kps = 0;
             split_slices(L, want, tiles, 0, slices, kps);
-            const double t = estimate_wgrad_seconds(v, all_costs()[i], L, slices, slices > 1 ? kps : L.K);
+            if (L.mode == 0 && slices == 1) continue;       // (a GEMM that is not split has more kernels: below)
+            const double t = L.mode == 0 ? estimate_gemm_split_seconds(v, L, slices, kps)
+                                         : estimate_wgrad_seconds(v, all_costs()[i], L, slices, slices > 1 ? kps : L.K);
             if (!best.v || t < best_t) {
                 best_t = t;
                 best.v = &v;
                 best.slices = slices;
                 best.k_per_slice = kps;
             }
+        }
+    }
+    // The few-row kernels and K groups often need less time for the whole of K than the launches of a split take: 1.4 to 1.8 times
+    // less at K = 4096 to 5000 (88 x 159 x 4200: 7.1 against 12.1 us), 1.2 times at 8192 and up to 16 tiles, more than a split from
+    // about 10000.
+    if (best.v && L.mode == 0 && L.K <= 8192) {
+        const VariantDesc *v = select_variant(L, nullptr);
+        if (v && estimate_seconds(*v, all_costs()[v - all_variants().data()], L) < 0.9 * best_t) {
+            best.v = v;
+            best.slices = 1;
         }
     }
     if (!best.v) return best;
@@ -312,9 +370,6 @@ WgradChoice choose_wgrad_split(const Launch &L, const ucl_tuning *tune) {
     if (tune->workspace && bytes > tune->workspace_bytes) best.v = nullptr;
     return best;
 }
-bool wgrad_split_left_open(const Launch &L, const ucl_tuning *tune) {
-    return L.mode == 4 && tune && tune->split_k_mode == UCL_SPLIT_K_PARALLEL && tune->split_k_slices == 0 && tune->scheduler == UCL_SCHED_DEFAULT;
-}
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
@@ -322,8 +377,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const bool explicit_tune = tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
     const VariantDesc *best = nullptr;
     double best_t = 0;
-    if (!explicit_tune && wgrad_split_left_open(L, tune))
-        if (const VariantDesc *v = choose_wgrad_split(L, tune).v) return v;
+    bool best_fits = false;
     const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
     for (size_t i = 0; i < vs.size(); ++i) {
         const VariantDesc &v = vs[i];
@@ -361,9 +415,18 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         if (split && v.k_groups > 1) continue;          // split-K has kernels without K groups only
         const double t = split ? estimate_split_seconds(v, costs[i], L, tune)
                          : L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
-        if (!best || t < best_t) { best_t = t; best = &v; }
+        // (a large tile must not make a call fail that a smaller one serves)
+        const bool fits = panels_fit(v, L);
+        if (!best || (fits && !best_fits) || (fits == best_fits && t < best_t)) { best_t = t; best = &v; best_fits = fits; }
     }
     return best;
+}
+
+// The kernel of a call, and the slices chosen with it where the call leaves both open (a named tile keeps its own slices' choice).
+const VariantDesc *select_with_split(const Launch &L, const ucl_tuning *tune, SplitChoice &choice) {
+    if (split_left_open(L, tune)) choice = choose_split(L, tune);
+    if (choice.v && !(tune->tile_m || tune->tile_n || tune->tile_k || tune->stages)) return choice.v;
+    return select_variant(L, tune);
 }
 
 // A 1x1 convolution at unit stride without padding IS a GEMM over the pixels: its forward pass (pixels x channels times filter
@@ -672,7 +735,7 @@ struct SplitPlan {
     int sk_ipt = 0, sk_q = 0, sk_rounds = 0, sk_grid = 0, sk_deal = 0;
 };
 
-ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *tune, int64_t total_tiles, SplitPlan &sp) {
+ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *tune, const SplitChoice &choice, int64_t total_tiles, SplitPlan &sp) {
     sp = SplitPlan();
     if (!tune) return UCL_OK;
     if (tune->scheduler < UCL_SCHED_DEFAULT || tune->scheduler > UCL_SCHED_STREAM_K)
@@ -732,11 +795,9 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
     if (L.mode != 0 && L.mode != 4) return fail(UCL_ERR_UNSUPPORTED, "split-K is built for gemm, batched_gemm and conv2d_wgrad");
     if (tune->scheduler == UCL_SCHED_PERSISTENT)
         return fail(UCL_ERR_UNSUPPORTED, "split-K and the persistent scheduler cannot be combined");
-    WgradChoice w;
-    if (wgrad_split_left_open(L, tune)) w = choose_wgrad_split(L, tune);
-    if (w.v == &v) {
-        sp.slices = w.slices;
-        sp.k_per_slice = w.k_per_slice;
+    if (choice.v == &v) {
+        sp.slices = choice.slices;
+        sp.k_per_slice = choice.k_per_slice;
     } else {
         split_slices(L, tune->split_k_slices, total_tiles, split_fill(L, v, tune), sp.slices, sp.k_per_slice);
     }
@@ -751,13 +812,15 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
 // Parallel split-K with up to this many slices lets the last launch of the tile kernel add them up itself.
 constexpr int kReduceInTileKernel = 2;
 
-ucl_status run(const Launch &L, KParams &kp, const ucl_tuning *tune, void *stream, bool clear_counters = false) {
+ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool clear_counters = false) {
+    L.lda = kp.lda; L.ldb = kp.ldb;
     if (tune && (tune->iterator < 0 || tune->iterator > UCL_ITER_FIXED_STRIDE_DILATION))
         return fail(UCL_ERR_INVALID_ARG, "iterator=%d is not a ucl_conv_iterator", tune->iterator);
     // (the GEMM entry points ignore the iterator)
     if (tune && (L.mode == 2 || L.mode == 3) && tune->iterator == UCL_ITER_FIXED_STRIDE_DILATION && !L.patch_c)
         return fail(UCL_ERR_UNSUPPORTED, "the fixed_stride_dilation iterator serves a 3x3 filter with unit stride and dilation, pad 1 and W <= 58: conv2d_fprop with 64 or 128 input channels, conv2d_dgrad with 64 or 128 output channels");
-    const VariantDesc *v = select_variant(L, tune);
+    SplitChoice choice;
+    const VariantDesc *v = select_with_split(L, tune, choice);
     if (!v) {
         if (tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages)) {
             if (tune->tile_k != 32 && tune->tile_k != 64)
@@ -802,7 +865,7 @@ ucl_status run(const Launch &L, KParams &kp, const ucl_tuning *tune, void *strea
     }
     if (total >= (1ll << 31)) return fail(UCL_ERR_UNSUPPORTED, "problem needs %lld tiles; the grid is limited to 2^31-1", (long long)total);
     SplitPlan sp;
-    if (ucl_status st = plan_split(L, *v, tune, total, sp)) return st;
+    if (ucl_status st = plan_split(L, *v, tune, choice, total, sp)) return st;
     if (sp.sk_grid > 0) {
         if (!tune->workspace)
             return fail(UCL_ERR_WORKSPACE, "the stream_k scheduler needs a workspace of %lld bytes (ucl_workspace_size); tune->workspace is NULL", (long long)sp.bytes);
@@ -828,10 +891,9 @@ ucl_status run(const Launch &L, KParams &kp, const ucl_tuning *tune, void *strea
         kp.ws_counters = (uint32_t *)tune->workspace;
         kp.ws_partials = (float *)((char *)tune->workspace + UCL_WORKSPACE_COUNTER_BYTES);
     }
-    // operand panels are addressed with 32-bit byte offsets inside range-checked buffer resources
-    if (v->la == 0 && ((int64_t)v->tile_m * kp.lda + L.K) * 2 >= (1ll << 31))
+    if (v->la == 0 && !panel_fits(v->tile_m, kp.lda, L.K))
         return fail(UCL_ERR_UNSUPPORTED, "A leading stride %lld too large: a %d-row panel must span less than 2 GiB", (long long)kp.lda, v->tile_m);
-    if (v->lb == 0 && ((int64_t)v->tile_n * kp.ldb + L.K) * 2 >= (1ll << 31))
+    if (v->lb == 0 && !panel_fits(v->tile_n, kp.ldb, L.K))
         return fail(UCL_ERR_UNSUPPORTED, "B leading stride %lld too large: a %d-row panel must span less than 2 GiB", (long long)kp.ldb, v->tile_n);
     kp.total_tiles = (int32_t)total;
     if (total == 0) return UCL_OK;     // grouped with every M_g == 0: nothing to do
@@ -1384,10 +1446,11 @@ ucl_status ucl_workspace_size(const ucl_problem *p, const ucl_tuning *tune, int6
     if (ucl_status st = launch_from_problem(p, L)) return st;
     if (tune && (tune->iterator < 0 || tune->iterator > UCL_ITER_FIXED_STRIDE_DILATION))
         return fail(UCL_ERR_INVALID_ARG, "iterator=%d is not a ucl_conv_iterator", tune->iterator);
-    const VariantDesc *v = select_variant(L, tune);
+    SplitChoice choice;
+    const VariantDesc *v = select_with_split(L, tune, choice);
     if (!v) return fail(UCL_ERR_UNSUPPORTED, "no kernel built for this problem and tuning; see ucl_variant()");
     SplitPlan sp;
-    if (ucl_status st = plan_split(L, *v, tune, count_tiles(L, v->tile_m, v->tile_n), sp)) return st;
+    if (ucl_status st = plan_split(L, *v, tune, choice, count_tiles(L, v->tile_m, v->tile_n), sp)) return st;
     *bytes = sp.bytes;
     if (slices_out) *slices_out = sp.slices;
     return UCL_OK;
