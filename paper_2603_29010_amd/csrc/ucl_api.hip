@@ -66,6 +66,16 @@ const std::vector<CostRow> &all_costs() {
     return c;
 }
 
+// Where the variants of one operation and input type stand in all_variants(): every call's choice walks these 2 to 40 of 195.
+const std::vector<int> &variants_of(int mode, int dt) {
+    static const std::vector<std::vector<int>> lists = [] {
+        std::vector<std::vector<int>> out(5 * 4);
+        for (size_t i = 0; i < all_variants().size(); ++i) out[all_variants()[i].mode * 4 + all_variants()[i].dt].push_back((int)i);
+        return out;
+    }();
+    return lists[mode * 4 + dt];
+}
+
 bool is8(int dt) { return dt == UCL_FP8_E4M3 || dt == UCL_FP8_E5M2; }
 int elem_size(int dt) { return dt == UCL_F32 ? 4 : is8(dt) ? 1 : 2; }
 bool is16(int dt) { return dt == UCL_F16 || dt == UCL_BF16; }
@@ -326,9 +336,9 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const int64_t kt = (L.K + 63) / 64;
     SplitChoice best;
     double best_t = 0;
-    for (size_t i = 0; i < all_variants().size(); ++i) {
+    for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = all_variants()[i];
-        if (v.mode != L.mode || v.dt != L.dt || v.persistent) continue;
+        if (v.persistent) continue;
         if (L.mode == 0 && !(has_gemm_split_row(v) && panels_fit(v, L))) continue;
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
@@ -379,9 +389,9 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     double best_t = 0;
     bool best_fits = false;
     const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
-    for (size_t i = 0; i < vs.size(); ++i) {
+    for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = vs[i];
-        if (v.mode != L.mode || v.dt != L.dt || v.persistent != want_persistent) continue;
+        if (v.persistent != want_persistent) continue;
         if (v.lb == 4 ? !(L.lb == 1 && L.ndirect_ok) : v.lb != L.lb) continue;
         if (L.mode == 2 || L.mode == 3) {
             // conv: the iterator knob picks between the per-tap gather (la 2) and the resident patch (la 3)
