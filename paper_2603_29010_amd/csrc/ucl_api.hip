@@ -66,7 +66,7 @@ const std::vector<CostRow> &all_costs() {
     return c;
 }
 
-// Where the variants of one operation and input type stand in all_variants(): every call's choice walks these 2 to 40 of 195.
+// Where the variants of one operation and input type stand in all_variants(): every call walks these 2 to 49 instead of all 195.
 const std::vector<int> &variants_of(int mode, int dt) {
     static const std::vector<std::vector<int>> lists = [] {
         std::vector<std::vector<int>> out(5 * 4);
