@@ -8,6 +8,8 @@ static const VariantDesc kTable[] = {
     describe<KernelCfg<64, 64, 64, 4, 0, 4, kMDirect, kNDirect>>(),
     describe<KernelCfg<128, 128, 32, 4, 1, 4, kMDirect, kNDirect>>(),
     describe<KernelCfg<64, 64, 32, 3, 1, 4, kMDirect, kNDirect>>(),
+    describe<KernelCfg<128, 128, 64, 2, 1, 4, kMDirect, kNDirect>>(),
+    describe<KernelCfg<64, 64, 64, 4, 1, 4, kMDirect, kNDirect>>(),
 };
 VariantList variants_conv_wgrad() { return {kTable, (int)(sizeof(kTable) / sizeof(kTable[0]))}; }
 }  // namespace ucl

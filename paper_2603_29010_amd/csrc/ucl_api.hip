@@ -66,7 +66,7 @@ const std::vector<CostRow> &all_costs() {
     return c;
 }
 
-// Where the variants of one operation and input type stand in all_variants(): every call walks these 2 to 49 instead of all 195.
+// Where the variants of one operation and input type stand in all_variants(): every call walks these 4 to 49 instead of all.
 const std::vector<int> &variants_of(int mode, int dt) {
     static const std::vector<std::vector<int>> lists = [] {
         std::vector<std::vector<int>> out(5 * 4);
@@ -343,7 +343,7 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
         // Over many pixels the two k-tiles that 64x64x32 has in flight, 4 KB of each operand, don't cover the trips to memory: 64 <- 576 columns over
         // 100352 pixels 32.8 us, 64x64x64 26.0 us; 128 <- 576 over as many 53.7 us, 128x128x32 33.9 us.  Below, its four workgroups per CU
         // do (128 <- 1152 over 6272: 17.0 against 17.0 us, 256 <- 2304 over 1568: 19.4 against 24 us).
-        if (L.mode == 4 && !named && v.dt == 0 && v.tile_m == 64 && v.tile_k == 32 && L.K > 24576) continue;
+        if (L.mode == 4 && !named && v.tile_m == 64 && v.tile_k == 32 && L.K > 24576) continue;
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
         // no split, a few slices, and what fills the chip with one to eight workgroups per CU
