@@ -265,10 +265,11 @@ double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const La
 }
 
 // Weight gradient: kernel and slices of a parallel split-K call that leaves the slices to the library, chosen together.
-// Its K (output pixels) is deep, its output small: what decides is how many k-tiles a workgroup chains (0.33 us each of the
+// Its K (output pixels) is deep, its output small: what decides is how many k-tiles a workgroup chains (0.37 us each of the
 // 64x64x32 kernel, whose four workgroups per CU hide the gathered operand best) against the bytes of partial tiles.
-// Measured against one or two workgroups per CU of the tile the general split model liked (440 geometries): 13 % in the
-// geometric mean; 64 <- 1152 columns over 117978 pixels 82 -> 43 us, 256 <- 576 over 4312 pixels 25.6 -> 16.0 us.
+// Measured against one or two workgroups per CU of the tile the general split model liked: about 10 % in the geometric mean over 440
+// geometries, 15 % over 32 layers of a residual network at batches 8 to 128 (128 <- 1152 over 25088 pixels 46.2 -> 26.4 us,
+// 128 <- 1152 over 6272 17.8 -> 18.5 us).
 struct SplitChoice {
     const VariantDesc *v = nullptr;
     int slices = 1, k_per_slice = 0;
