@@ -154,27 +154,10 @@ constexpr int64_t kMaxWideLd = 1ll << 21;
 // Workgroups of a variant that fit on one CU: 512 registers per lane and SIMD (the kernels are built
 // with a budget by tile area), 160 KB of LDS.
 int workgroups_per_cu(const VariantDesc &v) {
-    if (v.k_groups > 1) return v.wgs_per_cu;          // (their stage buffers take most of a CU's LDS: one)
     const int64_t area = (int64_t)v.tile_m * v.tile_n;
     const int by_regs = area >= 256 * 256 ? 1 : area >= 256 * 128 ? 2 : area >= 128 * 128 ? 3 : 4;
     const int by_lds = v.lds_bytes > 0 ? kLdsBytesPerCU / v.lds_bytes : 8;
     return by_regs < by_lds ? by_regs : by_lds;
-}
-
-// Rate of a CU that is busy with variant v, relative to the best variant (measured, see above).
-double relative_rate(const VariantDesc &v) {
-    const int64_t area = (int64_t)v.tile_m * v.tile_n;
-    const bool two_buf = v.stages == 2 && v.tile_k == 64 && v.lb != 1 && v.la != 1;
-    if (v.la == 1 || v.lb == 1) return area >= 128 * 128 ? 0.30 : 0.20;     // register-transposed operands
-    const double nd = (v.lb == 4 ? 0.95 : 1.0) * (v.la == 5 ? 0.9 : 1.0);   // two LDS reads per fragment of a directly copied operand
-    // conv from a resident patch: above the gather kernels.  (A 256-row tile with 128-channel pixels is alone on its
-    // CU, with nothing to run while its 96 KB patch loads: measured 32 us against 27 us for the 128-row tile.)
-    if (v.la == 3) return 2 * v.lds_bytes > kLdsBytesPerCU ? 0.65 : 0.85;
-    if (area >= 256 * 256) return nd * (two_buf ? 1.00 : v.stages >= 5 ? 0.92 : 0.90);
-    if (area >= 256 * 128) return nd * (two_buf ? 0.81 : v.stages == 3 ? 0.80 : 0.73);
-    // (with a directly copied operand the two-buffer loop of this size measured below the 4-stage one)
-    if (area >= 128 * 128) return nd * (two_buf ? (nd < 1.0 ? 0.62 : 0.86) : v.tile_k == 32 ? (v.stages >= 4 ? 0.67 : 0.65) : 0.58);
-    return nd * (v.tile_k == 64 ? 0.49 : v.stages == 3 ? 0.41 : 0.37);
 }
 
 // Launch time of a variant:  fixed + round * rounds + loop (+) output, where
@@ -234,6 +217,47 @@ void split_slices(const Launch &L, int64_t want, int64_t total_tiles, int fill, 
     slices = (int)((kt + per - 1) / per);
 }
 
+// Rate of a CU that is busy with variant v (gemm, batched gemm and weight gradient), relative to the best variant.
+double relative_rate(const VariantDesc &v) {
+    const int64_t area = (int64_t)v.tile_m * v.tile_n;
+    const bool two_buf = v.stages == 2 && v.tile_k == 64 && v.lb != 1 && v.la != 1;
+    if (v.la == 1 || v.lb == 1) return area >= 128 * 128 ? 0.30 : 0.20;     // register-transposed operands
+    const double nd = (v.lb == 4 ? 0.95 : 1.0) * (v.la == 5 ? 0.9 : 1.0);   // two LDS reads per fragment of a directly copied operand
+    if (area >= 256 * 256) return nd * (two_buf ? 1.00 : v.stages >= 5 ? 0.92 : 0.90);
+    if (area >= 256 * 128) return nd * (two_buf ? 0.81 : v.stages == 3 ? 0.80 : 0.73);
+    // (with a directly copied operand the two-buffer loop of this size measured below the 4-stage one)
+    if (area >= 128 * 128) return nd * (two_buf ? (nd < 1.0 ? 0.62 : 0.86) : v.tile_k == 32 ? (v.stages >= 4 ? 0.67 : 0.65) : 0.58);
+    return nd * (v.tile_k == 64 ? 0.49 : v.stages == 3 ? 0.41 : 0.37);
+}
+
+// Launch time of variant v without a split, in the terms of the split model below, for the comparison of the two:
+//     tiles of the busiest CU * ( tile FLOPs / rate + fixed cost of a tile, exposed as far as no co-resident workgroup hides it )
+// (estimate_seconds is fitted to other measurements: a split in one model against no split in the other takes slices where whole
+// tiles are sooner done, bf16 4096 x 512 x 16384 among them, and none where they pay.)
+double estimate_whole_seconds(const VariantDesc &v, const Launch &L) {
+    const double kCuRate = 1.38e15 / 256;            // FLOP/s of one CU at the best variant's measured rate
+    const double kCuStore = 4.6e12 / 256;            // B/s of output one CU gets when all CUs store
+    const int wg = workgroups_per_cu(v);
+    const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
+    const int64_t slots = 256 * (int64_t)wg;
+    // tiles the busiest CU works through: they run wg at a time, a new set starting when slots free up
+    const double per_cu = tiles <= slots ? (double)((tiles + 255) / 256) : (double)((tiles + slots - 1) / slots * wg);
+    // the chip is power-limited: CUs run faster when fewer of them are busy (measured ~1.5x at 144 of 256)
+    const double active = tiles / per_cu < 256.0 ? tiles / per_cu : 256.0;
+    double boost = pow(256.0 / (active < 1.0 ? 1.0 : active), 0.7);
+    if (boost > 1.5) boost = 1.5;
+    const double tile_flops = 2.0 * v.tile_m * v.tile_n * (double)L.K;
+    const double out_bytes = (double)v.tile_m * v.tile_n * (L.dtD == UCL_F32 ? 4.0 : 2.0);
+    const double fixed = 2.0e-6 + out_bytes / kCuStore;
+    // co-resident workgroups hide about half of what perfect overlap of one's fixed cost with the
+    // others' MFMA time would; a CU with a single tile has nothing to overlap with
+    const double exposed = per_cu > 1.0 ? 0.5 * (1.0 + 1.0 / wg) : 1.0;
+    // a variant built to share its CU runs below its rate when it has the CU to itself (one wave per SIMD
+    // with the register budget of two: measured 0.7x for 256x128 tiles)
+    const double alone = (wg >= 2 && per_cu < 2.0) ? 0.7 : 1.0;
+    return per_cu * (tile_flops / (relative_rate(v) * alone * kCuRate * boost) + fixed * exposed);
+}
+
 // Launch time of variant v under split-K, for the choice among the variants when the caller names no tile.
 // What counts differs from the unsplit case.  Every CU has a workgroup, so the mainloop is bound by one of: the
 // operand bytes all workgroups together copy into LDS (measured ~10 TB/s over the chip when they stream from
@@ -243,11 +267,11 @@ void split_slices(const Launch &L, int64_t want, int64_t total_tiles, int fill, 
 // of partial tiles; chains the reduction kernel finishes itself need one launch less, which is the same for every
 // tile and is left out of the comparison), in serial mode through the last workgroup of each tile, which reads all slices alone
 // (measured 15-28 GB/s per workgroup).
-double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const Launch &L, const ucl_tuning *tune) {
+double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_tuning *tune) {
     const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
     int slices = 1, kps = 0;
     split_slices(L, tune->split_k_slices, tiles, split_fill(L, v, tune), slices, kps);
-    if (slices <= 1) return estimate_seconds(v, row, L);
+    if (slices <= 1) return estimate_whole_seconds(v, L);
     const double wgs = (double)tiles * slices;
     const double rounds = ceil(wgs / (256.0 * workgroups_per_cu(v)));
     const double busy = wgs < 256.0 ? wgs / 256.0 : 1.0;
@@ -257,7 +281,7 @@ double estimate_split_seconds(const VariantDesc &v, const CostRow &row, const La
     double main = copy_bytes / ((resident ? 16.0e12 : 10.0e12) * busy);
     const double mfma = flops / (relative_rate(v) * 1.38e15 * busy);
     if (mfma > main) main = mfma;
-    const double chain = rounds * (kps / (double)v.tile_k) * (resident ? 0.8e-6 : 1.5e-6) / (v.stages > 1 ? v.stages - 1 : 1) / v.k_groups;
+    const double chain = rounds * (kps / (double)v.tile_k) * (resident ? 0.8e-6 : 1.5e-6) / (v.stages > 1 ? v.stages - 1 : 1);
     if (chain > main) main = chain;
     const double tile_bytes = (double)v.tile_m * v.tile_n * 4.0;
     if (tune->split_k_mode == UCL_SPLIT_K_PARALLEL) return main + 6.0e-6 + wgs * tile_bytes / 1.0e12;
@@ -296,6 +320,7 @@ bool panels_fit(const VariantDesc &v, const Launch &L) {
     return (v.la != 0 || panel_fits(v.tile_m, L.lda, L.K)) && (v.lb != 0 || panel_fits(v.tile_n, L.ldb, L.K));
 }
 
+bool names_tile(const ucl_tuning *tune);
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune);
 
 // GEMM, both 16-bit operands contiguous along K: the same, for the two kernels that were the fastest or next to it in 310 problems
@@ -329,11 +354,10 @@ bool split_left_open(const Launch &L, const ucl_tuning *tune) {
     if (L.mode == 4) return true;
     // (fp32 outputs keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
     // 4.4e-7 on 464 x 393 x 19848; a 16-bit output's error is the same to six digits either way)
-    return L.mode == 0 && L.dtD != UCL_F32 && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 &&
-           !(tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
+    return L.mode == 0 && L.dtD != UCL_F32 && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
 }
 SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
-    const bool named = tune->tile_m || tune->tile_n || tune->tile_k || tune->stages;
+    const bool named = names_tile(tune);
     const int64_t kt = (L.K + 63) / 64;
     SplitChoice best;
     double best_t = 0;
@@ -386,26 +410,30 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     return best;
 }
 
+// Does a variant of L's operation and input type serve its layouts, and the scheduler and iterator that the call names?
+bool serves(const VariantDesc &v, const Launch &L, const ucl_tuning *tune) {
+    const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
+    if (v.persistent != want_persistent) return false;
+    if (v.lb == 4 ? !(L.lb == 1 && L.ndirect_ok) : v.lb != L.lb) return false;
+    if (L.mode == 2 || L.mode == 3) {
+        // conv: the iterator knob picks between the per-tap gather (la 2) and the resident patch (la 3)
+        const int it = tune ? tune->iterator : 0;
+        return v.la == 3 ? (L.patch_c == v.patch_c && it != UCL_ITER_ANALYTIC) : (v.la == 2 && it != UCL_ITER_FIXED_STRIDE_DILATION);
+    }
+    return v.la == 5 ? (L.la == 1 && L.mdirect_ok) : v.la == L.la;
+}
+bool names_tile(const ucl_tuning *tune) { return tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages); }
+
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
     const auto &costs = all_costs();
-    const bool explicit_tune = tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages);
     const VariantDesc *best = nullptr;
     double best_t = 0;
     bool best_fits = false;
-    const int want_persistent = !tune ? 0 : tune->scheduler == UCL_SCHED_PERSISTENT ? 1 : tune->scheduler == UCL_SCHED_STREAM_K ? 2 : 0;
     for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = vs[i];
-        if (v.persistent != want_persistent) continue;
-        if (v.lb == 4 ? !(L.lb == 1 && L.ndirect_ok) : v.lb != L.lb) continue;
-        if (L.mode == 2 || L.mode == 3) {
-            // conv: the iterator knob picks between the per-tap gather (la 2) and the resident patch (la 3)
-            const int it = tune ? tune->iterator : 0;
-            if (v.la == 3 ? (L.patch_c != v.patch_c || it == UCL_ITER_ANALYTIC) : (v.la != 2 || it == UCL_ITER_FIXED_STRIDE_DILATION)) continue;
-        } else if (v.la == 5 ? !(L.la == 1 && L.mdirect_ok) : v.la != L.la) {
-            continue;
-        }
-        if (explicit_tune) {
+        if (!serves(v, L, tune)) continue;
+        if (names_tile(tune)) {
             if (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.stages != tune->stages || v.tile_k != tune->tile_k)
                 continue;
             if (tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
@@ -426,10 +454,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         // against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 52 of 976, K = 1152: 23 against 20 us).
         if (v.stages == 1 && L.K < (L.mode == 1 ? 1408 : 320)) continue;
         if (tune && tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
-        const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4);
-        if (split && v.k_groups > 1) continue;          // split-K has kernels without K groups only
-        const double t = split ? estimate_split_seconds(v, costs[i], L, tune)
-                         : L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
+        const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);
         if (!best || (fits && !best_fits) || (fits == best_fits && t < best_t)) { best_t = t; best = &v; best_fits = fits; }
@@ -437,11 +462,36 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     return best;
 }
 
-// The kernel of a call, and the slices chosen with it where the call leaves both open (a named tile keeps its own slices' choice).
+// Kernel and slices of a split-K call by the general rule: a named tile with the slices of split_slices, else the kernel that the
+// split model likes best with its slices.  Where that is no split at all the call runs as it would without a tuning.
+SplitChoice general_split(const Launch &L, const ucl_tuning *tune) {
+    SplitChoice c;
+    if (names_tile(tune)) {
+        c.v = select_variant(L, tune);
+        if (c.v) split_slices(L, tune->split_k_slices, count_tiles(L, c.v->tile_m, c.v->tile_n), split_fill(L, *c.v, tune), c.slices, c.k_per_slice);
+        return c;
+    }
+    double best_t = 0;
+    for (int i : variants_of(L.mode, L.dt)) {
+        const VariantDesc &v = all_variants()[i];
+        if (!serves(v, L, tune) || v.k_groups > 1) continue;          // split-K has kernels without K groups only
+        const double t = estimate_split_seconds(v, L, tune);
+        if (!c.v || t < best_t) { best_t = t; c.v = &v; }
+    }
+    if (!c.v) return c;
+    split_slices(L, tune->split_k_slices, count_tiles(L, c.v->tile_m, c.v->tile_n), split_fill(L, *c.v, tune), c.slices, c.k_per_slice);
+    if (c.slices <= 1) c.v = select_variant(L, nullptr);
+    return c;
+}
+
+// The kernel of a call, and under split-K the slices chosen with it.
 const VariantDesc *select_with_split(const Launch &L, const ucl_tuning *tune, SplitChoice &choice) {
+    const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4) &&
+                       tune->scheduler == UCL_SCHED_DEFAULT;
+    if (!split) return select_variant(L, tune);
     if (split_left_open(L, tune)) choice = choose_split(L, tune);
-    if (choice.v && !(tune->tile_m || tune->tile_n || tune->tile_k || tune->stages)) return choice.v;
-    return select_variant(L, tune);
+    if (!choice.v) choice = general_split(L, tune);
+    return choice.v;
 }
 
 // A 1x1 convolution at unit stride without padding IS a GEMM over the pixels: its forward pass (pixels x channels times filter
@@ -463,11 +513,10 @@ Launch gemm_of_conv(const Launch &conv) {
 // (Measured over 60 drawn layers: data gradients 1.41x, forward passes 1.11x.  Forward with one 64-wide k-tile is all output
 // and residual: the convolution kernels' choice is 10 % ahead there, 22.5 against 25.1 us on 36 x 60 x 60 x 64 -> 128.)
 bool takes_gemm(const Launch &conv, const Launch &gemm, const ucl_tuning *tune) {
-    if (conv.mode == 2 && conv.K < 128 && !(tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages))) return false;
+    if (conv.mode == 2 && conv.K < 128 && !names_tile(tune)) return false;
     if (!tune) return true;
     if (tune->split_k_mode != UCL_SPLIT_K_NONE || tune->split_k_slices != 0 || tune->scheduler != UCL_SCHED_DEFAULT || tune->iterator != UCL_ITER_DEFAULT) return false;
-    const bool named = tune->tile_m || tune->tile_n || tune->tile_k || tune->stages;
-    if (named && select_variant(conv, tune)) return false;
+    if (names_tile(tune) && select_variant(conv, tune)) return false;
     return select_variant(gemm, tune) != nullptr;
 }
 
@@ -810,12 +859,8 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
     if (L.mode != 0 && L.mode != 4) return fail(UCL_ERR_UNSUPPORTED, "split-K is built for gemm, batched_gemm and conv2d_wgrad");
     if (tune->scheduler == UCL_SCHED_PERSISTENT)
         return fail(UCL_ERR_UNSUPPORTED, "split-K and the persistent scheduler cannot be combined");
-    if (choice.v == &v) {
-        sp.slices = choice.slices;
-        sp.k_per_slice = choice.k_per_slice;
-    } else {
-        split_slices(L, tune->split_k_slices, total_tiles, split_fill(L, v, tune), sp.slices, sp.k_per_slice);
-    }
+    sp.slices = choice.slices;
+    sp.k_per_slice = choice.k_per_slice;
     if (sp.slices <= 1) { sp = SplitPlan(); return UCL_OK; }
     if (total_tiles > UCL_SPLIT_K_MAX_TILES)
         return fail(UCL_ERR_UNSUPPORTED, "split-K serves at most %d output tiles (this problem has %lld)", UCL_SPLIT_K_MAX_TILES, (long long)total_tiles);
@@ -837,7 +882,7 @@ ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool
     SplitChoice choice;
     const VariantDesc *v = select_with_split(L, tune, choice);
     if (!v) {
-        if (tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages)) {
+        if (names_tile(tune)) {
             if (tune->tile_k != 32 && tune->tile_k != 64)
                 return fail(UCL_ERR_UNSUPPORTED, "tile_k=%d: the built kernels stage K in steps of 32 or 64", tune->tile_k);
             const int64_t lds = (int64_t)(tune->tile_m + tune->tile_n) * tune->tile_k * 2 * tune->stages;
