@@ -111,6 +111,7 @@ struct Launch {
     const int64_t *M_g = nullptr;
     int64_t max_Mg = 0, sum_Mg = 0;
     int patch_c = 0;              // conv: the problem fits the resident-patch kernels built for pixels of this many channels (0: none)
+    bool f32_results = false;     // the output or a stored epilogue tensor is fp32: the sums' rounding shows in it
     int64_t cN = 0, cH = 0, cW = 0, str_h = 1, str_w = 1;    // conv dgrad: images, extents of the activations, strides
     bool ndirect_ok = false;      // B contiguous along N and small enough for 32-bit byte offsets: direct-copy kernels apply
     bool mdirect_ok = false;      // the same for A contiguous along M
@@ -322,6 +323,7 @@ bool panels_fit(const VariantDesc &v, const Launch &L) {
 
 bool names_tile(const ucl_tuning *tune);
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune);
+SplitChoice general_split(const Launch &L, const ucl_tuning *tune);
 
 // GEMM, both 16-bit operands contiguous along K: the same, for the two kernels that were the fastest or next to it in 310 problems
 // (32..768 rows and columns, K 2048..65536; tiles of 64x64 nearly always, of 128x128 where there are 20 and more).  Constants
@@ -352,15 +354,20 @@ double estimate_gemm_split_seconds(const VariantDesc &v, const Launch &L, int sl
 bool split_left_open(const Launch &L, const ucl_tuning *tune) {
     if (!tune || tune->split_k_mode != UCL_SPLIT_K_PARALLEL || tune->split_k_slices != 0 || tune->scheduler != UCL_SCHED_DEFAULT) return false;
     if (L.mode == 4) return true;
-    // (fp32 outputs keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
+    // (fp32 results keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
     // 4.4e-7 on 464 x 393 x 19848; a 16-bit output's error is the same to six digits either way)
-    return L.mode == 0 && L.dtD != UCL_F32 && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
+    return L.mode == 0 && !L.f32_results && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
 }
 SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const bool named = names_tile(tune);
     const int64_t kt = (L.K + 63) / 64;
     SplitChoice best;
     double best_t = 0;
+    // The filter gradient in fp32: the same slices as the general rule's or shorter ones, as longer ones would round more (fp16 32 x 28 x 28
+    // x 512 -> 256, 3x3 at stride 2: with 3 slices instead of 8 1.5e-7 instead of 1.1e-7 in a model of the sums).
+    SplitChoice shortest;
+    if (L.f32_results) shortest = general_split(L, tune);
+    const int64_t longest = shortest.v && shortest.slices > 1 ? shortest.k_per_slice : kt * 64;
     for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = all_variants()[i];
         if (v.persistent) continue;
@@ -372,7 +379,7 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
         // no split, a few slices, and what fills the chip with one to eight workgroups per CU
-        const int64_t fills[] = {1, 2 * tiles, 4 * tiles, 256, 512, 768, 1024, 1536, 2048};
+        const int64_t fills[] = {1, 2 * tiles, 4 * tiles, 256, 512, 768, 1024, 1536, 2048, shortest.slices * tiles};
         for (int64_t fill : fills) {
             int64_t want = (fill + tiles - 1) / tiles;
             if (want > kt / 2) want = kt / 2;
@@ -382,6 +389,7 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
             int slices = 1, kps = 0;
             split_slices(L, want, tiles, 0, slices, kps);
             if (L.mode == 0 && slices == 1) continue;       // (a GEMM that is not split has more kernels: below)
+            if (kps > longest) continue;
             const double t = L.mode == 0 ? estimate_gemm_split_seconds(v, L, slices, kps)
                                          : estimate_wgrad_seconds(v, all_costs()[i], L, slices, slices > 1 ? kps : L.K);
             if (!best.v || t < best_t) {
@@ -408,6 +416,19 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const int64_t bytes = best.slices <= 1 ? 0 : UCL_WORKSPACE_COUNTER_BYTES + (int64_t)best.slices * tiles * best.v->tile_m * best.v->tile_n * 4;
     if (tune->workspace && bytes > tune->workspace_bytes) best.v = nullptr;
     return best;
+}
+
+// Kernels that the general rule chooses among.  Split-K has kernels without K groups only.  And the slices an open call gets are what
+// fills the chip with the chosen tile, so a larger tile makes longer slices, and their fp32 sums round more: fp16 calls stay with the
+// tiles whose slices their results have always had (with all that bf16 has, fp16 -> fp32 512 x 512 x 8192 went from 16 slices
+// to 4 and from 1.1e-7 to 1.5e-7 in a model of the sums, A^T B 4096 x 256 x 16384 from 16 to none, 1.3e-7 to 4.0e-7).
+bool in_general_rule(const VariantDesc &v) {
+    if (v.k_groups > 1) return false;
+    if (v.dt != 1 || v.la == 1 || v.lb == 1) return true;
+    if (v.tile_m * v.tile_n == 64 * 64) return v.tile_k == 32 && v.stages == 3;
+    if (v.mode == 4) return v.tile_k == 32;
+    if (v.la == 5) return v.tile_m * v.tile_n == 256 * 256;
+    return v.lb != 4 || v.tile_m * v.tile_n != 256 * 128;
 }
 
 // Does a variant of L's operation and input type serve its layouts, and the scheduler and iterator that the call names?
@@ -474,7 +495,7 @@ SplitChoice general_split(const Launch &L, const ucl_tuning *tune) {
     double best_t = 0;
     for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = all_variants()[i];
-        if (!serves(v, L, tune) || v.k_groups > 1) continue;          // split-K has kernels without K groups only
+        if (!serves(v, L, tune) || !in_general_rule(v)) continue;
         const double t = estimate_split_seconds(v, L, tune);
         if (!c.v || t < best_t) { best_t = t; c.v = &v; }
     }
@@ -874,6 +895,8 @@ constexpr int kReduceInTileKernel = 2;
 
 ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool clear_counters = false) {
     L.lda = kp.lda; L.ldb = kp.ldb;
+    L.f32_results = L.dtD == UCL_F32;
+    for (int i = 0; i < kp.n_steps; ++i) L.f32_results = L.f32_results || (kp.steps[i].op == UCL_EPI_AUX_STORE && (kp.steps[i].dtype & 0xff) == UCL_F32);
     if (tune && (tune->iterator < 0 || tune->iterator > UCL_ITER_FIXED_STRIDE_DILATION))
         return fail(UCL_ERR_INVALID_ARG, "iterator=%d is not a ucl_conv_iterator", tune->iterator);
     // (the GEMM entry points ignore the iterator)
@@ -1209,6 +1232,9 @@ ucl_status launch_from_problem(const ucl_problem *p, Launch &L) {
     }
     L.dt = dt_code(p->dt_in);
     L.dtD = p->dt_out;
+    L.f32_results = L.dtD == UCL_F32;
+    for (int i = 0; p->epi && i < p->epi->n_steps; ++i)
+        L.f32_results = L.f32_results || (p->epi->steps[i].op == UCL_EPI_AUX_STORE && p->epi->steps[i].dtype == UCL_F32);
     if (L.mode == 2)
         L.patch_c = conv_patch_channels(p->cW, p->cC, p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
     if (L.mode == 3) {

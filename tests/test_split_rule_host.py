@@ -2,7 +2,7 @@
 import pytest
 
 import paper_2603_29010_amd as ucl
-from paper_2603_29010_amd.binding import Tuning
+from paper_2603_29010_amd.binding import Epilogue, Tuning
 
 
 def query(op, dt_in, dt_out, mode, tile=(), **kw):
@@ -21,3 +21,22 @@ def test_no_split_where_the_tiles_fill_the_chip(dt_out, mode, M, N, K, layouts):
 def test_split_where_the_model_splits():
     # (few large tiles: a split pays, though a launch of whole tiles looks cheap to the model that unsplit calls are priced by)
     assert query("gemm", "bf16", "f32", "parallel", M=4096, N=1000, K=32768, a_layout="mn", b_layout="mn")[1] == 4
+
+
+@pytest.mark.parametrize("op,dt_in,slices,problem", [
+    ("gemm", "f16", 16, dict(M=512, N=512, K=8192)),
+    ("gemm", "f16", 16, dict(M=4096, N=256, K=16384, a_layout="mn", b_layout="mn")),
+    ("gemm", "f16", 19, dict(M=848, N=184, K=38496, b_layout="mn")),
+    ("gemm", "bf16", 4, dict(M=4096, N=1000, K=32768, a_layout="mn", b_layout="mn")),
+    ("batched_gemm", "f16", 6, dict(batch=3, M=56, N=1808, K=51096)),
+    ("conv2d_wgrad", "f16", 8, dict(conv=(32, 28, 28, 512, 256, 3, 3, 1, 1, 2, 2, 1, 1))),
+    ("conv2d_wgrad", "bf16", 2, dict(conv=(4, 21, 21, 784, 24, 3, 3, 1, 1, 2, 2, 1, 1)))])
+def test_fp32_results_keep_slices_as_short(op, dt_in, slices, problem):
+    # the slices whose sums an fp32 result of these calls was rounded from before other kernels and rules came; fewer round more
+    assert query(op, dt_in, "f32", "parallel", **problem)[1] >= slices
+
+
+def test_fp32_tensor_stored_by_the_chain_counts_as_a_result():
+    problem = dict(M=200, N=136, K=6000)
+    aux = Epilogue([("aux_store", 4096, "f32", 136)])
+    assert query("gemm", "bf16", "bf16", "parallel", epi=aux, **problem)[1] == query("gemm", "bf16", "f32", "parallel", **problem)[1] > 1
