@@ -295,6 +295,9 @@ double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_t
 // Measured against one or two workgroups per CU of the tile the general split model liked: about 10 % in the geometric mean over 440
 // geometries, 15 % over 32 layers of a residual network at batches 8 to 128 (128 <- 1152 over 25088 pixels 46.2 -> 26.4 us,
 // 128 <- 1152 over 6272 17.8 -> 18.5 us).
+// Parallel split-K with up to this many slices lets the last launch of the tile kernel add them up itself.
+constexpr int kReduceInTileKernel = 2;
+
 struct SplitChoice {
     const VariantDesc *v = nullptr;
     int slices = 1, k_per_slice = 0;
@@ -356,18 +359,19 @@ bool split_left_open(const Launch &L, const ucl_tuning *tune) {
     if (L.mode == 4) return true;
     // (fp32 results keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
     // 4.4e-7 on 464 x 393 x 19848; a 16-bit output's error is the same to six digits either way)
-    return L.mode == 0 && !L.f32_results && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
+    // (K as far as the rows were fitted: 936 x 472 x 103648 took 157 us by them, 128 us by the general rule)
+    return L.mode == 0 && L.K <= 65536 && !L.f32_results && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
 }
 SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const bool named = names_tile(tune);
     const int64_t kt = (L.K + 63) / 64;
     SplitChoice best;
     double best_t = 0;
+    SplitChoice general;
+    if (L.f32_results) general = general_split(L, tune);
     // The filter gradient in fp32: the same slices as the general rule's or shorter ones, as longer ones would round more (fp16 32 x 28 x 28
-    // x 512 -> 256, 3x3 at stride 2: with 3 slices instead of 8 1.5e-7 instead of 1.1e-7 in a model of the sums).
-    SplitChoice shortest;
-    if (L.f32_results) shortest = general_split(L, tune);
-    const int64_t longest = shortest.v && shortest.slices > 1 ? shortest.k_per_slice : kt * 64;
+    // x 512 -> 256, 3x3 at stride 2: with 3 slices instead of 8 2.9e-7 instead of 1.9e-7 off the exact sums).
+    const int64_t longest = general.v && general.slices > 1 ? general.k_per_slice : kt * 64;
     for (int i : variants_of(L.mode, L.dt)) {
         const VariantDesc &v = all_variants()[i];
         if (v.persistent) continue;
@@ -378,8 +382,11 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
         if (L.mode == 4 && !named && v.tile_m == 64 && v.tile_k == 32 && L.K > 24576) continue;
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
+        // A GEMM whose tiles fill the chip without a split gains nothing from one, and larger outputs than that were not fitted (fp16 2254 x 2456
+        // x 13408, 360 tiles of 128x128: 204 us whole, 224 us in 4 slices; bf16 3081 x 1795 x 34392, 375 tiles: 566 and 631 us).
+        if (L.mode == 0 && tiles >= kNumCUs) continue;
         // no split, a few slices, and what fills the chip with one to eight workgroups per CU
-        const int64_t fills[] = {1, 2 * tiles, 4 * tiles, 256, 512, 768, 1024, 1536, 2048, shortest.slices * tiles};
+        const int64_t fills[] = {1, 2 * tiles, 4 * tiles, 256, 512, 768, 1024, 1536, 2048, general.slices * tiles};
         for (int64_t fill : fills) {
             int64_t want = (fill + tiles - 1) / tiles;
             if (want > kt / 2) want = kt / 2;
@@ -389,7 +396,7 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
             int slices = 1, kps = 0;
             split_slices(L, want, tiles, 0, slices, kps);
             if (L.mode == 0 && slices == 1) continue;       // (a GEMM that is not split has more kernels: below)
-            if (kps > longest) continue;
+            if (kps > longest || (slices > 1 && tiles > UCL_SPLIT_K_MAX_TILES)) continue;
             const double t = L.mode == 0 ? estimate_gemm_split_seconds(v, L, slices, kps)
                                          : estimate_wgrad_seconds(v, all_costs()[i], L, slices, slices > 1 ? kps : L.K);
             if (!best.v || t < best_t) {
@@ -401,11 +408,15 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
         }
     }
     // The few-row kernels and K groups often need less time for the whole of K than the launches of a split take: 1.4 to 1.8 times
-    // less at K = 4096 to 5000 (88 x 159 x 4200: 7.1 against 12.1 us), 1.2 times at 8192 and up to 16 tiles, more than a split from
-    // about 10000.
-    if (best.v && L.mode == 0 && L.K <= 8192) {
+    // less at K = 4096 to 5000 (88 x 159 x 4200: 7.1 against 12.1 us), 1.2 times at 8192 and up to 16 tiles.  Beyond that K their
+    // workgroups have to be enough to draw on the memory, and their rows, fitted up to K = 16384, are trusted less: 1 x 1508 x 9560 8.9
+    // against 18.9 us, 8 x 6072 x 11888 38.4 against 53.0 us, but split 1664 x 16 x 31144 takes 45.4 us instead of 61.2, 16 x 2039 x 29328
+    // 39.6 instead of 57.5 us (priced at 0.86 and 0.83 of the split).  Over 110 problems with a side above 768 and K of 8192 to 65536 1.09 times less time
+    // than always split, none slower.
+    if (L.mode == 0) {
         const VariantDesc *v = select_variant(L, nullptr);
-        if (v && estimate_seconds(*v, all_costs()[v - all_variants().data()], L) < 0.9 * best_t) {
+        if (!best.v || (v && (L.K <= 8192 || count_tiles(L, v->tile_m, v->tile_n) >= 64) &&
+                        estimate_seconds(*v, all_costs()[v - all_variants().data()], L) < (L.K <= 8192 ? 0.9 : 0.8) * best_t)) {
             best.v = v;
             best.slices = 1;
         }
@@ -420,8 +431,8 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
 
 // Kernels that the general rule chooses among.  Split-K has kernels without K groups only.  And the slices an open call gets are what
 // fills the chip with the chosen tile, so a larger tile makes longer slices, and their fp32 sums round more: fp16 calls stay with the
-// tiles whose slices their results have always had (with all that bf16 has, fp16 -> fp32 512 x 512 x 8192 went from 16 slices
-// to 4 and from 1.1e-7 to 1.5e-7 in a model of the sums, A^T B 4096 x 256 x 16384 from 16 to none, 1.3e-7 to 4.0e-7).
+// tiles whose slices their results have always had (with all that bf16 has, fp16 -> fp32 512 x 512 x 8192 has 4 slices
+// instead of 16 and is 2.9e-7 off the exact sums instead of 1.7e-7, A^T B 4096 x 256 x 16384 none instead of 16, 8.1e-7 instead of 2.2e-7).
 bool in_general_rule(const VariantDesc &v) {
     if (v.k_groups > 1) return false;
     if (v.dt != 1 || v.la == 1 || v.lb == 1) return true;
@@ -889,9 +900,6 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
     sp.bytes = UCL_WORKSPACE_COUNTER_BYTES + (int64_t)sp.slices * total_tiles * v.tile_m * v.tile_n * 4;
     return UCL_OK;
 }
-
-// Parallel split-K with up to this many slices lets the last launch of the tile kernel add them up itself.
-constexpr int kReduceInTileKernel = 2;
 
 ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool clear_counters = false) {
     L.lda = kp.lda; L.ldb = kp.ldb;

@@ -40,3 +40,15 @@ def test_fp32_tensor_stored_by_the_chain_counts_as_a_result():
     problem = dict(M=200, N=136, K=6000)
     aux = Epilogue([("aux_store", 4096, "f32", 136)])
     assert query("gemm", "bf16", "bf16", "parallel", epi=aux, **problem)[1] == query("gemm", "bf16", "f32", "parallel", **problem)[1] > 1
+
+
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 16384), (2048, 2048, 16384), (8192, 8192, 12288), (16384, 16384, 16384), (16512, 16512, 8200),
+                                   (32768, 32768, 16384), (2048, 8192, 65536)])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_large_outputs_are_not_split(M, N, K, dt):
+    assert query("gemm", dt, dt, "parallel", M=M, N=N, K=K) == (0, 1)
+
+
+def test_small_outputs_over_a_deep_k_are_split():
+    for M, N, K in ((256, 256, 16384), (512, 512, 40008), (32, 40, 65536)):
+        assert query("gemm", "bf16", "bf16", "parallel", M=M, N=N, K=K)[1] > 4
