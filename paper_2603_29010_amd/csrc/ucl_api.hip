@@ -314,7 +314,9 @@ double estimate_wgrad_seconds(const VariantDesc &v, const CostRow &r, const Laun
         SplitCostRow s = {0, 0, 0, 0, 2.f, 2.4f};
         for (const SplitCostRow &c : kWgradSplitRows)
             if (c.tile_m == v.tile_m && c.tile_n == v.tile_n && c.tile_k == v.tile_k && c.stages == v.stages) s = c;
-        t += s.fixed + (double)wgs * v.tile_m * v.tile_n * 4.0 / (s.tbs * 1e6);
+        t += s.fixed + (double)wgs * v.tile_m * v.tile_n * 4.0 / (s.tbs * 1e6) + 0.02 * slices;
+        // (two slices are not added up by the reduction kernel but by another launch of the tile kernel: 5 us more than three, 361 to 2916 pixels)
+        if (slices <= kReduceInTileKernel) t += 5.0;
     }
     return 1e-6 * t;
 }

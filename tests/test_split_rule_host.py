@@ -52,3 +52,15 @@ def test_large_outputs_are_not_split(M, N, K, dt):
 def test_small_outputs_over_a_deep_k_are_split():
     for M, N, K in ((256, 256, 16384), (512, 512, 40008), (32, 40, 65536)):
         assert query("gemm", "bf16", "bf16", "parallel", M=M, N=N, K=K)[1] > 4
+
+
+@pytest.mark.parametrize("conv", [(1, 15, 15, 24, 80, 1, 1, 0, 0, 1, 1, 1, 1), (1, 15, 15, 72, 176, 1, 1, 0, 0, 1, 1, 1, 1),
+                                  (1, 45, 45, 8, 16, 5, 5, 2, 2, 3, 3, 1, 1), (1, 32, 32, 248, 88, 1, 1, 0, 0, 2, 2, 1, 1)])
+def test_filter_gradients_over_few_pixels_are_not_split_in_two(conv):
+    # two slices go through a second launch of the tile kernel, which costs more than 225 to 256 pixels take: 11.2 us instead of 7.3
+    assert query("conv2d_wgrad", "bf16", "f32", "parallel", conv=conv)[1] != 2
+
+
+def test_filter_gradients_of_one_tile_keep_the_slices_few():
+    # every slice is one more load in a chain of the reduction: 196 of them took 13.6 us, 98 take 11.2 us
+    assert query("conv2d_wgrad", "f16", "f32", "parallel", conv=(8, 56, 56, 32, 32, 1, 1, 0, 0, 1, 1, 1, 1))[1] < 128
