@@ -380,8 +380,10 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
         if (L.mode == 0 && !(has_gemm_split_row(v) && panels_fit(v, L))) continue;
         // Over many pixels the two k-tiles that 64x64x32 has in flight, 4 KB of each operand, don't cover the trips to memory: 64 <- 576 columns over
         // 100352 pixels 32.8 us, 64x64x64 26.0 us; 128 <- 576 over as many 53.7 us, 128x128x32 33.9 us.  Below, its four workgroups per CU
-        // do (128 <- 1152 over 6272: 17.0 against 17.0 us, 256 <- 2304 over 1568: 19.4 against 24 us).
-        if (L.mode == 4 && !named && v.tile_m == 64 && v.tile_k == 32 && L.K > 24576) continue;
+        // do (128 <- 1152 over 6272: 17.0 against 17.0 us, 256 <- 2304 over 1568: 19.4 against 24 us).  Between, 54 layers of 20000 to 49152 pixels: with
+        // more than 32 filters it is mostly behind (184 <- 216 over 36000: 21.2 against 18.5 us, 264 <- 1512 over 33300: 97 against 76 us), with up to
+        // 32 mostly ahead (24 <- 2952 over 25200: 36.6 against 41.0 us, 16 <- 1584 over 31360: 28.5 against 32.8 us).
+        if (L.mode == 4 && !named && v.tile_m == 64 && v.tile_k == 32 && L.K > (L.M <= 32 ? 49152 : 24576)) continue;
         if (named && (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.tile_k != tune->tile_k || v.stages != tune->stages)) continue;
         const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
         // A GEMM whose tiles fill the chip without a split gains nothing from one, and larger outputs than that were not fitted (fp16 2254 x 2456

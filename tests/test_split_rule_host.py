@@ -64,3 +64,12 @@ def test_filter_gradients_over_few_pixels_are_not_split_in_two(conv):
 def test_filter_gradients_of_one_tile_keep_the_slices_few():
     # every slice is one more load in a chain of the reduction: 196 of them took 13.6 us, 98 take 11.2 us
     assert query("conv2d_wgrad", "f16", "f32", "parallel", conv=(8, 56, 56, 32, 32, 1, 1, 0, 0, 1, 1, 1, 1))[1] < 128
+
+
+@pytest.mark.parametrize("filters,slices", [(16, 44), (128, None)])
+def test_filter_gradients_of_few_filters_keep_the_small_tile(filters, slices):
+    # up to 32 filters the 64x64x32 kernel stays ahead to 49152 pixels (16 <- 1080 over 25088: 21.5 against 26.5 us)
+    conv = (32, 28, 28, 120, filters, 3, 3, 1, 1, 1, 1, 1, 1)
+    got = query("conv2d_wgrad", "f16", "f32", "parallel", conv=conv)
+    named = query("conv2d_wgrad", "f16", "f32", "parallel", (64, 64, 32, 3), conv=conv)
+    assert (got == named) == (filters <= 32) and slices in (None, got[1])
