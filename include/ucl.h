@@ -374,7 +374,10 @@ ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out);
 
 /* Bytes of workspace a call on problem p with tuning `tune` needs (0 without a split):
  * UCL_WORKSPACE_COUNTER_BYTES + slices x tiles x tile_m x tile_n x 4.  *slices_out (may be NULL)
- * receives the number of K slices the call will use.  With the STREAM_K scheduler:
+ * receives the number of K slices the call will use.  PARALLEL with split_k_slices 0 also covers what
+ * calls on p with other strides or chains may need; given less, or nothing, such a call splits as
+ * far as that allows, by a simpler rule, and is rejected only where that rule needs more.  tune->workspace is
+ * not looked at here.  With the STREAM_K scheduler:
  * UCL_WORKSPACE_COUNTER_BYTES + workgroups x 2 x tile_m x tile_n x 4, *slices_out = the largest
  * number of parts a tile can fall into; the number of workgroups follows from how many of them a
  * CU holds, which is asked of the HIP runtime (this one query needs a device to be present). */

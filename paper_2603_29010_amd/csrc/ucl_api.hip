@@ -425,12 +425,11 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
             best.slices = 1;
         }
     }
-    if (!best.v) return best;
-    // A caller's workspace that holds the partial tiles of the general rule, but not these, goes on serving that rule.
-    const int64_t tiles = count_tiles(L, best.v->tile_m, best.v->tile_n);
-    const int64_t bytes = best.slices <= 1 ? 0 : UCL_WORKSPACE_COUNTER_BYTES + (int64_t)best.slices * tiles * best.v->tile_m * best.v->tile_n * 4;
-    if (tune->workspace && bytes > tune->workspace_bytes) best.v = nullptr;
     return best;
+}
+int64_t split_bytes(const Launch &L, const SplitChoice &c) {
+    if (!c.v || c.slices <= 1) return 0;
+    return UCL_WORKSPACE_COUNTER_BYTES + (int64_t)c.slices * count_tiles(L, c.v->tile_m, c.v->tile_n) * c.v->tile_m * c.v->tile_n * 4;
 }
 
 // Kernels that the general rule chooses among.  Split-K has kernels without K groups only.  And the slices an open call gets are what
@@ -520,12 +519,18 @@ SplitChoice general_split(const Launch &L, const ucl_tuning *tune) {
     return c;
 }
 
-// The kernel of a call, and under split-K the slices chosen with it.
-const VariantDesc *select_with_split(const Launch &L, const ucl_tuning *tune, SplitChoice &choice) {
+// The kernel of a call, and under split-K the slices chosen with it.  A call without a workspace, or with one that the partial tiles of
+// chosen slices don't fit into, is served by the general rule: it may need less, or none at all.  `sizing`: no call yet,
+// any workspace can be had.
+const VariantDesc *select_with_split(const Launch &L, const ucl_tuning *tune, SplitChoice &choice, bool sizing = false) {
     const bool split = tune && tune->split_k_mode != UCL_SPLIT_K_NONE && tune->split_k_slices >= 0 && (L.mode == 0 || L.mode == 4) &&
                        tune->scheduler == UCL_SCHED_DEFAULT;
     if (!split) return select_variant(L, tune);
-    if (split_left_open(L, tune)) choice = choose_split(L, tune);
+    if (split_left_open(L, tune)) {
+        choice = choose_split(L, tune);
+        const int64_t bytes = split_bytes(L, choice);
+        if (!sizing && bytes > 0 && (!tune->workspace || !aligned16(tune->workspace) || bytes > tune->workspace_bytes)) choice = SplitChoice();
+    }
     if (!choice.v) choice = general_split(L, tune);
     return choice.v;
 }
@@ -1545,12 +1550,18 @@ ucl_status ucl_workspace_size(const ucl_problem *p, const ucl_tuning *tune, int6
     if (tune && (tune->iterator < 0 || tune->iterator > UCL_ITER_FIXED_STRIDE_DILATION))
         return fail(UCL_ERR_INVALID_ARG, "iterator=%d is not a ucl_conv_iterator", tune->iterator);
     SplitChoice choice;
-    const VariantDesc *v = select_with_split(L, tune, choice);
+    const VariantDesc *v = select_with_split(L, tune, choice, /*sizing=*/true);
     if (!v) return fail(UCL_ERR_UNSUPPORTED, "no kernel built for this problem and tuning; see ucl_variant()");
     SplitPlan sp;
     if (ucl_status st = plan_split(L, *v, tune, choice, count_tiles(L, v->tile_m, v->tile_n), sp)) return st;
     *bytes = sp.bytes;
     if (slices_out) *slices_out = sp.slices;
+    if (split_left_open(L, tune)) {
+        // (strides that the chosen kernel cannot address, or an fp32 tensor stored by a chain that p does not show, leave the
+        // call to the general rule: what this answers serves that too)
+        const int64_t general = split_bytes(L, general_split(L, tune));
+        if (general > *bytes) *bytes = general;
+    }
     return UCL_OK;
 }
 

@@ -75,3 +75,39 @@ def test_leading_stride_beyond_the_large_tiles():
     ucl.ucl_gemm(M, N, K, A.data_ptr(), "bf16", lda, 1, B.data_ptr(), "bf16", 1, K, D.data_ptr(), "f32", N, 1, None, None,
                  torch.cuda.current_stream().cuda_stream)
     assert torch.equal(D, a.float().contiguous() @ B.float().t())
+
+
+def served(spec, tune, label):
+    check = parity.check_exact if spec["dt_out"] == "f32" else parity.check
+    check(spec, tune, label=label)
+
+
+@pytest.mark.parametrize("what", ["none", "off 16 bytes", "counters only"])
+def test_calls_that_need_no_workspace_by_the_general_rule_run_without_one(what):
+    # the choice would split these, the general rule does not: they always ran with any workspace, or none
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    given = {"none": dict(workspace=0, workspace_bytes=0), "off 16 bytes": dict(workspace=ws.data_ptr() + 8, workspace_bytes=ws.numel() - 8),
+             "counters only": dict(workspace=ws.data_ptr(), workspace_bytes=COUNTERS)}[what]
+    tune = Tuning(split_k="parallel", **given)
+    for dt in ("bf16", "f16"):
+        gemm = synth.gemm_spec(1152, 952, 3128, dt_in=dt, dt_out=dt, epilogue=(), integer=True)
+        assert ucl.ucl_workspace_size("gemm", dt, dt, Tuning(split_k="parallel"), M=1152, N=952, K=3128)[1] > 1
+        served(gemm, tune, f"gemm {dt}, {what}")
+        wgrad = synth.conv_grad_spec("wgrad", dt_in=dt, dt_out="f32", integer=True, Nb=2, H=37, W=37, C=8, Ko=832, R=5, S=5, pad=(2, 2), stride=(3, 3))
+        assert ucl.ucl_workspace_size("conv2d_wgrad", dt, "f32", Tuning(split_k="parallel"), conv=(2, 37, 37, 8, 832, 5, 5, 2, 2, 3, 3, 1, 1))[1] > 1
+        served(wgrad, tune, f"wgrad {dt}, {what}")
+
+
+def test_a_workspace_that_holds_the_general_rule_serves_it():
+    # bytes of the general rule's partial tiles, fewer than those of the slices that would be chosen
+    spec = synth.gemm_spec(8, 8, 9488, dt_in="f16", dt_out="f16", epilogue=(), integer=True)
+    assert ucl.ucl_workspace_size("gemm", "f16", "f16", Tuning(split_k="parallel"), M=8, N=8, K=9488)[0] > 557056
+    ws = workspace(557056)
+    served(spec, tuning(ws), "gemm")
+    spec = synth.conv_grad_spec("wgrad", dt_in="bf16", dt_out="f32", integer=True, Nb=7, H=40, W=40, C=8, Ko=40, R=1, S=1, pad=(0, 0), stride=(3, 3))
+    assert ucl.ucl_workspace_size("conv2d_wgrad", "bf16", "f32", Tuning(split_k="parallel"), conv=(7, 40, 40, 8, 40, 1, 1, 0, 0, 3, 3, 1, 1))[0] > 147456
+    ws = workspace(147456)
+    served(spec, tuning(ws), "wgrad")
+    with pytest.raises(ucl.UclError) as e:           # less than either needs: refused, as it always was
+        served(spec, tuning(ws[:147440]), "wgrad")
+    assert e.value.status == "UCL_ERR_WORKSPACE"

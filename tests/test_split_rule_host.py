@@ -73,3 +73,10 @@ def test_filter_gradients_of_few_filters_keep_the_small_tile(filters, slices):
     got = query("conv2d_wgrad", "f16", "f32", "parallel", conv=conv)
     named = query("conv2d_wgrad", "f16", "f32", "parallel", (64, 64, 32, 3), conv=conv)
     assert (got == named) == (filters <= 32) and slices in (None, got[1])
+
+
+def test_the_size_covers_what_the_general_rule_needs():
+    # a call with other strides, or whose chain stores an fp32 tensor, falls back on that rule (here: 17 slices of one row of 64x64 tiles)
+    assert query("gemm", "bf16", "bf16", "parallel", M=32, N=176, K=5392) == (901120, 1)
+    ws = Tuning(split_k="parallel", workspace=4096, workspace_bytes=16)
+    assert ucl.ucl_workspace_size("gemm", "bf16", "bf16", ws, M=32, N=176, K=5392) == (901120, 1)
