@@ -143,8 +143,13 @@ int64_t count_tiles(const Launch &L, int tm, int tn) {
 }
 
 // Launch description of a data gradient: extents for the tile count, and the mean depth over the residue classes of a
-// strided convolution (every tap meets one class in stride_h * stride_w).
+// strided convolution (every tap meets one class in stride_h * stride_w).  Extents, pads and dilated filters are below 2^24: every
+// stride from kWidestStride on has one output row and pairs it with the same pixels, so wider ones (the kernels count in
+// 32 bits) are taken as that.
+constexpr int64_t kWidestStride = 1ll << 26;
 void dgrad_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t stride_h, int64_t stride_w) {
+    if (stride_h > kWidestStride) stride_h = kWidestStride;
+    if (stride_w > kWidestStride) stride_w = kWidestStride;
     L.cN = N; L.cH = H; L.cW = W; L.str_h = stride_h; L.str_w = stride_w;
     if (stride_h * stride_w > 1) L.K = (L.K + stride_h * stride_w - 1) / (stride_h * stride_w);
 }
@@ -1436,8 +1441,8 @@ ucl_status ucl_conv2d_dgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     KParams kp;
     memset(&kp, 0, sizeof(kp));
     // (the tiles that take longest start first)
-    kp.dg_reverse = dgrad_taps((int)stride_h - 1, (int)pad_h, (int)dil_h, (int)stride_h, (int)R).count >
-                    dgrad_taps(0, (int)pad_h, (int)dil_h, (int)stride_h, (int)R).count;
+    kp.dg_reverse = dgrad_taps((int)L.str_h - 1, (int)pad_h, (int)dil_h, (int)L.str_h, (int)R).count >
+                    dgrad_taps(0, (int)pad_h, (int)dil_h, (int)L.str_h, (int)R).count;
     if (ucl_status st = check_epilogue(epi, L, kp)) return st;
     kp.A = dy; kp.B = w; kp.D = dx;
     kp.a_bytes = N * P * Q * Kout * 2;
@@ -1446,7 +1451,7 @@ ucl_status ucl_conv2d_dgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     kp.M = (int32_t)M; kp.N = (int32_t)C; kp.K = (int32_t)Kg; kp.dtD = dtDx;
     // the gathered tensor is dy: its extents take the place of the image's, the rows are input pixels
     kp.cH = (int32_t)P; kp.cW = (int32_t)Q; kp.cC = (int32_t)Kout; kp.cS = (int32_t)S; kp.cP = (int32_t)H; kp.cQ = (int32_t)W;
-    kp.pad_h = (int32_t)pad_h; kp.pad_w = (int32_t)pad_w; kp.str_h = (int32_t)stride_h; kp.str_w = (int32_t)stride_w;
+    kp.pad_h = (int32_t)pad_h; kp.pad_w = (int32_t)pad_w; kp.str_h = (int32_t)L.str_h; kp.str_w = (int32_t)L.str_w;
     kp.dil_h = (int32_t)dil_h; kp.dil_w = (int32_t)dil_w;
     kp.d_vec = aligned16(dx) && (C % (16 / elem_size(dtDx)) == 0);
     if (is_plain_gemm(R, S, pad_h, pad_w, stride_h, stride_w)) {

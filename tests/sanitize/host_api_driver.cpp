@@ -92,6 +92,11 @@ int main() {
     EXPECT(ucl_grouped_gemm(2, neg, 64, 64, (const void *const *)P, UCL_BF16, 64, 1, (const void *const *)P, UCL_BF16, 1, 64, (void *const *)P, UCL_BF16, 64, 1, nullptr, nullptr, nullptr) == UCL_ERR_INVALID_ARG);
     EXPECT(ucl_conv2d_fprop(1, 8, 8, 3, 8, 3, 3, 1, 1, 1, 1, 1, 1, P, UCL_BF16, P, UCL_BF16, P, UCL_BF16, nullptr, nullptr, nullptr) == UCL_ERR_UNSUPPORTED);
     EXPECT(ucl_conv2d_dgrad(1, 8, 8, 8, 12, 3, 3, 1, 1, 1, 1, 1, 1, P, UCL_BF16, P, UCL_BF16, P, UCL_BF16, nullptr, nullptr, nullptr) == UCL_ERR_UNSUPPORTED);
+    // strides beyond 32 bits (no kernels linked: what is tested is the arithmetic in front of the launch)
+    for (int64_t s : {(int64_t)1 << 26, ((int64_t)1 << 31) + 1, (int64_t)1 << 32, (int64_t)1 << 40, (int64_t)1 << 62}) {
+        EXPECT(ucl_conv2d_dgrad(1, 8, 8, 8, 16, 3, 3, 1, 1, s, 1, 1, 1, P, UCL_BF16, P, UCL_BF16, P, UCL_BF16, nullptr, nullptr, nullptr) == UCL_ERR_UNSUPPORTED);
+        EXPECT(ucl_conv2d_dgrad(1, 8, 8, 8, 16, 3, 3, 1, 1, s, s, 1, 1, P, UCL_BF16, P, UCL_BF16, P, UCL_BF16, nullptr, nullptr, nullptr) == UCL_ERR_UNSUPPORTED);
+    }
     EXPECT(ucl_conv2d_wgrad(1, 2, 2, 8, 8, 5, 5, 0, 0, 1, 1, 1, 1, P, UCL_BF16, P, UCL_BF16, P, UCL_BF16, nullptr, nullptr, nullptr) == UCL_ERR_INVALID_ARG);
     EXPECT(ucl_transpose(1, 64, 64, P, UCL_F32, P, UCL_F32, nullptr) == UCL_ERR_INVALID_ARG);
     EXPECT(ucl_transpose(0, 64, 64, nullptr, UCL_F32, nullptr, UCL_F32, nullptr) == UCL_OK);

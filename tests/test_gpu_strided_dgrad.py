@@ -19,6 +19,8 @@ GEOMS = [
     dict(Nb=2, H=15, W=15, C=16, Ko=24, R=3, S=3, pad=(2, 2), stride=(2, 2), dil=(2, 2)),  # odd residues meet no tap
     dict(Nb=2, H=15, W=16, C=16, Ko=24, R=4, S=3, pad=(3, 1), stride=(2, 3), dil=(3, 2)),
     dict(Nb=2, H=4, W=5, C=8, Ko=8, R=2, S=2, pad=(1, 1), stride=(7, 6)),               # stride beyond the image
+    dict(Nb=2, H=4, W=5, C=8, Ko=16, R=3, S=3, pad=(1, 1), stride=((1 << 32), 2)),      # strides beyond 32 bits: one output row
+    dict(Nb=2, H=4, W=5, C=8, Ko=16, R=3, S=3, pad=(2, 1), stride=((1 << 31) + 3, 1 << 40)),
     dict(Nb=1, H=1, W=33, C=8, Ko=64, R=1, S=3, pad=(0, 1), stride=(1, 2)),
 ]
 
