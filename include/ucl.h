@@ -187,9 +187,9 @@ typedef enum ucl_tile_scheduler { UCL_SCHED_DEFAULT = 0, UCL_SCHED_PERSISTENT = 
  * overlap in time.  Without a split, workspace is ignored.
  * scheduler is a ucl_tile_scheduler; STREAM_K uses the workspace in the same way (zeroed counters, left zero).
  * k_groups: groups of four wavefronts that share a tile inside one workgroup, each multiplying its own part of K
- * (their sums meet in LDS in group order; no workspace).  With no tile named the library chooses.  With a tile
- * named, 0 takes the kernel of that shape without K groups if one is built, else the one with; n > 1 takes the
- * one built with n groups (ucl_variant_k_groups()), 1 the one without. */
+ * (their sums meet in LDS in group order; no workspace).  Looked at only where a tile is named and no split: the
+ * kernel of that shape with so many groups (ucl_variant_k_groups()) is taken if one is built; otherwise, as for 0,
+ * the one without K groups, or failing that the one with.  Split-K has kernels without K groups only. */
 typedef struct ucl_tuning {
     int32_t tile_m, tile_n, tile_k, stages, raster;
     int32_t iterator;

@@ -367,7 +367,7 @@ bool split_left_open(const Launch &L, const ucl_tuning *tune) {
     // (fp32 results keep the slices of the general rule: the sums' rounding shows in them, and longer slices round more, 2.2e-7 to
     // 4.4e-7 on 464 x 393 x 19848; a 16-bit output's error is the same to six digits either way)
     // (K as far as the rows were fitted: 936 x 472 x 103648 took 157 us by them, 128 us by the general rule)
-    return L.mode == 0 && L.K <= 65536 && !L.f32_results && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && tune->k_groups == 0 && !names_tile(tune);
+    return L.mode == 0 && L.K <= 65536 && !L.f32_results && L.batch == 1 && L.la == 0 && L.lb == 0 && (L.dt == 0 || L.dt == 1) && !names_tile(tune);
 }
 SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     const bool named = names_tile(tune);
@@ -476,13 +476,12 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         if (names_tile(tune)) {
             if (v.tile_m != tune->tile_m || v.tile_n != tune->tile_n || v.stages != tune->stages || v.tile_k != tune->tile_k)
                 continue;
-            if (tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
-            if (v.stages == 1 && tune->split_k_mode != UCL_SPLIT_K_NONE) continue;      // (no partial tiles in the few-row kernels)
-            // of several kernels with the named shape: the resident-patch one, else one without K groups (unless named),
+            if (v.k_groups > 1 && tune->split_k_mode != UCL_SPLIT_K_NONE) continue;     // (split-K has kernels without K groups only)
+            // of several kernels with the named shape: the resident-patch one, else one with the K groups named, else one without,
             // else a direct-copy one, else the first
             if (v.la == 3) return &v;
             if (best && best->k_groups != v.k_groups) {
-                if (v.k_groups < best->k_groups) best = &v;
+                if (best->k_groups != tune->k_groups && (v.k_groups == tune->k_groups || v.k_groups < best->k_groups)) best = &v;
                 continue;
             }
             const bool direct = v.la == 5 || v.lb == 4;
@@ -493,7 +492,6 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         // calls have workgroups enough without them unless K is deep (49 experts of 2400 columns, bf16: K = 576 40 us
         // against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 52 of 976, K = 1152: 23 against 20 us).
         if (v.stages == 1 && L.K < (L.mode == 1 ? 1408 : 320)) continue;
-        if (tune && tune->k_groups > 0 && v.k_groups != tune->k_groups) continue;
         const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);

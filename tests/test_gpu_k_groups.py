@@ -61,6 +61,16 @@ def test_exact(v):
         parity.check_exact(spec, tuning(v), label=f"{ident(v)} {g}")
 
 
+@pytest.mark.parametrize("mode,slices", [("serial", 4), ("parallel", 2), ("parallel", 5)])
+def test_named_k_groups_leave_split_k_alone(mode, slices):
+    # split-K has kernels without K groups only: the one of the named shape runs
+    spec = synth.gemm_spec(200, 136, 1992, dt_out="f32", epilogue=(), integer=True)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    ucl.ucl_workspace_init(ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    tune = Tuning(64, 64, 64, 4, split_k=mode, slices=slices, k_groups=2, workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+    parity.check_exact(spec, tune, label=f"{mode} x{slices}")
+
+
 def test_few_row_kernels_refuse_split_k():
     v = next(v for v in VARIANTS if v["stages"] == 1 and v["mode"] == 0)
     spec = synth.gemm_spec(16, 64, 4096, dt_in=v["dt"])

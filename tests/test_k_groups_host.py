@@ -1,0 +1,38 @@
+"""ucl_tuning.k_groups names a kernel where there is one and is never a reason to refuse a call: the word was reserved and
+ignored before it had a meaning (host only)."""
+import pytest
+
+import paper_2603_29010_amd as ucl
+from paper_2603_29010_amd.binding import Tuning, UclError
+
+PROBLEM = dict(M=200, N=136, K=1992)
+
+
+@pytest.mark.parametrize("k_groups", [-1, 1, 2, 3, 4, 7, 1 << 30])
+def test_served_whatever_it_holds(k_groups):
+    for dt in ("bf16", "f16", "e4m3"):
+        problem = dict(PROBLEM, K=2000)
+        for tile in ((), (64, 64, 64, 4), (128, 128, 64, 2)):
+            assert ucl.ucl_workspace_size("gemm", dt, "bf16", Tuning(*tile, k_groups=k_groups), **problem) == (0, 1)
+    conv = (2, 9, 7, 40, 72, 3, 3, 1, 1, 1, 1, 1, 1)
+    for op in ("conv2d_fprop", "conv2d_dgrad", "conv2d_wgrad"):
+        assert ucl.ucl_workspace_size(op, "bf16", "bf16", Tuning(k_groups=k_groups), conv=conv) == (0, 1)
+
+
+@pytest.mark.parametrize("mode", ["serial", "parallel"])
+def test_split_k_does_not_look_at_it(mode):
+    for tile in ((), (64, 64, 64, 4)):
+        for dt_out in ("bf16", "f32"):
+            plain = ucl.ucl_workspace_size("gemm", "bf16", dt_out, Tuning(*tile, split_k=mode), M=200, N=136, K=30000)
+            assert plain[1] > 1
+            assert ucl.ucl_workspace_size("gemm", "bf16", dt_out, Tuning(*tile, split_k=mode, k_groups=2), M=200, N=136, K=30000) == plain
+
+
+def test_shapes_built_with_k_groups_only_serve_no_split():
+    conv = (2, 9, 7, 40, 72, 3, 3, 1, 1, 1, 1, 1, 1)
+    assert ucl.ucl_workspace_size("conv2d_fprop", "bf16", "bf16", Tuning(128, 64, 64, 3), conv=conv) == (0, 1)
+    for tile in ((16, 32, 64, 1), (32, 32, 64, 1)):
+        assert ucl.ucl_workspace_size("gemm", "bf16", "bf16", Tuning(*tile), **PROBLEM) == (0, 1)
+        with pytest.raises(UclError) as e:
+            ucl.ucl_workspace_size("gemm", "bf16", "bf16", Tuning(*tile, split_k="parallel", slices=4), **PROBLEM)
+        assert e.value.status == "UCL_ERR_UNSUPPORTED"
