@@ -194,7 +194,7 @@ class Tuning:
         return C.byref(self.c)
 
     def as_dict(self):
-        return {k: getattr(self.c, k) for k in ("tile_m", "tile_n", "tile_k", "stages", "raster", "iterator")}
+        return {k: getattr(self.c, k) for k in ("tile_m", "tile_n", "tile_k", "stages", "raster", "iterator", "k_groups")}
 
 
 def _opt(x):

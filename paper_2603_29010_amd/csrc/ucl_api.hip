@@ -540,8 +540,9 @@ const VariantDesc *select_with_split(const Launch &L, const ucl_tuning *tune, Sp
 
 // A 1x1 convolution at unit stride without padding IS a GEMM over the pixels: its forward pass (pixels x channels times filter
 // rows) and its data gradient (output gradient times the filter, contiguous along N) run on the GEMM kernels, which copy rows
-// instead of gathering taps and come in more tiles.  Convolution kernels that the caller names, their iterator or another
-// scheduler among it, are taken as named; a GEMM tile can be named too.
+// instead of gathering taps and come in more tiles.  A named tile is the GEMM kernel's where one is built (what ucl_select_tuning
+// answers names the same kernel again), else the convolution kernel's; with an iterator named, or another
+// scheduler, it is the convolution kernel's.
 bool is_plain_gemm(int64_t R, int64_t S, int64_t pad_h, int64_t pad_w, int64_t stride_h, int64_t stride_w) {
     return R == 1 && S == 1 && pad_h == 0 && pad_w == 0 && stride_h == 1 && stride_w == 1;
 }
@@ -560,7 +561,6 @@ bool takes_gemm(const Launch &conv, const Launch &gemm, const ucl_tuning *tune) 
     if (conv.mode == 2 && conv.K < 128 && !names_tile(tune)) return false;
     if (!tune) return true;
     if (tune->split_k_mode != UCL_SPLIT_K_NONE || tune->split_k_slices != 0 || tune->scheduler != UCL_SCHED_DEFAULT || tune->iterator != UCL_ITER_DEFAULT) return false;
-    if (names_tile(tune) && select_variant(conv, tune)) return false;
     return select_variant(gemm, tune) != nullptr;
 }
 

@@ -1,9 +1,11 @@
 """1x1 convolutions at unit stride without padding run on the GEMM kernels: exact with the library's choice, with named GEMM
 and convolution tiles and with the gather iterator; the choice can be named again."""
 import pytest
+import torch
 
 from paper_2603_29010_amd import synth
 from paper_2603_29010_amd.binding import Tuning
+from paper_2603_29010_amd.workload import DeviceWorkload
 
 import paper_2603_29010_amd as ucl
 import parity
@@ -22,13 +24,37 @@ def test_exact(geom, op, dt):
     spec = make(dt_in=dt, dt_out="f32", epilogue=(), integer=True)
     conv = (g["Nb"], g["H"], g["W"], g["C"], g["Ko"], 1, 1, 0, 0, 1, 1, 1, 1)
     t = ucl.ucl_select_tuning(f"conv2d_{op}", dt, "f32", conv=conv)
-    named = Tuning(t["tile_m"], t["tile_n"], t["tile_k"], t["stages"], t["raster"], t["iterator"])
+    named = Tuning(**t)
     for tune in (None, named, Tuning(64, 64, 32, 3), Tuning(128, 128, 64, 2), Tuning(iterator=1), Tuning(raster=2)):
-        if tune is not None and op == "dgrad" and (tune.c.tile_m, tune.c.tile_k) == (128, 64) and tune is not named and dt == "f16":
-            continue
         parity.check_exact(spec, tune, label=f"{op} {dt} {geom} {tune and tune.as_dict()}")
     spec = make(dt_in=dt, dt_out=dt, epilogue=("bias", "aux_load", "relu"))
     parity.check(spec, None, label=f"{op} {dt} {geom} chain")
+
+
+def kernels_of(spec, tune):
+    w = DeviceWorkload(spec)
+    w.run(tune=tune)
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        w.run(tune=tune)
+        torch.cuda.synchronize()
+    return [e.name for e in p.events() if "ucl_" in e.name]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("op", ["fprop", "dgrad"])
+@pytest.mark.parametrize("geom", [dict(Nb=3, H=28, W=28, C=128, Ko=256), dict(Nb=2, H=7, W=7, C=1024, Ko=512), dict(Nb=1, H=4, W=4, C=512, Ko=512)],
+                         ids=lambda g: "x".join(str(v) for v in g.values()))
+def test_the_choice_can_be_named_again(geom, op, dt):
+    g = dict(geom, R=1, S=1, pad=(0, 0))
+    make = (lambda **k: synth.conv_spec(**g, **k)) if op == "fprop" else (lambda **k: synth.conv_grad_spec("dgrad", **g, **k))
+    spec = make(dt_in=dt, dt_out=dt, epilogue=())
+    conv = (g["Nb"], g["H"], g["W"], g["C"], g["Ko"], 1, 1, 0, 0, 1, 1, 1, 1)
+    chosen = kernels_of(spec, None)
+    assert len(chosen) == 1
+    assert kernels_of(spec, Tuning(**ucl.ucl_select_tuning(f"conv2d_{op}", dt, dt, conv=conv))) == chosen
+    gather = kernels_of(spec, Tuning(64, 64, 32, 3, iterator=1))
+    assert len(gather) == 1 and gather != chosen and gather != kernels_of(spec, Tuning(64, 64, 32, 3))
 
 
 def test_what_was_refused_stays_refused():
