@@ -122,7 +122,8 @@ typedef struct ucl_epilogue {
  * every geometry.  FIXED_STRIDE_DILATION (3x3 filter, unit stride and dilation, pad 1,
  * W <= 58; fprop: C = 64 or 128, dgrad: Kout = 64 or 128) copies the pixels a tile needs into LDS
  * once and reads all nine taps from there.  DEFAULT: the table takes the second where it
- * applies.  conv2d_wgrad accepts any valid value and ignores it. */
+ * applies; 1x1 filters at unit stride without padding run on the GEMM kernels (a named tile on the GEMM kernel of that
+ * shape if one is built, else on the gathering one).  conv2d_wgrad accepts any valid value and ignores it. */
 typedef enum ucl_conv_iterator {
     UCL_ITER_DEFAULT = 0,
     UCL_ITER_ANALYTIC = 1,
@@ -395,7 +396,7 @@ ucl_status ucl_workspace_init(void *workspace, int64_t workspace_bytes, void *st
 ucl_status ucl_tile_map(int32_t groups, const int32_t *tiles_m, int32_t tiles_n, int32_t raster,
                         int32_t wg, int32_t *group, int32_t *tile_m, int32_t *tile_n);
 
-/* The kernel variants built in.  An explicit ucl_tuning must name the (tile_m,
+/* The kernel variants built in (the few-row kernels follow behind ucl_num_variants(), see below).  An explicit ucl_tuning must name the (tile_m,
  * tile_n, tile_k, stages[, iterator]) of a variant built for the call's operation,
  * input type and operand layouts. */
 typedef struct ucl_variant_info {

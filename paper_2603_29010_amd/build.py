@@ -59,6 +59,50 @@ def _check_asm(obj):
                     any("s_cbranch_execnz" in x for x in lines[k + 1:k + 6]):
                 raise RuntimeError(f"{asm}: line {k + 1}: a global -> LDS copy sits in a readfirstlane loop "
                                    "(its buffer resource is held in vector registers)")
+        bad = early_use_of_transpose_reads(lines)
+        if bad:
+            raise RuntimeError(f"{asm}: line {bad[0]}: `{bad[1]}` touches the result of a transpose read that may still be in flight")
+
+
+def _vregs(text):
+    out = set()
+    for m in re.finditer(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)", text):
+        first, last = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
+        out |= {(m.group(1), i) for i in range(int(first), int(last) + 1)}
+    return out
+
+
+def early_use_of_transpose_reads(lines):
+    """The kernels' transpose reads are asm statements, for which the compiler counts no waits: the first (line number, instruction)
+    that touches the destination of one before a wait covers it, or None.  LDS accesses return in order; lines are taken
+    as they stand (a loop's back edge is not followed)."""
+    pending = []                                      # destinations of the LDS accesses in flight, oldest first
+    for number, line in enumerate(lines, 1):
+        ins = line.split(";")[0].strip()
+        if not ins or ins.startswith("."):
+            continue
+        if ins.endswith(":"):
+            if ins.startswith("_Z"):
+                pending = []
+            continue
+        op = ins.split()[0]
+        if op == "s_waitcnt":
+            m = re.search(r"lgkmcnt\((\d+)\)", ins)
+            if m:
+                keep = int(m.group(1))
+                pending = pending[len(pending) - keep:] if 0 < keep < len(pending) else pending if keep else []
+            elif re.fullmatch(r"s_waitcnt\s+0", ins):
+                pending = []
+            continue
+        if any(pending):
+            used = _vregs(ins[len(op):])
+            if any(used & dst for dst in pending):
+                return number, ins
+        if op == "ds_read_b64_tr_b16":
+            pending.append(_vregs(ins[len(op):].split(",")[0]))
+        elif op.startswith("ds_") or op.startswith("s_load"):
+            pending.append(set())
+    return None
 
 
 def build(force=False, jobs=None, verbose=False):

@@ -1201,7 +1201,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     // order, so it has arrived once at most W reads are outstanding, W being a number of reads known
     // to have been issued after it (2: the two transpose reads of the previous row block's request).  A ring of two
     // requests it in the row block just before, behind which only that row block's B fragments follow: none of them if
-    // that was the last row block of a k-step.
+    // that was the last row block of a k-step.  (Where B is contiguous along K its fragments are ordinary loads, which the compiler could
+    // move to either side; waiting for everything there would cost 1.6 %.  build.py refuses a listing in which a wait
+    // no longer covers the transpose reads.)
     auto a_ready = [&](auto w_) __attribute__((always_inline)) {
         constexpr int W = decltype(w_)::value;
         if constexpr (LA == kMDirect && W >= 0) __builtin_amdgcn_s_waitcnt((0xF) | (0x3 << 14) | (0x7 << 4) | (W << 8));

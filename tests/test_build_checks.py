@@ -1,0 +1,22 @@
+"""What the build refuses in the kernels' listings (host only)."""
+from paper_2603_29010_amd.build import early_use_of_transpose_reads
+
+READ_A = ["ds_read_b64_tr_b16 v[10:11], v2", "ds_read_b64_tr_b16 v[12:13], v2 offset:1024"]
+READ_B = ["ds_read_b128 v[20:23], v3", "ds_read_b128 v[24:27], v3 offset:2048"]
+MUL = ["v_mfma_f32_16x16x32_bf16 v[0:3], v[20:23], v[10:13], v[0:3]"]
+
+
+def scan(*parts):
+    return early_use_of_transpose_reads(["_ZN3ucl6kernelE:"] + [line for part in parts for line in part])
+
+
+def test_a_wait_has_to_cover_the_transpose_read():
+    assert scan(READ_A, MUL) == (4, MUL[0])
+    assert scan(READ_A, READ_B, ["s_waitcnt lgkmcnt(2)"], MUL) is None
+    # the same wait with the ordinary loads moved ahead of the transpose reads, or behind the wait: it covers nothing
+    assert scan(READ_B, READ_A, ["s_waitcnt lgkmcnt(2)"], MUL) is not None
+    assert scan(READ_A, ["s_waitcnt lgkmcnt(2)"], READ_B, MUL) is not None
+    assert scan(READ_B, READ_A, ["s_waitcnt lgkmcnt(0)"], MUL) is None
+    assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0)"], MUL) is not None
+    assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0) lgkmcnt(0)"], MUL) is None
+    assert scan(READ_A, ["v_add_u32_e32 v12, 1, v4"], ["s_waitcnt lgkmcnt(0)"]) is not None        # overwritten in flight
