@@ -464,6 +464,20 @@ bool serves(const VariantDesc &v, const Launch &L, const ucl_tuning *tune) {
 }
 bool names_tile(const ucl_tuning *tune) { return tune && (tune->tile_m || tune->tile_n || tune->tile_k || tune->stages); }
 
+// Is a few-row kernel a candidate where no tile is named?  (L.K counts pairs for 8-bit inputs.)
+// GEMM: from the second 64-wide step of a wave's row on; measured over 104 problems of up to 600 rows and K of 72 to 640 they are 4 to 32 %
+// ahead of the tile kernels wherever the cost rows choose them, none behind.  16-bit inputs at K up to 256, where that is 4 to 20 %, stay
+// with the tile kernels that ucl_select_tuning has always reported for them.
+// Grouped: with a tile for each CU at most they are ahead from K = 256 on (6 groups of 896 columns, e4m3, K = 960: 4.5 against 5.7 us; 7 of 832
+// columns bf16 4.8 against 6.1 us); with more tiles there are workgroups enough without them unless K is deep (49 experts of 2400
+// columns, bf16: K = 576 40 us against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 54 of 3704, K = 1088: 99 against
+// 89 us; e4m3 64 of 2048, K = 1024: 33.8 against 32.6 us).  Convolutions: five steps, as their row was fitted.
+bool few_rows_apply(const VariantDesc &v, const Launch &L) {
+    if (L.mode == 1) return L.K >= 1408 || (L.K >= 128 && count_tiles(L, v.tile_m, v.tile_n) <= kNumCUs);
+    if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256);
+    return L.K >= 320;
+}
+
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
     const auto &costs = all_costs();
@@ -488,10 +502,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
             if (!best || (direct && !(best->la == 5 || best->lb == 4))) best = &v;
             continue;
         }
-        // The few-row kernels overlap the steps of their waves: below five steps of K there is nothing to overlap.  Grouped
-        // calls have workgroups enough without them unless K is deep (49 experts of 2400 columns, bf16: K = 576 40 us
-        // against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 52 of 976, K = 1152: 23 against 20 us).
-        if (v.stages == 1 && L.K < (L.mode == 1 ? 1408 : 320)) continue;
+        if (v.stages == 1 && !few_rows_apply(v, L)) continue;
         const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);

@@ -36,3 +36,13 @@ def test_shapes_built_with_k_groups_only_serve_no_split():
         with pytest.raises(UclError) as e:
             ucl.ucl_workspace_size("gemm", "bf16", "bf16", Tuning(*tile, split_k="parallel", slices=4), **PROBLEM)
         assert e.value.status == "UCL_ERR_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("kw,few_rows", [
+    (dict(op="grouped_gemm", dt="e4m3", M_g=[20, 4, 27, 30], N=304, K=704), True), (dict(op="grouped_gemm", dt="bf16", M_g=[21, 20], N=616, K=640), True),
+    (dict(op="grouped_gemm", dt="e4m3", M_g=[(7 * g) % 33 for g in range(64)], N=2048, K=1024), False),
+    (dict(op="grouped_gemm", dt="bf16", M_g=[30] * 49, N=2400, K=576), False),
+    (dict(op="gemm", dt="e4m3", M=25, N=21, K=608), True), (dict(op="gemm", dt="bf16", M=55, N=101, K=296), True), (dict(op="gemm", dt="bf16", M=256, N=256, K=256), False)])
+def test_where_the_few_row_kernels_begin(kw, few_rows):
+    kw = dict(kw)
+    assert (ucl.ucl_select_tuning(kw.pop("op"), kw.pop("dt"), "bf16", **kw)["stages"] == 1) == few_rows
