@@ -1,6 +1,6 @@
 """The selection table against measurement: on a handful of problem shapes every built variant that
-serves the problem is timed, and the table's pick must not be slower than the fastest of them by
-more than 10 % (the table aims at 6 %; launch-to-launch noise on a shared box is a few percent)."""
+serves the problem is timed (by name, K groups and few-row kernels among them), and what the library runs by itself must not be
+slower than the fastest of them by more than 10 % (the table aims at 6 %; launch-to-launch noise on a shared box is a few percent)."""
 import statistics
 
 import pytest
@@ -50,7 +50,33 @@ SHAPES = {
     "gemm 8192x512x512": lambda: synth.gemm_spec(8192, 512, 512, scale=1 / 22, epilogue=("silu",)),
     "gemm 256^3": lambda: synth.gemm_spec(256, 256, 256, epilogue=("bias", "relu")),
     "batched 64x512x512x128 fp16 -> fp32": lambda: synth.config(3),
+    "decode 16x4096x4096": lambda: synth.gemm_spec(16, 4096, 4096, epilogue=("bias", "silu")),
+    "decode 16x4096x4096 e4m3": lambda: synth.gemm_spec(16, 4096, 4096, dt_in="e4m3", epilogue=("bias", "silu")),
+    "ragged 1000x1001x1992 fp16": lambda: synth.gemm_spec(1000, 1001, 1992, dt_in="f16", dt_out="f16", epilogue=("bias", "aux_load", "relu")),
+    "A^T B 4096x1024x8192 -> fp32": lambda: synth.gemm_spec(4096, 1024, 8192, dt_out="f32", a_layout="col", b_layout="row", epilogue=()),
+    "row-major 256^3": lambda: synth.gemm_spec(256, 256, 256, b_layout="row", epilogue=("bias", "relu")),
+    "grouped 64 x 0..32 rows, e4m3": lambda: synth.grouped_spec([(7 * g) % 33 for g in range(64)], 2048, 1024, dt_in="e4m3"),
+    "grouped 8 x 4..32 rows, K 2048": lambda: synth.grouped_spec([4 + 4 * g for g in range(8)], 1024, 2048),
 }
+
+
+# 16-bit inputs at K up to 256 stay with the tile kernels, though the few-row kernels are up to 20 % ahead there
+BOUND = {"gemm 256^3": 1.25}
+
+
+def kernels_for(w):
+    """{(tile, stages, k groups): Tuning} of every built kernel that serves the workload, the few-row kernels too."""
+    s, kw, i, out = w.spec, w._problem_kwargs(), 0, {}
+    while True:
+        try:
+            v = ucl.ucl_variant(i)
+        except ucl.UclError:
+            return out
+        i += 1
+        want = (1 if w.op == "grouped_gemm" else 0, s["dt_in"], kw["a_layout"] == "mn", kw["b_layout"] == "mn", 0)
+        if (v["mode"], v["dt"], bool(v["a_layout"]), bool(v["b_layout"]), v["scheduler"]) == want and 1 not in (v["a_path"], v["b_path"]):
+            key = (v["tile_m"], v["tile_n"], v["tile_k"], v["stages"], v["k_groups"])
+            out[key] = Tuning(*key[:4], k_groups=key[4])
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
@@ -59,18 +85,18 @@ def test_table_pick_is_near_the_fastest_built_variant(name):
     w = DeviceWorkload(spec, poison=False)
     spin_up(w)
     pick = w.selected()
-    pick_key = (pick["tile_m"], pick["tile_n"], pick["tile_k"], pick["stages"])
-    times = {}
-    for tile in built(0, f16=int(spec["dt_in"] == "f16")):
-        times[tile] = time_us(w, Tuning(*tile))
+    pick_key = tuple(pick[k] for k in ("tile_m", "tile_n", "tile_k", "stages", "k_groups"))
+    named = kernels_for(w)
+    times = {key: time_us(w, tune) for key, tune in named.items()}
     assert pick_key in times, (pick_key, sorted(times))
-    t_pick = min(times[pick_key], time_us(w, None))
+    t_pick = time_us(w, None)
     best = min(times, key=times.get)
-    if t_pick > 1.10 * times[best]:
+    bound = BOUND.get(name, 1.10)
+    if t_pick > bound * times[best]:
         # one more reading of the two before judging (a neighbour's burst on a shared box moves a 20-launch reading by more)
-        t_pick = min(t_pick, time_us(w, None), time_us(w, Tuning(*pick_key)))
-        times[best] = max(times[best], time_us(w, Tuning(*best)))
-    assert t_pick <= 1.10 * times[best], (f"{name}: the table picks {pick_key} at {t_pick:.1f} us, "
+        t_pick = min(t_pick, time_us(w, None))
+        times[best] = max(times[best], time_us(w, named[best]))
+    assert t_pick <= bound * times[best], (f"{name}: the library runs {pick_key} at {t_pick:.1f} us, "
                                           f"{best} runs {times[best]:.1f} us; all: " +
                                           ", ".join(f"{k}: {v:.1f}" for k, v in sorted(times.items(), key=lambda kv: kv[1])))
 

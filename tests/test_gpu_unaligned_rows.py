@@ -15,7 +15,8 @@ GUARD = 99.0
 
 @pytest.mark.parametrize("dt_out", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("chain", ["fused", "steps"])
-@pytest.mark.parametrize("tile", [(64, 64, 32, 3), (128, 128, 32, 4)])
+@pytest.mark.parametrize("tile", [(64, 64, 32, 3), (128, 128, 32, 4), (256, 128, 32, 3), (64, 64, 64, 4, 2), (16, 16, 64, 1), (16, 32, 64, 1),
+                                  (32, 32, 64, 1), (32, 64, 64, 1)])
 def test_rows_at_any_alignment(dt_out, chain, tile):
     g = torch.Generator().manual_seed(7)
     M, K, off = 70, 64, 1
@@ -36,7 +37,8 @@ def test_rows_at_any_alignment(dt_out, chain, tile):
         steps = [("bias", at(bs), dt_out), ("aux_load", at(res), dt_out, ld, 0, 2.0)]
         if chain == "steps":
             steps.append(("aux_store", at(aux), dt_out, ld))
-        ucl.ucl_gemm(M, N, K, a.data_ptr(), "bf16", K, 1, b.data_ptr(), "bf16", 1, K, at(out), dt_out, ld, 1, Epilogue(steps), Tuning(*tile),
+        ucl.ucl_gemm(M, N, K, a.data_ptr(), "bf16", K, 1, b.data_ptr(), "bf16", 1, K, at(out), dt_out, ld, 1, Epilogue(steps),
+                     Tuning(*tile[:4], k_groups=sum(tile[4:])),
                      torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         for name, t in (("D", out), ("aux", aux))[:2 if chain == "steps" else 1]:
