@@ -503,6 +503,12 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
             continue;
         }
         if (v.stages == 1 && !few_rows_apply(v, L)) continue;
+        // A^T B of one row or column of up to 64 64x64 tiles: the fitted rows price the 128x128 kernel with K groups, whose copies bound
+        // every problem it was fitted on, without its chain, and the 64x64 one without them below the one with (8 x 8 x 2048 fp32:
+        // 15.4, 9.2 and 8.6 us; 8 x 24 x 7168 36.4, 23.2 and 19.3 us; 64 x 4096 x 2048 12.5 us without, 12.2 with).
+        if (L.mode == 0 && v.la == 5 && v.lb == 4 && (L.M <= 64 || L.N <= 64) && count_tiles(L, 64, 64) <= 64 &&
+            (v.tile_m == 128 ? v.k_groups > 1 : v.tile_m == 64 && v.tile_k == 64 && v.k_groups == 1 && L.K >= 2048))
+            continue;
         const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);

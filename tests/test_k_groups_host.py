@@ -46,3 +46,10 @@ def test_shapes_built_with_k_groups_only_serve_no_split():
 def test_where_the_few_row_kernels_begin(kw, few_rows):
     kw = dict(kw)
     assert (ucl.ucl_select_tuning(kw.pop("op"), kw.pop("dt"), "bf16", **kw)["stages"] == 1) == few_rows
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_small_products_of_transposed_operands_take_small_tiles(dt):
+    for (M, N, K) in ((8, 8, 2048), (8, 24, 7168), (64, 64, 4096), (40, 512, 3000)):
+        t = ucl.ucl_select_tuning("gemm", dt, "f32", M=M, N=N, K=K, a_layout="mn", b_layout="mn")
+        assert (t["tile_m"], t["tile_n"], t["tile_k"], t["k_groups"]) == (64, 64, 64, 2)
