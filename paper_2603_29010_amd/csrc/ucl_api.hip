@@ -509,6 +509,9 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         if (L.mode == 0 && v.la == 5 && v.lb == 4 && (L.M <= 64 || L.N <= 64) && count_tiles(L, 64, 64) <= 64 &&
             (v.tile_m == 128 ? v.k_groups > 1 : v.tile_m == 64 && v.tile_k == 64 && v.k_groups == 1 && L.K >= 2048))
             continue;
+        // K groups of the data gradient: with fewer than three k-tiles for each of the two there is nothing to share out (24 <- 32 at 3x3, 9 x 5 x 5:
+        // 9.7 against 8.3 us, 24 <- 24 over 3 x 24 x 24 9.7 against 8.6 us).
+        if (L.mode == 3 && v.k_groups > 1 && L.K < 320) continue;
         const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);

@@ -53,3 +53,8 @@ def test_small_products_of_transposed_operands_take_small_tiles(dt):
     for (M, N, K) in ((8, 8, 2048), (8, 24, 7168), (64, 64, 4096), (40, 512, 3000)):
         t = ucl.ucl_select_tuning("gemm", dt, "f32", M=M, N=N, K=K, a_layout="mn", b_layout="mn")
         assert (t["tile_m"], t["tile_n"], t["tile_k"], t["k_groups"]) == (64, 64, 64, 2)
+
+
+def test_data_gradients_of_few_taps_have_nothing_for_k_groups():
+    for conv in ((9, 5, 5, 24, 32, 3, 3, 1, 1, 1, 1, 1, 1), (3, 24, 24, 24, 24, 3, 3, 1, 1, 1, 1, 1, 1)):
+        assert ucl.ucl_select_tuning("conv2d_dgrad", "bf16", "bf16", conv=conv)["k_groups"] == 1
