@@ -109,7 +109,7 @@ struct Launch {
     int dtD = 0;
     int groups = 0;
     const int64_t *M_g = nullptr;
-    int64_t max_Mg = 0, sum_Mg = 0;
+    int64_t sum_Mg = 0;
     int patch_c = 0;              // conv: the problem fits the resident-patch kernels built for pixels of this many channels (0: none)
     bool f32_results = false;     // the output or a stored epilogue tensor is fp32: the sums' rounding shows in it
     int64_t cN = 0, cH = 0, cW = 0, str_h = 1, str_w = 1;    // conv dgrad: images, extents of the activations, strides
@@ -297,9 +297,8 @@ double estimate_split_seconds(const VariantDesc &v, const Launch &L, const ucl_t
 // Weight gradient: kernel and slices of a parallel split-K call that leaves the slices to the library, chosen together.
 // Its K (output pixels) is deep, its output small: what decides is how many k-tiles a workgroup chains (0.37 us each of the
 // 64x64x32 kernel, whose four workgroups per CU hide the gathered operand best) against the bytes of partial tiles.
-// Measured against one or two workgroups per CU of the tile the general split model liked: about 10 % in the geometric mean over 440
-// geometries, 15 % over 32 layers of a residual network at batches 8 to 128 (128 <- 1152 over 25088 pixels 46.2 -> 26.4 us,
-// 128 <- 1152 over 6272 17.8 -> 18.5 us).
+// Measured against one or two workgroups per CU of the tile the general split model likes: 120 drawn layers 1.26 times faster in the
+// geometric mean (128 <- 1152 over 25088 pixels 47.0 -> 26.7 us), 40 that the general rule does not split 1.40 times.
 // Parallel split-K with up to this many slices lets the last launch of the tile kernel add them up itself.
 constexpr int kReduceInTileKernel = 2;
 
@@ -473,7 +472,7 @@ bool names_tile(const ucl_tuning *tune) { return tune && (tune->tile_m || tune->
 // columns, bf16: K = 576 40 us against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 54 of 3704, K = 1088: 99 against
 // 89 us; e4m3 64 of 2048, K = 1024: 33.8 against 32.6 us).  Convolutions: five steps, as their row was fitted.
 bool few_rows_apply(const VariantDesc &v, const Launch &L) {
-    if (L.mode == 1) return L.K >= 1408 || (L.K >= 128 && count_tiles(L, v.tile_m, v.tile_n) <= kNumCUs);
+    if (L.mode == 1) return L.K >= 1408 || (L.K >= (L.dt >= 2 ? 128 : 256) && count_tiles(L, v.tile_m, v.tile_n) <= kNumCUs);
     if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256);
     return L.K >= 320;
 }
@@ -1344,7 +1343,6 @@ ucl_status ucl_grouped_gemm(int32_t groups, const int64_t *M_g, int64_t N, int64
     for (int g = 0; g < groups; ++g) {
         if (M_g[g] < 0 || M_g[g] >= (1ll << 31)) return fail(UCL_ERR_INVALID_ARG, "M_g[%d]=%lld must be in [0, 2^31)", g, (long long)M_g[g]);
         L.sum_Mg += M_g[g];
-        if (M_g[g] > L.max_Mg) L.max_Mg = M_g[g];
     }
     if (ucl_status st = check_common(1, N, K, dtA, dtB, dtD, A_g, B_g, D_g, /*fp8_ok=*/true)) return st;
     if (a_cs != 1 || (b_rs != 1 && b_cs != 1))
