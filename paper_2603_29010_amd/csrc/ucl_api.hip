@@ -113,6 +113,8 @@ struct Launch {
     int patch_c = 0;              // conv: the problem fits the resident-patch kernels built for pixels of this many channels (0: none)
     bool f32_results = false;     // the output or a stored epilogue tensor is fp32: the sums' rounding shows in it
     int64_t cN = 0, cH = 0, cW = 0, str_h = 1, str_w = 1;    // conv dgrad: images, extents of the activations, strides
+    int taps_stride = 0;          // conv wgrad: stride of a problem that wgrad_taps_kernel serves (0: it does not)
+    int64_t cP = 0, cQ = 0, cC = 0;
     bool ndirect_ok = false;      // B contiguous along N and small enough for 32-bit byte offsets: direct-copy kernels apply
     bool mdirect_ok = false;      // the same for A contiguous along M
 };
@@ -126,6 +128,17 @@ int conv_patch_channels(int64_t W, int64_t channels, int64_t R, int64_t S, int64
     const bool ok = (channels == 64 || channels == 128) && R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == 1 &&
                     str_w == 1 && dil_h == 1 && dil_w == 1 && W + 1 <= 59;
     return ok ? (int)channels : 0;
+}
+
+// Filter gradients that wgrad_taps_kernel serves: 3x3 filters at pad 1, unit dilation and a stride of 1 or 2 whose rows are narrow enough for
+// the ring of its x pixels (four k-tiles, of which the taps may reach over one).  (Up to 32 filters, half of a workgroup's, the choice and the
+// workspace of the tile kernel stay.)
+void taps_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t C, int64_t P, int64_t Q, int64_t R, int64_t S, int64_t pad_h, int64_t pad_w,
+                 int64_t str_h, int64_t str_w, int64_t dil_h, int64_t dil_w) {
+    L.cN = N; L.cH = H; L.cW = W; L.cP = P; L.cQ = Q; L.cC = C;
+    const bool ok = R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == str_w && (str_h == 1 || str_h == 2) && dil_h == 1 && dil_w == 1 &&
+                    Q <= 62 && L.M > 32 && L.dt < variants_wgrad_taps().n && N * (P + 1) * (Q + 1) < (1ll << 30) && N * P * Q * L.M * 2 < (1ll << 30) && N * H * W * C * 2 < (1ll << 30);
+    L.taps_stride = ok ? (int)str_h : 0;
 }
 
 // Per-problem selection: of the variants built for this (mode, input type, operand layouts) the one with the smallest
@@ -436,6 +449,50 @@ int64_t split_bytes(const Launch &L, const SplitChoice &c) {
     return UCL_WORKSPACE_COUNTER_BYTES + (int64_t)c.slices * count_tiles(L, c.v->tile_m, c.v->tile_n) * c.v->tile_m * c.v->tile_n * 4;
 }
 
+// Filter gradients whose slices are left to the library: wgrad_taps_kernel and its slices (0: the kernel and slices chosen above).
+// The constants of its launch time were fitted to 32000 launches (8000 geometries of 1 to 64 images, 3 to 62 pixels a side, 8 to 512 channels
+// and filters, up to ten choices of slices each; 5 % off in the mean near the best choice): microseconds of a launch, of a round of
+// workgroups and of a k-tile in it, of the second launch, TB/s of partial sums, what a slice and a MB of the gradient add.
+struct TapsRow {
+    double fixed, round, ktile, second, partial_tbs, slice, out;
+};
+constexpr TapsRow kTapsRows[2] = {{3.78, 2.48, 0.679, 2.88, 2.97, 0.025, 0.244}, {3.75, 2.56, 0.534, 2.86, 3.16, 0.023, 0.180}};
+struct TapsChoice {
+    int slices = 0, px_per_slice = 0;
+};
+TapsChoice choose_taps(const Launch &L, const VariantDesc &v, const SplitChoice &other) {
+    TapsChoice best;
+    const TapsRow &r = kTapsRows[L.taps_stride - 1];
+    const int64_t kt = L.taps_stride == 1 ? 128 : 64, nk = (L.cN * (L.cP + 1) * (L.cQ + 1) + kt - 1) / kt;
+    const int64_t tiles = ((L.M + 63) / 64) * ((L.cC + 31) / 32);
+    const double out_mb = (double)L.M * L.N * 4e-6;
+    // What the tile kernel is expected to take.  Both models are off by some 5 %: a tie stays with it.
+    double best_t = 0.94e6 * estimate_wgrad_seconds(v, all_costs()[&v - all_variants().data()], L, other.slices, other.slices > 1 ? other.k_per_slice : L.K);
+    // An accumulator's roundings: one per MFMA (32 pixels) of its chain and one per slice; their squares weigh about alike in the error of the sum.
+    // fp32 results take no choice with more of them than the tile kernel's.
+    const int64_t roundings = (other.slices > 1 ? other.k_per_slice : L.K) / 32 + other.slices;
+    // no split, and what gives 1/4 to all of the CUs a workgroup, or two
+    const int fills[] = {1, 64, 96, 128, 160, 192, 224, 256, 384, 512};
+    for (int fill : fills) {
+        int64_t want = fill / tiles;
+        if (want > nk) want = nk;
+        if (want < 1) want = 1;
+        const int64_t per = (nk + want - 1) / want, slices = (nk + per - 1) / per;
+        if (L.f32_results && per * kt / 64 + slices > roundings) continue;
+        const int64_t rounds = (tiles * slices + kNumCUs - 1) / kNumCUs;
+        const double t = r.fixed + (double)rounds * (r.round + r.ktile * (double)per) + out_mb * r.out +
+                         (slices > 1 ? r.second + (double)slices * (out_mb / r.partial_tbs + r.slice) : 0.0);
+        if (t < best_t) {
+            best_t = t;
+            best.slices = (int)slices;
+            best.px_per_slice = (int)(per * kt);
+        }
+    }
+    return best;
+}
+bool takes_taps(const Launch &L, const ucl_tuning *tune) { return L.taps_stride > 0 && split_left_open(L, tune) && !names_tile(tune); }
+int64_t taps_bytes(const Launch &L, const TapsChoice &c) { return c.slices > 1 ? UCL_WORKSPACE_COUNTER_BYTES + (int64_t)c.slices * L.M * L.N * 4 : 0; }
+
 // Kernels that the general rule chooses among.  Split-K has kernels without K groups only.  And the slices an open call gets are what
 // fills the chip with the chosen tile, so a larger tile makes longer slices, and their fp32 sums round more: fp16 calls stay with the
 // tiles whose slices their results have always had (with all that bf16 has, fp16 -> fp32 512 x 512 x 8192 has 4 slices
@@ -733,6 +790,8 @@ __device__ inline V sum_slices(const V *src, int64_t stride, int slices) {
     int s = 0;
     sum_slices<16>(src, stride, slices, s, acc);
     sum_slices<8>(src, stride, slices, s, acc);
+    sum_slices<4>(src, stride, slices, s, acc);      // (left to single loads, 31 slices cost 2 us more than 24)
+    sum_slices<2>(src, stride, slices, s, acc);
     sum_slices<1>(src, stride, slices, s, acc);
     return acc;
 }
@@ -853,6 +912,23 @@ __global__ __launch_bounds__(256) void splitk_reduce_store_kernel(const ReduceSt
     }
 }
 
+// Adds up the slices of wgrad_taps_kernel, slice 0 first, and stores the gradient (the same order of elements).
+template <class V>
+__global__ __launch_bounds__(256) void wgrad_taps_reduce_kernel(const float *partials, void *dw, int64_t n, int slices, int32_t dtD, float alpha) {
+    constexpr int kPer = sizeof(V) / 4;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n / kPer) return;
+    const V acc = sum_slices((const V *)partials + i, n / kPer, slices);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        float x;
+        if constexpr (kPer == 4) x = acc[e]; else x = acc;
+        x *= alpha;
+        if (dtD == UCL_F32) ((float *)dw)[i * kPer + e] = x;
+        else ((uint16_t *)dw)[i * kPer + e] = (uint16_t)f32_to_bits16(x, dtD);
+    }
+}
+
 // split-K plan of a launch: slices (1 = none), K extent per slice, workspace bytes.
 struct SplitPlan {
     int slices = 1;
@@ -929,6 +1005,24 @@ ucl_status plan_split(const Launch &L, const VariantDesc &v, const ucl_tuning *t
         return fail(UCL_ERR_UNSUPPORTED, "split-K serves at most %d output tiles (this problem has %lld)", UCL_SPLIT_K_MAX_TILES, (long long)total_tiles);
     if (total_tiles * sp.slices >= (1ll << 31)) return fail(UCL_ERR_UNSUPPORTED, "tiles x slices exceeds the grid limit");
     sp.bytes = UCL_WORKSPACE_COUNTER_BYTES + (int64_t)sp.slices * total_tiles * v.tile_m * v.tile_n * 4;
+    return UCL_OK;
+}
+
+ucl_status run_taps(const Launch &L, KParams &kp, const TapsChoice &c, void *workspace, void *stream) {
+    kp.split_k = c.slices;
+    kp.k_per_slice = c.px_per_slice;
+    kp.ws_partials = c.slices > 1 ? (float *)((char *)workspace + UCL_WORKSPACE_COUNTER_BYTES) : nullptr;
+    hipError_t e = variants_wgrad_taps().v[L.dt].launch(kp, nullptr, (int)((L.M + 63) / 64 * ((L.cC + 31) / 32) * c.slices), (hipStream_t)stream);
+    if (e == hipSuccess && c.slices > 1) {
+        const int64_t n = L.M * L.N, n4 = n / 4;
+        const float alpha = kp.fused.has_scale ? kp.fused.alpha : 1.f;
+        if (n4 < kReduceScalarBelow)
+            hipLaunchKernelGGL(wgrad_taps_reduce_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, kp.ws_partials, kp.D, n, c.slices, kp.dtD, alpha);
+        else
+            hipLaunchKernelGGL(wgrad_taps_reduce_kernel<f32x4>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, (hipStream_t)stream, kp.ws_partials, kp.D, n, c.slices, kp.dtD, alpha);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) return fail(UCL_ERR_LAUNCH, "kernel launch failed: %s", hipGetErrorString(e));
     return UCL_OK;
 }
 
@@ -1018,6 +1112,11 @@ ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool
     if (v->lb == 0 && !panel_fits(v->tile_n, kp.ldb, L.K))
         return fail(UCL_ERR_UNSUPPORTED, "B leading stride %lld too large: a %d-row panel must span less than 2 GiB", (long long)kp.ldb, v->tile_n);
     kp.total_tiles = (int32_t)total;
+    if (L.mode == 4 && takes_taps(L, tune) && kp.fused.enabled && !kp.fused.has_bias && !kp.fused.has_res && !kp.fused.act && aligned16(kp.D)) {
+        const TapsChoice taps = choose_taps(L, *v, choice);
+        if (taps.slices == 1 || (taps.slices > 1 && tune->workspace && aligned16(tune->workspace) && taps_bytes(L, taps) <= tune->workspace_bytes))
+            return run_taps(L, kp, taps, tune->workspace, stream);
+    }
     if (total == 0) return UCL_OK;     // grouped with every M_g == 0: nothing to do
     const GroupTable *gtp = L.mode == 1 ? &gt : nullptr;
     hipError_t e;
@@ -1274,6 +1373,9 @@ ucl_status launch_from_problem(const ucl_problem *p, Launch &L) {
     L.f32_results = L.dtD == UCL_F32;
     for (int i = 0; p->epi && i < p->epi->n_steps; ++i)
         L.f32_results = L.f32_results || (p->epi->steps[i].op == UCL_EPI_AUX_STORE && p->epi->steps[i].dtype == UCL_F32);
+    if (L.mode == 4)
+        taps_launch(L, p->cN, p->cH, p->cW, p->cC, conv_out(p->cH, p->pad_h, p->dil_h, p->cR, p->stride_h), conv_out(p->cW, p->pad_w, p->dil_w, p->cS, p->stride_w),
+                    p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
     if (L.mode == 2)
         L.patch_c = conv_patch_channels(p->cW, p->cC, p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
     if (L.mode == 3) {
@@ -1504,6 +1606,7 @@ ucl_status ucl_conv2d_wgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     kp.pad_h = (int32_t)pad_h; kp.pad_w = (int32_t)pad_w; kp.str_h = (int32_t)stride_h; kp.str_w = (int32_t)stride_w;
     kp.dil_h = (int32_t)dil_h; kp.dil_w = (int32_t)dil_w;
     kp.d_vec = aligned16(dw) && (Ng % (16 / elem_size(dtDw)) == 0);
+    taps_launch(L, N, H, W, C, P, Q, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
     return run(L, kp, tune, stream);
 }
 
@@ -1582,6 +1685,12 @@ ucl_status ucl_workspace_size(const ucl_problem *p, const ucl_tuning *tune, int6
         // call to the general rule: what this answers serves that too)
         const int64_t general = split_bytes(L, general_split(L, tune));
         if (general > *bytes) *bytes = general;
+        const bool plain = !p->epi || p->epi->n_steps == 0 || (p->epi->n_steps == 1 && p->epi->steps[0].op == UCL_EPI_SCALE);
+        if (L.mode == 4 && takes_taps(L, tune) && plain) {
+            const TapsChoice taps = choose_taps(L, *v, choice);
+            if (taps.slices > 0 && slices_out) *slices_out = taps.slices;
+            if (taps_bytes(L, taps) > *bytes) *bytes = taps_bytes(L, taps);
+        }
     }
     return UCL_OK;
 }

@@ -59,4 +59,8 @@ VariantList variants_kgroups_mn();
 VariantList variants_kgroups_conv();
 VariantList variants_kgroups_conv_grad();
 
+// conv2d_wgrad with all taps of a pixel in one workgroup, by input type (not among the variants that a tile names; split_k and k_per_slice of
+// its arguments are slices and padded pixels per slice)
+VariantList variants_wgrad_taps();
+
 }  // namespace ucl
