@@ -507,6 +507,28 @@ constexpr int bshare(int mi, int mblocks, int n) {
     return (mi < h ? mi : h) * n / h;
 }
 
+// find_group by a whole wave, `mine` = tile_start[lane]: lane i looks at groups i, i + 64, ...  One trip to the argument segment,
+// which does not wait for anything else the kernel reads there, instead of the binary search's one per halving.
+__device__ __forceinline__ int find_group_wave(const GroupTable &gt, int mine, int groups, int t, int lane) {
+    int below = __builtin_popcountll(__ballot(mine <= t));            // (entries from `groups` on hold the number of tiles, > t)
+    for (int g = 64; g < groups; g += 64) below += __builtin_popcountll(__ballot(gt.tile_start[g + lane] <= t));
+    return __builtin_amdgcn_readfirstlane(below) - 1;
+}
+
+// Asks for every argument that a kernel reads before its first copy in one trip: left alone the compiler loads each where it is
+// used, and the prologue waits for up to eight trips one after the other.  With the search by a whole wave: 64 experts of 0 .. 32 rows, 2048
+// columns, K = 1024, e4m3 33.6 -> 32.1 us, 8 groups of 128 .. 2048 rows, 1024 columns, K = 1024 34.3 -> 33.7 us; large groups as before.  (In
+// the convolution kernels, which sit at their scalar registers, it made the patch kernel 1.5 % slower: grouped and few-row kernels only.)
+template <int MODE, class P>
+__device__ __forceinline__ void touch_arguments(const P &p) {
+    if constexpr (MODE == 1)
+        asm volatile("" ::"s"(p.total_tiles), "s"(p.tiles_n), "s"(p.raster), "s"(p.lda), "s"(p.ldb), "s"(p.N), "s"(p.K), "s"(p.fused.enabled), "s"(p.fused.has_bias),
+                     "s"(p.fused.bias), "s"(p.groups), "s"(p.A_g), "s"(p.B_g), "s"(p.D_g));
+    else
+        asm volatile("" ::"s"(p.total_tiles), "s"(p.tiles_n), "s"(p.raster), "s"(p.lda), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.fused.enabled), "s"(p.fused.has_bias),
+                     "s"(p.fused.bias), "s"(p.A), "s"(p.B), "s"(p.a_bs), "s"(p.b_bs), "s"(p.tiles_per_batch), "s"(p.split_k), "s"(p.k_per_slice));
+}
+
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(const KParams p_arg, const typename Cfg::Groups gt) {
     constexpr int TM = Cfg::TM, TN = Cfg::TN, TK = Cfg::TK, STAGES = Cfg::STAGES;
@@ -565,6 +587,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
+    int first_tile = 0;
+    if constexpr (MODE == 1) first_tile = gt.tile_start[lane];
+    if constexpr (MODE == 1 && !Cfg::PERSIST) touch_arguments<MODE>(p);
     // split-K (gemm / batched / wgrad): the (slice, tile) pairs are numbered slice by slice and that numbering is
     // dealt to the XCDs in runs, like tiles are: the tiles of one K slice, which read the same rows of A and B,
     // run side by side on one XCD and share them in its L2
@@ -598,7 +623,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
     DgradClass dg{0, 0, 1, 1, 1, 0};                             // gathered data gradient: residue class and its taps
     DgradTaps dg_h{0, 1, 1, 0, 0}, dg_w{0, 1, 1, 0, 0};
     if constexpr (MODE == 1) {
-        group = find_group(gt.tile_start, p.groups, t);
+        group = find_group_wave(gt, first_tile, p.groups, t, lane);
+        const void *a_g = p.A_g[group], *b_g = p.B_g[group], *d_g = p.D_g[group];
         t -= gt.tile_start[group];
         Mloc = gt.m[group];
         band_raster(t, (Mloc + TM - 1) / TM, p.tiles_n, p.raster, tm, tn);
@@ -606,9 +632,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void ucl_tile_kernel(
         // (persistent kernels: the table is read again after the previous tile's stores) they arrive in vector
         // registers, and a buffer resource built on such a pointer makes every global -> LDS copy a readfirstlane
         // loop.  They are the same in every lane: say so.
-        Ab = uniform_ptr((const char *)p.A_g[group]);
-        Bb = uniform_ptr((const char *)p.B_g[group]);
-        Db = (char *)uniform_ptr((const char *)p.D_g[group]);
+        Ab = uniform_ptr((const char *)a_g);
+        Bb = uniform_ptr((const char *)b_g);
+        Db = (char *)uniform_ptr((const char *)d_g);
     } else if constexpr (MODE == 3 && LA == kIm2col) {
         dg = dgrad_class(t, p.M / (p.cP * p.cQ), p.cP, p.cQ, p.str_h, p.str_w, TM, p.tiles_n);
         Mloc = p.M / (p.cP * p.cQ) * dg.Hc * dg.Wc;

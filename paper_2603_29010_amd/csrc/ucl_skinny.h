@@ -63,18 +63,22 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
     (void)p_arg;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int first_tile = 0;
+    if constexpr (MODE == 1) first_tile = gt.tile_start[lane];
+    touch_arguments<MODE>(p);
     int t = xcd_remap(blockIdx.x, p.total_tiles);
     int batch = 0, group = -1, tm, tn, Mloc = p.M;
     const char *Ab = (const char *)p.A, *Bb = (const char *)p.B;
     char *Db = (char *)p.D;
     if constexpr (MODE == 1) {
-        group = find_group(gt.tile_start, p.groups, t);
+        group = find_group_wave(gt, first_tile, p.groups, t, lane);
+        const void *a_g = p.A_g[group], *b_g = p.B_g[group], *d_g = p.D_g[group];
         t -= gt.tile_start[group];
         Mloc = gt.m[group];
         band_raster(t, (Mloc + TM - 1) / TM, p.tiles_n, p.raster, tm, tn);
-        Ab = uniform_ptr((const char *)p.A_g[group]);
-        Bb = uniform_ptr((const char *)p.B_g[group]);
-        Db = (char *)uniform_ptr((const char *)p.D_g[group]);
+        Ab = uniform_ptr((const char *)a_g);
+        Bb = uniform_ptr((const char *)b_g);
+        Db = (char *)uniform_ptr((const char *)d_g);
     } else {
         batch = t / p.tiles_per_batch;
         t -= batch * p.tiles_per_batch;
