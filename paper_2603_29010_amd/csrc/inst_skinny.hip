@@ -23,6 +23,8 @@ static const VariantDesc kTable[] = {
     describe_skinny<SkinnyCfg<2, 2, 4, 2, 1, 1>>(),
     describe_skinny<SkinnyCfg<2, 2, 4, 2, 2, 1>>(),
     describe_skinny<SkinnyCfg<2, 2, 4, 2, 3, 1>>(),
+    describe_skinny<SkinnyCfg<4, 4, 8, 1, 0, 0>>(),
+    describe_skinny<SkinnyCfg<4, 4, 8, 1, 1, 0>>(),
     describe_skinny<SkinnyCfg<1, 2, 4, 4, 0, 2>>(),
     describe_skinny<SkinnyCfg<1, 2, 4, 4, 1, 2>>(),
 };

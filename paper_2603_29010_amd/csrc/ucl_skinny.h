@@ -1,4 +1,4 @@
-// Kernel for problems of few rows (decoding: 1 .. 64 tokens against a weight matrix): gemm / batched_gemm /
+// Kernel for problems of few rows (decoding: 1 .. 64 tokens against a weight matrix) or few tiles: gemm / batched_gemm /
 // grouped_gemm with both operands contiguous along K.
 //
 // Such a call is a read of B.  The tile kernel walks B through LDS in 64-column tiles: 64 workgroups for 4096 columns,
@@ -10,6 +10,11 @@
 // Bound by what a CU copies: 100 to 110 GB/s of the 112 to 130 that copies of whole lines reach from L2 (16 KB in flight are
 // enough for that: the tile kernels' 64 GB/s are their barriers').  Loading the fragments straight into registers was tried
 // first: sixteen consecutive lanes then read sixteen different rows, and a CU takes in 38 GB/s whatever is in flight.
+// What the chain reads (bias, residual) is requested at the start: at the end it cost another trip to memory (0.3 us of 5).
+// 64x64 tiles have eight waves and one stage buffer each: a step's fragments go to registers, the buffer is refilled while they are
+// multiplied.  No barrier in the loop and half the LDS reads of 32x32 wave tiles; ahead of the tile kernel with two K groups where rows
+// are not whole 128-byte lines, which it feels more: 1000x1001x1992 fp16 16.0 -> 14.3 us (K = 1984: 13.2 -> 12.9 us).  64x64 tiles of four waves
+// with two stages, or with steps of 128, were slower (16.0 and 15.0 us).
 // Measured, 64x64x64x4 tiles with two K groups -> here: 16x4096x4096 bf16 14.5 -> 8.5 us (18.2 before the K groups; the
 // weight's trip from memory is 6.8), 2x792x7744 21.5 -> 8.4 us, 185x584x6960 34.5 -> 12.3 us, 305x336x1984 10.0 -> 6.2 us.
 #pragma once
@@ -29,7 +34,9 @@ struct SkinnyCfg {
     static constexpr int LDS_BYTES = W * S * STAGE_BYTES > MEET_BYTES ? W * S * STAGE_BYTES : MEET_BYTES;
     static constexpr int PER_CU = kLdsBytesPerCU / LDS_BYTES * W / 4 > 4 ? 4 : kLdsBytesPerCU / LDS_BYTES * W / 4;   // waves per SIMD
     static_assert(W == 4 || W == 8, "one or two waves per SIMD");
-    static_assert(LDS_BYTES <= kLdsBytesPerCU && S >= 2, "stage buffers exceed LDS");
+    static_assert(LDS_BYTES <= kLdsBytesPerCU, "stage buffers exceed LDS");
+    static_assert(S > 1 || MODE != 2, "gathered copies step through the taps and are issued for every step");
+    static constexpr int UNITS = TM * TN / 8, UPT = (UNITS + THREADS - 1) / THREADS;      // 8-column pieces of the output, per thread
     using Groups = typename std::conditional<MODE == 1, GroupTable, NoGroupTable>::type;
 };
 
@@ -88,23 +95,37 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
     }
     const int m0 = tm * TM, n0 = tn * TN, K = p.K;
 
+    const int a_rows = Mloc - m0 < TM ? Mloc - m0 : TM, b_rows = p.N - n0 < TN ? p.N - n0 : TN;
+    // ---- the chain's operands, requested first: at the end they would cost another trip to memory --------------------
+    const __attribute__((address_space(4))) FusedEpi &f = p.fused;
+    constexpr int UPT = Cfg::UPT;
+    Raw8 bias_raw[UPT], res_raw[UPT];
+    static_for<UPT>([&](auto q) {
+        const int u = q * Cfg::THREADS + tid, row = u / (TN / 8), n = n0 + (u % (TN / 8)) * 8;
+        const int nvalid = row < a_rows ? p.N - n : 0;
+        if (f.enabled && f.has_bias) bias_raw[q] = load8(group >= 0 ? ((const void *const *)f.bias)[group] : f.bias, f.bias_dt & 0xff, n, nvalid);
+        if (f.enabled && f.has_res)
+            res_raw[q] = load8(group >= 0 ? ((const void *const *)f.res)[group] : f.res, f.res_dt & 0xff,
+                               (int64_t)batch * f.res_bs + (int64_t)(m0 + row) * f.res_ld + n, nvalid);
+    });
+
     // ---- copies: a wave instruction fills eight rows of 128 bytes, chunks XORed by row as in the tile kernel ----------
     // Buffer resources over the rows that exist: rows past the edge and (by an out-of-range offset) k past the end
     // land as zeros and cost no traffic.
     const int f_row = lane & 15, f_kg = lane >> 4;
-    const int a_rows = Mloc - m0 < TM ? Mloc - m0 : TM, b_rows = p.N - n0 < TN ? p.N - n0 : TN;
     const rsrc_t a_rsrc = MODE == 2 ? buffer_rsrc(Ab, (uint32_t)p.a_bytes)
                                     : buffer_rsrc(Ab + (int64_t)m0 * p.lda * 2, (uint32_t)(((int64_t)(a_rows - 1) * p.lda + K) * 2));
     const rsrc_t b_rsrc = buffer_rsrc(Bb + (int64_t)n0 * p.ldb * 2, (uint32_t)(((int64_t)(b_rows - 1) * p.ldb + K) * 2));
+    constexpr int CA = TM / 8, CB = TN / 8;                       // copies per step
     const int c_row = lane >> 3;
     // (swz(row + 8) = swz(row) ^ 1: two chunk positions serve all of a wave's copies)
     const int kc[2] = {((lane & 7) ^ lds_swz<8>(c_row)) * 8, ((lane & 7) ^ lds_swz<8>(c_row + 8)) * 8};
-    uint32_t a_off[2 * MI], b_off[2 * NI];
+    uint32_t a_off[CA], b_off[CB];
     // conv: the row's output pixel as its first tap's input pixel, and the (tap, channel) each chunk position stands at
-    int a_h0[MODE == 2 ? 2 * MI : 1], a_w0[MODE == 2 ? 2 * MI : 1], t_c[2], t_r[2], t_s[2];
+    int a_h0[MODE == 2 ? CA : 1], a_w0[MODE == 2 ? CA : 1], t_c[2], t_r[2], t_s[2];
     if constexpr (MODE == 2) {
 #pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {
+        for (int i = 0; i < CA; ++i) {
             const bool there = i * 8 + c_row < a_rows;
             const int row = m0 + (there ? i * 8 + c_row : 0);
             const int pq = row / p.cQ, q = row - pq * p.cQ, nb = pq / p.cP, pp = pq - nb * p.cP;
@@ -121,17 +142,17 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) a_off[i] = i * 8 + c_row < a_rows ? (uint32_t)(((int64_t)(i * 8 + c_row) * p.lda + kc[i & 1]) * 2) : kOobOffset;
+        for (int i = 0; i < CA; ++i) a_off[i] = i * 8 + c_row < a_rows ? (uint32_t)(((int64_t)(i * 8 + c_row) * p.lda + kc[i & 1]) * 2) : kOobOffset;
     }
 #pragma unroll
-    for (int i = 0; i < 2 * NI; ++i) b_off[i] = i * 8 + c_row < b_rows ? (uint32_t)(((int64_t)(i * 8 + c_row) * p.ldb + kc[i & 1]) * 2) : kOobOffset;
+    for (int i = 0; i < CB; ++i) b_off[i] = i * 8 + c_row < b_rows ? (uint32_t)(((int64_t)(i * 8 + c_row) * p.ldb + kc[i & 1]) * 2) : kOobOffset;
     char *const mine = smem + wave * (S * Cfg::STAGE_BYTES);
-    constexpr int COPIES = 2 * (MI + NI);
+    constexpr int COPIES = CA + CB;
     auto copy = [&](int step, auto stage_) __attribute__((always_inline)) {
         char *dst = mine + decltype(stage_)::value * Cfg::STAGE_BYTES;
         const int k = step * Cfg::STEP;
         const bool ok[2] = {k + kc[0] < K, k + kc[1] < K};
-        static_for<2 * NI>([&](auto i) {
+        static_for<CB>([&](auto i) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, UCL_LDS_PTR(dst + i * 1024), 16, ok[i & 1] ? b_off[i] : kOobOffset, k * 2, 0, 0);
         });
         if constexpr (MODE == 2) {
@@ -144,7 +165,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
                 dw[h] = t_s[h] * p.dil_w;
                 tap_off[h] = (uint32_t)(((dh[h] * p.cW + dw[h]) * p.cC + t_c[h]) * 2);
             }
-            static_for<2 * MI>([&](auto i) {
+            static_for<CA>([&](auto i) {
                 const int h = a_h0[i] + dh[i & 1], w = a_w0[i] + dw[i & 1];
                 const bool in = ok[i & 1] && (unsigned)h < (unsigned)p.cH && (unsigned)w < (unsigned)p.cW;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, UCL_LDS_PTR(dst + TN * 128 + i * 1024), 16, in ? a_off[i] + tap_off[i & 1] : kOobOffset, 0, 0, 0);
@@ -158,7 +179,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
                 }
             }
         } else {
-            static_for<2 * MI>([&](auto i) {
+            static_for<CA>([&](auto i) {
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, UCL_LDS_PTR(dst + TN * 128 + i * 1024), 16, ok[i & 1] ? a_off[i] : kOobOffset, k * 2, 0, 0);
             });
         }
@@ -167,14 +188,16 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
     static_for<MI>([&](auto i) { static_for<NI>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }); });
     // (B as the first operand: a lane then holds 4 consecutive columns of one row)
     const int f_x = lds_swz<8>(f_row);
-    auto multiply = [&](auto stage_) __attribute__((always_inline)) {
+    u32x4_t fa[2][MI], fb[2][NI];
+    auto fetch = [&](auto stage_) __attribute__((always_inline)) {
         const char *src = mine + decltype(stage_)::value * Cfg::STAGE_BYTES + f_row * 128;
-        u32x4_t fa[2][MI], fb[2][NI];
         static_for<2>([&](auto h) {
             const int x = ((h * 4 + f_kg) ^ f_x) << 4;
             static_for<NI>([&](auto j) { fb[h][j] = *(const u32x4_t *)(src + j * 2048 + x); });
             static_for<MI>([&](auto i) { fa[h][i] = *(const u32x4_t *)(src + TN * 128 + i * 2048 + x); });
         });
+    };
+    auto multiply = [&]() __attribute__((always_inline)) {
         static_for<2>([&](auto h) {
             static_for<MI>([&](auto i) { static_for<NI>([&](auto j) { acc[i][j] = mfma_step<Cfg::DT>(fb[h][j], fa[h][i], acc[i][j]); }); });
         });
@@ -182,17 +205,35 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
     // Wave w takes steps w, w + W, ...; S - 1 of them are in flight while one is multiplied.  The copies are
     // unconditional (past the end of K they read nothing), so what is waited for is always the oldest step alone.
     const int steps = (K + Cfg::STEP - 1) / Cfg::STEP;
-    static_for<S - 1>([&](auto d) { copy(wave + d * W, d); });
-    for (int c = wave; c < steps;) {
-        static_for<S>([&](auto d) {
-            copy(c + (S - 1) * W, std::integral_constant<int, (decltype(d)::value + S - 1) % S>{});
+    if constexpr (S == 1) {
+        // one stage buffer: all of a step's fragments go to registers, then its buffer is refilled while they are multiplied
+        copy(wave, std::integral_constant<int, 0>{});
+        for (int c = wave; c < steps; c += W) {
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * COPIES));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             asm volatile("" ::: "memory");
-            multiply(d);
-            __builtin_amdgcn_sched_barrier(0);     // (its buffer is refilled next: every read of it has returned by then)
-            c += W;
-        });
+            fetch(std::integral_constant<int, 0>{});
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt((0xF) | (0x3 << 14) | (0x7 << 4) | (0x0 << 8));   // lgkmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
+            if (c + W < steps) copy(c + W, std::integral_constant<int, 0>{});
+            multiply();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        static_for<S - 1>([&](auto d) { copy(wave + d * W, d); });
+        for (int c = wave; c < steps;) {
+            static_for<S>([&](auto d) {
+                copy(c + (S - 1) * W, std::integral_constant<int, (decltype(d)::value + S - 1) % S>{});
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * COPIES));
+                asm volatile("" ::: "memory");
+                fetch(d);
+                multiply();
+                __builtin_amdgcn_sched_barrier(0);     // (its buffer is refilled next: every read of it has returned by then)
+                c += W;
+            });
+        }
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();                               // every wave is done with its stage buffers
@@ -205,10 +246,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
     __syncthreads();
     typedef const __attribute__((address_space(4))) EpiStepDev ConstStep;
     ConstStep *const ksteps = (ConstStep *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(KParams, steps));
-    const __attribute__((address_space(4))) FusedEpi &f = p.fused;
-    constexpr int UNITS = TM * TN / 8;
-#pragma clang loop unroll(disable)
-    for (int u = tid; u < UNITS; u += Cfg::THREADS) {
+    static_for<UPT>([&](auto q) {
+        const int u = q * Cfg::THREADS + tid;
         const int row = u / (TN / 8), col = (u % (TN / 8)) * 8;
         EpiCtx cx;
         cx.m = m0 + row;
@@ -216,7 +255,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
         cx.nvalid = row < a_rows ? p.N - cx.n : 0;
         cx.batch = batch;
         cx.group = group;
-        if (cx.nvalid <= 0) continue;
+        if (u >= Cfg::UNITS || cx.nvalid <= 0) return;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = 0.f;
@@ -233,16 +272,12 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
             float b8[8], r8[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) b8[e] = 0.f;
-            if (f.has_bias) {
-                const void *bp = group >= 0 ? ((const void *const *)f.bias)[group] : f.bias;
-                decode8(load8(bp, f.bias_dt & 0xff, cx.n, cx.nvalid), f.bias_dt & 0xff, b8);
-            }
+            if (f.has_bias) decode8(bias_raw[q], f.bias_dt & 0xff, b8);
             const float alpha = f.has_scale ? f.alpha : 1.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = v[e] * alpha + b8[e];
             if (f.has_res) {
-                const void *rp = group >= 0 ? ((const void *const *)f.res)[group] : f.res;
-                decode8(load8(rp, f.res_dt & 0xff, (int64_t)batch * f.res_bs + cx.m * f.res_ld + cx.n, cx.nvalid), f.res_dt & 0xff, r8);
+                decode8(res_raw[q], f.res_dt & 0xff, r8);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] += f.beta * r8[e];
             }
@@ -277,7 +312,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::PER_CU) void ucl_skinny_kernel(c
             }
         }
         store8(Db, p.dtD, (MODE == 1 ? 0 : (int64_t)batch * p.d_bs) + cx.m * p.ldd + cx.n, v, cx.nvalid);
-    }
+    });
 }
 
 template <class Cfg>
