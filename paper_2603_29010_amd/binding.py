@@ -4,7 +4,13 @@ Device buffers are passed as integer addresses (``tensor.data_ptr()``); nothing 
 their contents.  A nonzero status raises UclError carrying ucl_last_error().
 """
 import ctypes as C
+import functools
 import os
+
+try:
+    from . import _calls
+except ImportError:
+    _calls = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libucl.so")
@@ -137,6 +143,8 @@ def _load():
         lib.ucl_last_error.restype = C.c_char_p
         lib.ucl_version.restype = C.c_char_p
         _lib = lib
+        for name, entry in _calls_made.items():
+            entry.bind(C.cast(getattr(lib, name), vp).value)
     return _lib
 
 
@@ -201,18 +209,35 @@ def _opt(x):
     return x.ref() if x is not None else None
 
 
+# Launching entry points are callables of the extension module _calls (csrc/py_calls.c), which convert the usual arguments and call the
+# C function themselves; everything else goes through the Python functions below, as all of it does where the module was not built.
+_calls_made = {}
+
+
+def _native(kind):
+    def make(python):
+        if _calls is None:
+            return python
+        entry = _calls_made[python.__name__] = functools.update_wrapper(_calls.Call(kind, python, DTYPES, Epilogue, Tuning, _check), python)
+        return entry
+    return make
+
+
+@_native("gemm")
 def ucl_gemm(M, N, K, A, dtA, a_rs, a_cs, B, dtB, b_rs, b_cs, D, dtD, d_rs, d_cs, epi=None, tune=None,
              stream=0):
     _check(_load().ucl_gemm(M, N, K, A, _dt(dtA), a_rs, a_cs, B, _dt(dtB), b_rs, b_cs, D, _dt(dtD), d_rs, d_cs,
                             _opt(epi), _opt(tune), stream or None))
 
 
+@_native("gemm")
 def ucl_gemm_static_workspace(M, N, K, A, dtA, a_rs, a_cs, B, dtB, b_rs, b_cs, D, dtD, d_rs, d_cs, epi=None, tune=None,
                               stream=0):
     _check(_load().ucl_gemm_static_workspace(M, N, K, A, _dt(dtA), a_rs, a_cs, B, _dt(dtB), b_rs, b_cs, D, _dt(dtD),
                                              d_rs, d_cs, _opt(epi), _opt(tune), stream or None))
 
 
+@_native("batched")
 def ucl_batched_gemm(batch, M, N, K, A, dtA, a_rs, a_cs, a_bs, B, dtB, b_rs, b_cs, b_bs, D, dtD, d_rs, d_cs,
                      d_bs, epi=None, tune=None, stream=0):
     _check(_load().ucl_batched_gemm(batch, M, N, K, A, _dt(dtA), a_rs, a_cs, a_bs, B, _dt(dtB), b_rs, b_cs, b_bs,
@@ -228,24 +253,28 @@ def ucl_grouped_gemm(M_g, N, K, A_g, dtA, a_rs, a_cs, B_g, dtB, b_rs, b_cs, D_g,
                                     _dt(dtD), d_rs, d_cs, _opt(epi), _opt(tune), stream or None))
 
 
+@_native("conv")
 def ucl_conv2d_fprop(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w, x, dtX, w, dtW,
                      y, dtY, epi=None, tune=None, stream=0):
     _check(_load().ucl_conv2d_fprop(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w,
                                     x, _dt(dtX), w, _dt(dtW), y, _dt(dtY), _opt(epi), _opt(tune), stream or None))
 
 
+@_native("conv")
 def ucl_conv2d_dgrad(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w, dy, dtDy, w, dtW,
                      dx, dtDx, epi=None, tune=None, stream=0):
     _check(_load().ucl_conv2d_dgrad(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w,
                                     dy, _dt(dtDy), w, _dt(dtW), dx, _dt(dtDx), _opt(epi), _opt(tune), stream or None))
 
 
+@_native("conv")
 def ucl_conv2d_wgrad(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w, dy, dtDy, x, dtX,
                      dw, dtDw, epi=None, tune=None, stream=0):
     _check(_load().ucl_conv2d_wgrad(N, H, W, Cin, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w,
                                     dy, _dt(dtDy), x, _dt(dtX), dw, _dt(dtDw), _opt(epi), _opt(tune), stream or None))
 
 
+@_native("transpose")
 def ucl_transpose(batch, rows, cols, src, dt_src, dst, dt_dst, stream=0):
     _check(_load().ucl_transpose(batch, rows, cols, src, _dt(dt_src), dst, _dt(dt_dst), stream or None))
 

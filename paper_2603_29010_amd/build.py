@@ -9,11 +9,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libucl.so")
+CALLS = os.path.join(HERE, "_calls.so")          # extension module: the launching entry points as Python calls them
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -105,8 +107,15 @@ def early_use_of_transpose_reads(lines):
     return None
 
 
+def _build_calls(force):
+    src, deps = os.path.join(CSRC, "py_calls.c"), [os.path.join(CSRC, "py_calls.c"), os.path.join(HERE, "..", "include", "ucl.h")]
+    if force or not os.path.exists(CALLS) or os.path.getmtime(CALLS) < max(os.path.getmtime(d) for d in deps):
+        subprocess.check_call(["gcc", "-O2", "-Wall", "-Wextra", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], src, "-o", CALLS])
+
+
 def build(force=False, jobs=None, verbose=False):
     os.makedirs(OBJ, exist_ok=True)
+    _build_calls(force)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     jobs = jobs or min(8, os.cpu_count() or 1)
     objs = []
