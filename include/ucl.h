@@ -416,7 +416,7 @@ typedef struct ucl_variant_info {
 int32_t ucl_num_variants(void);
 ucl_status ucl_variant(int32_t i, ucl_variant_info *out);
 int32_t ucl_variant_k_groups(int32_t i);   /* K groups variant i is built with (1: none; 0: no such variant) */
-/* ucl_variant() goes on behind ucl_num_variants() with the few-row kernels (stages 1, tiles of 16 to 64 rows, every wavefront a K
+/* ucl_variant() goes on behind ucl_num_variants() with the few-row kernels (stages 1; grouped also 4: one for each wavefront; tiles of 16 to 64 rows, every wavefront a K
  * group of its own), until it reports an invalid index.  The library chooses among them as among the others; they
  * can be named, but serve no split-K. */
 

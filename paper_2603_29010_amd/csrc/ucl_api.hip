@@ -66,6 +66,23 @@ const std::vector<CostRow> &all_costs() {
     return c;
 }
 
+// The rows of the few-row kernels for more tiles than CUs, in the same order (resident 0: none).
+const std::vector<CostRow> &many_tiles_costs() {
+    static const std::vector<CostRow> c = [] {
+        std::vector<CostRow> out;
+        for (const VariantDesc &v : all_variants()) {
+            CostRow row = {};
+            for (const CostRow &r : kManyTilesRows)
+                if (r.mode == v.mode && r.la == v.la && r.lb == v.lb && r.eight_bit == (v.dt >= 2) && r.tile_m == v.tile_m && r.tile_n == v.tile_n &&
+                    v.stages == 1 && r.k_groups == v.k_groups)
+                    row = r;
+            out.push_back(row);
+        }
+        return out;
+    }();
+    return c;
+}
+
 // Where the variants of one operation and input type stand in all_variants(): every call walks these 4 to 49 instead of all.
 const std::vector<int> &variants_of(int mode, int dt) {
     static const std::vector<std::vector<int>> lists = [] {
@@ -213,6 +230,13 @@ double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L)
 }
 
 constexpr int kNumCUs = 256;
+
+const CostRow &cost_row(int i, const Launch &L) {
+    const VariantDesc &v = all_variants()[i];
+    const CostRow &many = many_tiles_costs()[i];
+    // (as far as those rows were fitted: a 32x64 kernel priced by them takes 1564 x 752 x 4752 in 45.2 us, the tile kernels 40.6 us)
+    return many.resident > 0 && L.batch == 1 && L.M <= 300 && takes_one_buffer(count_tiles(L, v.tile_m, v.tile_n), L.K) ? many : all_costs()[i];
+}
 
 // Slices a split-K launch of `total_tiles` tiles gets: as asked for, or (0) enough to give every CU a workgroup
 // while each keeps at least 4 x 64 of K; slices are whole multiples of 64 along K.
@@ -437,7 +461,7 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     if (L.mode == 0) {
         const VariantDesc *v = select_variant(L, nullptr);
         if (!best.v || (v && (L.K <= 8192 || count_tiles(L, v->tile_m, v->tile_n) >= 64) &&
-                        estimate_seconds(*v, all_costs()[v - all_variants().data()], L) < (L.K <= 8192 ? 0.9 : 0.8) * best_t)) {
+                        estimate_seconds(*v, cost_row((int)(v - all_variants().data()), L), L) < (L.K <= 8192 ? 0.9 : 0.8) * best_t)) {
             best.v = v;
             best.slices = 1;
         }
@@ -525,18 +549,23 @@ bool names_tile(const ucl_tuning *tune) { return tune && (tune->tile_m || tune->
 // ahead of the tile kernels wherever the cost rows choose them, none behind.  16-bit inputs at K up to 256, where that is 4 to 20 %, stay
 // with the tile kernels that ucl_select_tuning has always reported for them.
 // Grouped: with a tile for each CU at most they are ahead from K = 256 on (6 groups of 896 columns, e4m3, K = 960: 4.5 against 5.7 us; 7 of 832
-// columns bf16 4.8 against 6.1 us); with more tiles there are workgroups enough without them unless K is deep (49 experts of 2400
-// columns, bf16: K = 576 40 us against 36 us for the tile kernels; 38 of 2100, K = 1536: 45 us against 58 us; 54 of 3704, K = 1088: 99 against
-// 89 us; e4m3 64 of 2048, K = 1024: 33.8 against 32.6 us).  Convolutions: five steps, as their row was fitted.
+// columns bf16 4.8 against 6.1 us).  With more tiles, those with one buffer per wave from K = 512 on, the least that was fitted (64 experts of 0 ..
+// 32 rows, 2048 columns, K = 1024, e4m3 27 us, tile kernel 32 us; 128 of 4096 columns, K = 512 54 and 70 us; 49 of 30 rows, 2400 columns, K = 576 bf16
+// 32.4 and 37.5 us; below, 39 groups of 51 rows, 2312 columns, K = 256 bf16 21.8 and 17.2 us), and those with several where K is deep (38 of 2100
+// columns, K = 1536: 45 us against 58 us for the tile kernels).  Convolutions: five steps, as their row was fitted.
 bool few_rows_apply(const VariantDesc &v, const Launch &L) {
-    if (L.mode == 1) return L.K >= 1408 || (L.K >= (L.dt >= 2 ? 128 : 256) && count_tiles(L, v.tile_m, v.tile_n) <= kNumCUs);
-    if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256);
+    if (L.mode == 1) {
+        const bool many = count_tiles(L, v.tile_m, v.tile_n) > kOneBufferAbove;
+        if (v.stages != 1) return many && L.K >= (L.dt >= 2 ? 256 : 512);
+        return L.K >= 1408 || (!many && L.K >= (L.dt >= 2 ? 128 : 256));
+    }
+    // (64 rows: for half of them at least, which is what its row was fitted to; 26 x 12360 x 7680 bf16 46.0 us, 16x32 tiles 41.4 us)
+    if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256) && (v.tile_m < 64 || L.M > 32);
     return L.K >= 320;
 }
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
-    const auto &costs = all_costs();
     const VariantDesc *best = nullptr;
     double best_t = 0;
     bool best_fits = false;
@@ -558,7 +587,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
             if (!best || (direct && !(best->la == 5 || best->lb == 4))) best = &v;
             continue;
         }
-        if (v.stages == 1 && !few_rows_apply(v, L)) continue;
+        if (is_few_row(v) && !few_rows_apply(v, L)) continue;
         // A^T B of one row or column of up to 64 64x64 tiles: the fitted rows price the 128x128 kernel with K groups, whose copies bound
         // every problem it was fitted on, without its chain, and the 64x64 one without them below the one with (8 x 8 x 2048 fp32:
         // 15.4, 9.2 and 8.6 us; 8 x 24 x 7168 36.4, 23.2 and 19.3 us; 64 x 4096 x 2048 12.5 us without, 12.2 with).
@@ -568,7 +597,7 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         // K groups of the data gradient: with fewer than three k-tiles for each of the two there is nothing to share out (24 <- 32 at 3x3, 9 x 5 x 5:
         // 9.7 against 8.3 us, 24 <- 24 over 3 x 24 x 24 9.7 against 8.6 us).
         if (L.mode == 3 && v.k_groups > 1 && L.K < 320) continue;
-        const double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], L);
+        const double t = L.mode == 4 ? estimate_wgrad_seconds(v, all_costs()[i], L, 1, L.K) : estimate_seconds(v, cost_row(i, L), L);
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);
         if (!best || (fits && !best_fits) || (fits == best_fits && t < best_t)) { best_t = t; best = &v; best_fits = fits; }
@@ -1732,7 +1761,7 @@ ucl_status ucl_tile_map(int32_t groups, const int32_t *tiles_m, int32_t tiles_n,
 int32_t ucl_num_variants(void) {
     const auto &vs = all_variants();
     int32_t n = (int32_t)vs.size();
-    while (n > 0 && vs[n - 1].stages == 1) --n;
+    while (n > 0 && is_few_row(vs[n - 1])) --n;
     return n;
 }
 

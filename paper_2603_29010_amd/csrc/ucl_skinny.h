@@ -326,10 +326,35 @@ hipError_t launch_skinny(const KParams &p, const GroupTable *gt, int grid, hipSt
     return hipGetLastError();
 }
 
+// Two stage depths of one tile: with a workgroup per CU at most, what is in flight are the stages of its waves; with more, workgroups that
+// share a CU have as much in flight with one buffer each, and one's start and end hide under the others' copies.  (32 rows, 64 columns,
+// three stages -> one buffer: 64x16384x1024 bf16, 512 tiles 14.3 -> 10.3 us; 16x16: 16x4096x4096, 256 tiles 8.7 us with four stages, 10.5 us with one.
+// Over a deep K the stages stream better again: 26x12360x7680 bf16 42.4 and 46.2 us.)
+template <class Deep, class One>
+hipError_t launch_skinny_pair(const KParams &p, const GroupTable *gt, int grid, hipStream_t stream) {
+    return takes_one_buffer(grid, p.K) ? launch_skinny<One>(p, gt, grid, stream) : launch_skinny<Deep>(p, gt, grid, stream);
+}
+
 // (stages 1 tells these from the tile kernels of the same shape; k_groups = waves)
 template <class Cfg>
 constexpr VariantDesc describe_skinny() {
     return VariantDesc{Cfg::TM, Cfg::TN, 64, 1, Cfg::DT, Cfg::MODE, Cfg::MODE == 2 ? 2 : 0, 0, Cfg::LDS_BYTES, 0, kLdsBytesPerCU / Cfg::LDS_BYTES, Cfg::W, 0, &launch_skinny<Cfg>, nullptr};
+}
+
+template <int MI, int NI, int S, int DT, int MODE>
+constexpr VariantDesc describe_skinny_pair() {
+    VariantDesc v = describe_skinny<SkinnyCfg<MI, NI, 4, S, DT, MODE>>();
+    v.launch = &launch_skinny_pair<SkinnyCfg<MI, NI, 4, S, DT, MODE>, SkinnyCfg<MI, NI, 4, 1, DT, MODE>>;
+    return v;
+}
+
+// A kernel of one buffer per wave under a name of its own: the stages it has are those of its waves together.
+template <class Cfg>
+constexpr VariantDesc describe_one_buffer() {
+    static_assert(Cfg::S == 1, "one stage buffer per wave");
+    VariantDesc v = describe_skinny<Cfg>();
+    v.stages = Cfg::W;
+    return v;
 }
 
 }  // namespace ucl

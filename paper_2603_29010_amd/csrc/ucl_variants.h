@@ -20,6 +20,14 @@ struct VariantDesc {
     int (*resident)();          // workgroups one CU holds at a time (queried from the runtime)
 };
 
+// Few-row kernels of four waves: with more tiles than this, one per CU, those with one stage buffer per wave serve (gemm and batched calls: the
+// launch takes them, up to kOneBufferMaxK; grouped calls: variants of their own).
+constexpr int kOneBufferAbove = 256, kOneBufferMaxK = 4096;
+inline bool takes_one_buffer(int64_t tiles, int64_t K) { return tiles > kOneBufferAbove && K <= kOneBufferMaxK; }
+
+// (few-row kernels: stages 1, and 4 for those with one buffer for each of their waves)
+inline bool is_few_row(const VariantDesc &v) { return v.stages == 1 || v.tile_m < 64; }
+
 struct VariantList {
     const VariantDesc *v;
     int n;
