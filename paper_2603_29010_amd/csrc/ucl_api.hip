@@ -148,13 +148,14 @@ int conv_patch_channels(int64_t W, int64_t channels, int64_t R, int64_t S, int64
 }
 
 // Filter gradients that wgrad_taps_kernel serves: 3x3 filters at pad 1, unit dilation and a stride of 1 or 2 whose rows are narrow enough for
-// the ring of its x pixels (four k-tiles, of which the taps may reach over one).  (Up to 32 filters, half of a workgroup's, the choice and the
-// workspace of the tile kernel stay.)
+// the ring of its x pixels (four k-tiles, of which the taps may reach over one) and which have fewer than 2^20 rows: the kernel finds the row of a
+// slot's first pixel by an fp32 product, exact for twice as many (its relative error of 2^-22.5 over up to 2 (P + 1) + 64 rows has to stay below half a
+// row in P + 1; 4210560 rows come out one off).  (Up to 32 filters, half of a workgroup's, the choice and the workspace of the tile kernel stay.)
 void taps_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t C, int64_t P, int64_t Q, int64_t R, int64_t S, int64_t pad_h, int64_t pad_w,
                  int64_t str_h, int64_t str_w, int64_t dil_h, int64_t dil_w) {
     L.cN = N; L.cH = H; L.cW = W; L.cP = P; L.cQ = Q; L.cC = C;
     const bool ok = R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == str_w && (str_h == 1 || str_h == 2) && dil_h == 1 && dil_w == 1 &&
-                    Q <= 62 && L.M > 32 && L.dt < variants_wgrad_taps().n && N * (P + 1) * (Q + 1) < (1ll << 30) && N * P * Q * L.M * 2 < (1ll << 30) && N * H * W * C * 2 < (1ll << 30);
+                    Q <= 62 && P < (1 << 20) && L.M > 32 && L.dt < variants_wgrad_taps().n && N * (P + 1) * (Q + 1) < (1ll << 30) && N * P * Q * L.M * 2 < (1ll << 30) && N * H * W * C * 2 < (1ll << 30);
     L.taps_stride = ok ? (int)str_h : 0;
 }
 

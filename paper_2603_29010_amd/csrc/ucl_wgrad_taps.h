@@ -71,7 +71,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
     const rsrc_t x_rsrc = buffer_rsrc(a.x, a.x_bytes);
     const uint32_t ey = (uint32_t)a.Kout * 2, ex = (uint32_t)a.C * 2;
     const int kn = a.step_n, kp = a.step_p, kq = a.step_q;
-    // the slice's first pixel; a slot's pixel is at most a k-tile and a halo from it, near enough for divisions in fp32
+    // the slice's first pixel; a slot's pixel is at most a k-tile and a halo from it, near enough for divisions in fp32 (taps_launch bounds P and Q for that)
     const int n0 = s0 / img, p0 = (s0 - n0 * img) / Qp, q0 = s0 - n0 * img - p0 * Qp;
     const uint32_t dyq = ey, dyp = a.Q * ey, dyn = a.P * a.Q * ey;
     const uint32_t xq = ST * ex, xp = ST * a.W * ex, xn = a.H * a.W * ex;

@@ -50,6 +50,14 @@ def test_exact(g, dt):
     parity.check_exact(spec, tune, label=f"{g} {dt}, the workspace that the query names")
 
 
+def test_the_tallest_image():
+    # (its row indexes come out of fp32 products; |sums| stay far below 2^24)
+    spec = synth.conv_grad_spec("wgrad", dt_in="bf16", dt_out="f32", integer=True, **geom(1, (1 << 20) - 1, 1, 32, 40))
+    tune, ws = open_split()
+    assert any("wgrad_taps_kernel" in k for k in kernels_of(spec, tune))
+    parity.check_exact(spec, tune, label="tallest")
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 def test_other_outputs(dt):
     tune, ws = open_split()
