@@ -41,17 +41,30 @@ __device__ __forceinline__ void mfma16_v(f32x4_t &c, const u32x4_t &a, const u32
     else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
-template <int DT, int ST>
-__global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
-    constexpr int KT = ST == 1 ? 128 : 64, BLOCKS = 4, PLANES = ST * ST, STAGES = 4;
+template <int ST>
+struct TapsLds {
+    static constexpr int KT = ST == 1 ? 128 : 64, BLOCKS = 4, PLANES = ST * ST, STAGES = 4;
+    static constexpr int BLOCK_BYTES = KT * 64, PLANE_BYTES = (BLOCKS + 1) * BLOCK_BYTES, X_BYTES = PLANES * PLANE_BYTES, DY_BYTES = KT * 128;
+    static constexpr int LD = 292;                                // floats per filter where the sums meet (9 x 32, and padding against bank conflicts)
+    static constexpr int MEET_BYTES = 2 * 64 * LD * 4, END_BYTES = MEET_BYTES + 32;      // (and whether each wave has a NaN)
+    static constexpr int BYTES = X_BYTES + STAGES * DY_BYTES > END_BYTES ? X_BYTES + STAGES * DY_BYTES : END_BYTES;
+    static_assert(BYTES <= kLdsBytesPerCU, "LDS");
+};
+
+// Stores the workgroup's sums; true where they hold a NaN and PADDING_OUT is false.
+// Padded pixels have dy = 0, but their taps read real pixels of x, and an infinity or NaN there times 0 would be a NaN in the sums of taps that it
+// does not belong to.  Testing every fragment would cost VALU time beside the MFMAs.  But such a product always leaves a NaN: a workgroup that
+// finds one starts again (PADDING_OUT) and takes what padded pixels multiply out of the x fragments, one k-step after the other.  Finite inputs pay
+// 0.1 us at most for it (both gradients of 32 x 28 x 28 x 128, 32.7 us, 0.3 % apart); with a NaN in x the filter gradient takes 43 us instead of 23.
+template <int DT, int ST, bool PADDING_OUT>
+__device__ __forceinline__ bool wgrad_taps_pass(const WgradTaps &a, char *smem) {
+    constexpr int KT = TapsLds<ST>::KT, BLOCKS = TapsLds<ST>::BLOCKS, PLANES = TapsLds<ST>::PLANES;
     constexpr int DY_SLOTS = KT / 64, X_SLOTS = KT * PLANES / 128, COPIES = DY_SLOTS + X_SLOTS;
-    constexpr int BLOCK_BYTES = KT * 64, PLANE_BYTES = (BLOCKS + 1) * BLOCK_BYTES, X_BYTES = PLANES * PLANE_BYTES, DY_BYTES = KT * 128;
-    constexpr int LD = 292;                                       // floats per filter where the sums meet (9 x 32, and padding against bank conflicts)
-    constexpr int MEET_BYTES = 2 * 64 * LD * 4;
-    constexpr int LDS_BYTES = X_BYTES + STAGES * DY_BYTES > MEET_BYTES ? X_BYTES + STAGES * DY_BYTES : MEET_BYTES;
-    static_assert(LDS_BYTES <= kLdsBytesPerCU, "LDS");
-    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
-    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int BLOCK_BYTES = TapsLds<ST>::BLOCK_BYTES, PLANE_BYTES = TapsLds<ST>::PLANE_BYTES, X_BYTES = TapsLds<ST>::X_BYTES, DY_BYTES = TapsLds<ST>::DY_BYTES;
+    constexpr int LD = TapsLds<ST>::LD, MEET_BYTES = TapsLds<ST>::MEET_BYTES;
+    int tid = threadIdx.x;
+    if constexpr (PADDING_OUT) asm volatile("" : "+v"(tid));       // (nothing that follows from it stays in registers over the first pass)
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int tiles = a.tiles_k * a.tiles_c;
@@ -99,8 +112,8 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
         }
     });
     // slot i of stage kt (k-tile kt's dy, and block kt + 1 of x: the taps reach into it), then the slot steps on by one k-tile
-    auto copy = [&](auto i_, auto buf_, int kt) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_)::value, buf = decltype(buf_)::value;
+    auto copy = [&](auto i_, int buf, int kt) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_)::value;
         constexpr bool Y = i < DY_SLOTS;
         bool ok = (q[i] < a.Q) & (p[i] < a.P);
         if constexpr (!Y && ST == 2) ok = ok & (ST * p[i] + plane_h[i - DY_SLOTS] < a.H) & (ST * q[i] + plane_w[i - DY_SLOTS] < a.W);
@@ -111,11 +124,11 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, UCL_LDS_PTR(smem + X_BYTES + buf * DY_BYTES + (i * 8 + wave) * 1024), 16, at, 0, 0, 0);
         } else {
             const int idx = (i - DY_SLOTS) * 8 + wave, plane = ST == 1 ? 0 : idx >> 2, part = ST == 1 ? idx : idx & 3;
-            constexpr int block = (buf + 1) % BLOCKS;
+            const int block = (buf + 1) % BLOCKS;
             char *dst = smem + plane * PLANE_BYTES + block * BLOCK_BYTES + part * 1024;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, UCL_LDS_PTR(dst), 16, at, 0, 0, 0);
             // (block 0 stands behind block 3 once more, so that nobody's addresses wrap)
-            if constexpr (block == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, UCL_LDS_PTR(dst + BLOCKS * BLOCK_BYTES), 16, at, 0, 0, 0);
+            if (block == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, UCL_LDS_PTR(dst + BLOCKS * BLOCK_BYTES), 16, at, 0, 0, 0);
         }
         const uint32_t eq = Y ? dyq : xq, ep = Y ? dyp : xp, en = Y ? dyn : xn;
         q[i] += kq;
@@ -151,16 +164,16 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
     // waits for: a phase ends with all of them back.
     u32x4_t af[2][2], bf[2][9];
     const uint32_t a_addr[2] = {(uint32_t)a_addr0, (uint32_t)a_addr0 ^ 32u};
-    auto read = [&](auto set_, auto f_, auto buf_, auto ks_) __attribute__((always_inline)) {
+    auto read = [&](auto set_, auto f_, auto buf_, auto ks_, int block) __attribute__((always_inline)) {
         constexpr int set = decltype(set_)::value, f = decltype(f_)::value, buf = decltype(buf_)::value, ks = decltype(ks_)::value;
         u32x2_t lo, hi;
         if constexpr (f < 2) {
             constexpr int at = buf * DY_BYTES + ks * 32 * 128;
-            asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4" : "=&v"(lo), "=&v"(hi) : "v"(a_addr[f]), "n"(at), "n"(at + 512));
+            asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4" : "=&v"(lo), "=&v"(hi) : "v"(a_addr[f] + block * DY_BYTES), "n"(at), "n"(at + 512));
             af[set][f] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
         } else {
             constexpr int tap = f - 2, at = buf * BLOCK_BYTES + ks * 32 * 64;
-            asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%4\n\tds_read_b64_tr_b16 %1, %3 offset:%4" : "=&v"(lo), "=&v"(hi) : "v"(b_addr[tap][0]), "v"(b_addr[tap][1]), "n"(at));
+            asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%4\n\tds_read_b64_tr_b16 %1, %3 offset:%4" : "=&v"(lo), "=&v"(hi) : "v"(b_addr[tap][0] + block * BLOCK_BYTES), "v"(b_addr[tap][1] + block * BLOCK_BYTES), "n"(at));
             bf[set][tap] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
         }
     };
@@ -177,8 +190,8 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
         static_for<18>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
             mfma16_v<DT>(acc[i & 1][i >> 1], bf[set][i >> 1], af[set][i & 1]);
-            if constexpr (i < 11) read(std::integral_constant<int, 1 - set>{}, i_, buf_, ks_);
-            else if constexpr (fill >= 0 && i - 11 < COPIES) copy(std::integral_constant<int, i - 11>{}, fill_, kt_load);
+            if constexpr (i < 11) read(std::integral_constant<int, 1 - set>{}, i_, buf_, ks_, 0);
+            else if constexpr (fill >= 0 && i - 11 < COPIES) copy(std::integral_constant<int, i - 11>{}, fill, kt_load);
         });
         landed(std::integral_constant<int, 1 - set>{});
     };
@@ -188,11 +201,8 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
     constexpr auto copies_of = [](int b) { return COPIES + ((b + 1) % BLOCKS == 0 ? X_SLOTS : 0); };
 
     // x block 0 (as the last slots of a stage -1), then stages 0, 1, 2
-    static_for<X_SLOTS>([&](auto j) { copy(std::integral_constant<int, DY_SLOTS + decltype(j)::value>{}, std::integral_constant<int, BLOCKS - 1>{}, -1); });
+    static_for<X_SLOTS>([&](auto j) { copy(std::integral_constant<int, DY_SLOTS + decltype(j)::value>{}, BLOCKS - 1, -1); });
     static_for<3>([&](auto st) { static_for<COPIES>([&](auto i) { copy(i, st, decltype(st)::value); }); });
-    pipeline_barrier<copies_of(1) + copies_of(2)>();
-    static_for<11>([&](auto f) { read(I0{}, f, I0{}, I0{}); });
-    landed(I0{});
     // k-tile kt in buffer u, its first k-step's fragments in registers
     auto tile = [&](auto u_, int kt) __attribute__((always_inline)) {
         constexpr int u = decltype(u_)::value, nxt = (u + 1) % 4;
@@ -201,15 +211,49 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
         pipeline_barrier<copies_of((u + 2) % 4)>();
         phase(std::integral_constant<int, ST == 1 ? 1 : u & 1>{}, std::integral_constant<int, nxt>{}, I0{}, std::integral_constant<int, (u + 3) % 4>{}, kt + 3);
     };
-    for (int kt = 0;;) {
-        tile(I0{}, kt);
-        if (++kt >= KTn) break;
-        tile(I1{}, kt);
-        if (++kt >= KTn) break;
-        tile(std::integral_constant<int, 2>{}, kt);
-        if (++kt >= KTn) break;
-        tile(std::integral_constant<int, 3>{}, kt);
-        if (++kt >= KTn) break;
+    // k-tile kt with what padded pixels multiply taken out: pixels in rows of Qp, rows in images of Pp
+    auto careful = [&](int kt) __attribute__((always_inline)) {
+        pipeline_barrier<0>();
+        static_for<KT / 64>([&](auto ks) {
+            static_for<11>([&](auto f) { read(I0{}, f, I0{}, ks, kt % 4); });
+            landed(I0{});
+            const int first = s0 + kt * KT + kg * (KT / 2) + (int)ks * 32 + 8 * g, rows = first / Qp;        // the lane's eight pixels
+            int fq = first - rows * Qp, fp = rows % Pp;
+            uint32_t real = 0;
+#pragma clang loop unroll(disable)
+            for (int e = 0; e < 8; ++e) {
+                if (fq < a.Q && fp < a.P && first + e < a.px) real |= 1u << e;
+                const bool end = ++fq == Qp;
+                fq = end ? 0 : fq;
+                fp = end ? (fp + 1 == Pp ? 0 : fp + 1) : fp;
+            }
+            u32x4_t mask;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mask[j] = (real >> (2 * j) & 1) * 0xffffu | (real >> (2 * j + 1) & 1) * 0xffff0000u;
+            static_for<9>([&](auto tap) { bf[0][tap] &= mask; keep_alive(bf[0][tap]); });
+            asm volatile("s_nop 3");                              // (the MFMAs are asm too: nobody else counts the wait states behind the ANDs)
+            static_for<18>([&](auto i) { mfma16_v<DT>(acc[i & 1][i >> 1], bf[0][i >> 1], af[0][i & 1]); });
+        });
+        pipeline_barrier<0>();                                    // (stage kt + 3's block of x takes the place of k-tile kt's)
+        static_for<COPIES>([&](auto i) { copy(i, (kt + 3) % 4, kt + 3); });
+    };
+    if constexpr (!PADDING_OUT) {
+        pipeline_barrier<copies_of(1) + copies_of(2)>();
+        static_for<11>([&](auto f) { read(I0{}, f, I0{}, I0{}, 0); });
+        landed(I0{});
+        for (int kt = 0;;) {
+            tile(I0{}, kt);
+            if (++kt >= KTn) break;
+            tile(I1{}, kt);
+            if (++kt >= KTn) break;
+            tile(std::integral_constant<int, 2>{}, kt);
+            if (++kt >= KTn) break;
+            tile(std::integral_constant<int, 3>{}, kt);
+            if (++kt >= KTn) break;
+        }
+    } else {
+#pragma clang loop unroll(disable)
+        for (int kt = 0; kt < KTn; ++kt) careful(kt);
     }
     __builtin_amdgcn_s_waitcnt((0xF) | (0x3 << 14) | (0x7 << 4) | (0x0 << 8));
     asm volatile("s_nop 15");
@@ -225,10 +269,12 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
         });
     });
     __syncthreads();
+    float nan = 0.f;                                              // (one at the latest where a sum is)
     const int64_t row_elems = 9 * (int64_t)a.C;
     static_for<9>([&](auto i) {
         const int u = i * 512 + tid, ko = u / 72, rest = u - ko * 72, tap = rest >> 3, c = (rest & 7) * 4;
         const f32x4_t v = *(const f32x4_t *)(meet + ko * LD + tap * 32 + c) + *(const f32x4_t *)(meet + (64 + ko) * LD + tap * 32 + c);
+        if constexpr (!PADDING_OUT) nan = __builtin_fmaf(v[2], v[3], __builtin_fmaf(v[0], v[1], nan));
         if (k0 + ko < a.Kout && c0 + c < a.C) {
             const int64_t at = (int64_t)(k0 + ko) * row_elems + tap * a.C + c0 + c;
             if (a.slices > 1) {
@@ -243,6 +289,22 @@ __global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
             }
         }
     });
+    if constexpr (PADDING_OUT) return false;
+    // (beside the stores, which nobody waits for)
+    uint32_t *const nans = (uint32_t *)(smem + MEET_BYTES);
+    const bool any = __ballot(__builtin_isnan(nan)) != 0;
+    if (lane == 0) nans[wave] = any;
+    pipeline_barrier<63>();
+    const u32x4_t f = *(const u32x4_t *)nans | *(const u32x4_t *)(nans + 4);
+    return __builtin_amdgcn_readfirstlane(f[0] | f[1] | f[2] | f[3]) != 0;
+}
+
+template <int DT, int ST>
+__global__ __launch_bounds__(512, 2) void wgrad_taps_kernel(const WgradTaps a) {
+    __shared__ __attribute__((aligned(1024))) char smem[TapsLds<ST>::BYTES];
+    if (__builtin_expect(!wgrad_taps_pass<DT, ST, false>(a, smem), 1)) return;
+    __syncthreads();                                              // (the stores are out, and the next copies go where sums and flags were read)
+    wgrad_taps_pass<DT, ST, true>(a, smem);
 }
 
 template <int DT>
