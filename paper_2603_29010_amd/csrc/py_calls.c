@@ -16,7 +16,7 @@ enum { MAX_ARGS = 24 };
 
 typedef struct {
     PyObject_HEAD
-    PyObject *dict, *python;            /* python: the function it was made from */
+    PyObject *dict, *weak, *python;     /* python: the function it was made from */
     PyObject *dtypes, *epilogue, *tuning, *check;
     void *entry;                        /* address of the C function, NULL until the library is loaded */
     const char *kinds;                  /* one letter per argument: i integer, p pointer, d dtype, e epilogue, t tuning, s stream */
@@ -31,7 +31,7 @@ typedef union {
 
 static PyObject *name_c;
 
-/* 1: converted, 0: not for us, -1: Python error set */
+/* 1: converted, 0: not for us */
 static int convert(Call *self, char kind, PyObject *o, Arg *a, Py_buffer *view, int *held) {
     int overflow = 0;
     switch (kind) {
@@ -154,6 +154,7 @@ static int call_clear(Call *self) {
 }
 static void call_dealloc(Call *self) {
     PyObject_GC_UnTrack(self);
+    if (self->weak) PyObject_ClearWeakRefs((PyObject *)self);
     call_clear(self);
     Py_TYPE(self)->tp_free((PyObject *)self);
 }
@@ -165,7 +166,26 @@ static PyObject *call_bind(Call *self, PyObject *address) {
     Py_RETURN_NONE;
 }
 
-static PyMethodDef methods[] = {{"bind", (PyCFunction)call_bind, METH_O, "Sets the address of the C function."}, {NULL, NULL, 0, NULL}};
+/* It stands where a function stood: what one answers, it answers (pickled and copied as the name of its module that it is, bound as a method of a class that
+ * holds it, attributes that it has not those of the function it was made from). */
+static PyObject *call_reduce(Call *self, PyObject *none) {
+    (void)none;
+    return PyObject_GetAttrString(self->python, "__qualname__");
+}
+static PyObject *call_getattro(PyObject *self, PyObject *name) {
+    PyObject *v = PyObject_GenericGetAttr(self, name);
+    if (v || !PyErr_ExceptionMatches(PyExc_AttributeError) || !((Call *)self)->python) return v;
+    PyErr_Clear();
+    return PyObject_GetAttr(((Call *)self)->python, name);
+}
+static PyObject *call_get(PyObject *self, PyObject *of, PyObject *type) {
+    (void)type;
+    if (of && of != Py_None) return PyMethod_New(self, of);
+    Py_INCREF(self);
+    return self;
+}
+
+static PyMethodDef methods[] = {{"__reduce__", (PyCFunction)call_reduce, METH_NOARGS, "The name under which its module holds it."}, {"bind", (PyCFunction)call_bind, METH_O, "Sets the address of the C function."}, {NULL, NULL, 0, NULL}};
 static PyGetSetDef getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, NULL, NULL}, {NULL, NULL, NULL, NULL, NULL}};
 static PyTypeObject CallType = {
     PyVarObject_HEAD_INIT(NULL, 0).tp_name = "paper_2603_29010_amd._calls.Call",
@@ -176,6 +196,9 @@ static PyTypeObject CallType = {
     .tp_traverse = (traverseproc)call_traverse,
     .tp_clear = (inquiry)call_clear,
     .tp_call = PyVectorcall_Call,
+    .tp_getattro = call_getattro,
+    .tp_descr_get = call_get,
+    .tp_weaklistoffset = offsetof(Call, weak),
     .tp_vectorcall_offset = offsetof(Call, vectorcall),
     .tp_dictoffset = offsetof(Call, dict),
     .tp_methods = methods,

@@ -1,7 +1,10 @@
 """The launching entry points through the extension module: what they convert themselves and what they leave to the Python function
 gives the same answers (host only: every call here is refused before a launch)."""
+import copy
 import ctypes
 import inspect
+import pickle
+import weakref
 
 import pytest
 
@@ -56,6 +59,24 @@ def test_same_as_the_python_function(name):
         assert first is not None, args
     assert outcome(native, *bad, stream=0) == outcome(python, *bad, stream=0)
     assert outcome(native, *bad, nonsense=0) is TypeError
+
+
+@pytest.mark.parametrize("name", NAMES + ["ucl_grouped_gemm"])
+def test_programs_may_treat_them_as_the_functions_they_were(name):
+    f = getattr(ucl, name)
+    assert pickle.loads(pickle.dumps(f)) is f and pickle.loads(pickle.dumps({"call": f}, protocol=2))["call"] is f
+    assert copy.copy(f) is f and copy.deepcopy([f])[0] is f and weakref.ref(f)() is f
+    python = getattr(f, "__wrapped__", f)
+    assert f.__defaults__ == python.__defaults__ and f.__defaults__[-1] == 0
+    assert f.__code__ is python.__code__ and f.__kwdefaults__ is None and f.__qualname__ == name and f.__module__ == binding.__name__
+    assert not hasattr(f, "nothing_of_that_name")
+
+    class Holder:
+        call = f
+    assert Holder.call is f and Holder().call.__self__.__class__ is Holder
+    f.noted = 3
+    assert f.noted == 3
+    del f.noted
 
 
 def test_the_structures_are_passed_through():
