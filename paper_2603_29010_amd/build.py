@@ -10,14 +10,17 @@ import re
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libucl.so")
-CALLS = os.path.join(HERE, "_calls.so")          # extension module: the launching entry points as Python calls them
+# Extension module: the launching entry points as Python calls them (named for the interpreter it is built for: another one does not load it)
+CALLS = os.path.join(HERE, "_calls" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CC = os.environ.get("CC", "gcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-disable-promote-alloca-to-lds",
@@ -108,9 +111,21 @@ def early_use_of_transpose_reads(lines):
 
 
 def _build_calls(force):
+    """Without a compiler or Python.h the binding goes through ctypes alone: a warning, and no module of an earlier source is left behind."""
     src, deps = os.path.join(CSRC, "py_calls.c"), [os.path.join(CSRC, "py_calls.c"), os.path.join(HERE, "..", "include", "ucl.h")]
-    if force or not os.path.exists(CALLS) or os.path.getmtime(CALLS) < max(os.path.getmtime(d) for d in deps):
-        subprocess.check_call(["gcc", "-O2", "-Wall", "-Wextra", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], src, "-o", CALLS])
+    if not force and os.path.exists(CALLS) and os.path.getmtime(CALLS) >= max(os.path.getmtime(d) for d in deps):
+        return
+    for stale in (CALLS, os.path.join(os.path.dirname(CALLS), "_calls.so")):         # (the name that every interpreter loads)
+        if os.path.exists(stale):
+            os.remove(stale)
+    cmd = [CC, "-O2", "-Wall", "-Wextra", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], src, "-o", CALLS]
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        why = (r.stderr or f"exit status {r.returncode}") if r.returncode else ""
+    except OSError as e:
+        why = str(e)
+    if why:
+        warnings.warn(f"the extension module of the launching entry points was not built, calls go through ctypes: {why.strip()[:500]}")
 
 
 def build(force=False, jobs=None, verbose=False):

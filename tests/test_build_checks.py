@@ -1,4 +1,10 @@
-"""What the build refuses in the kernels' listings (host only)."""
+"""What the build refuses in the kernels' listings, and what it does without a C compiler (host only)."""
+import importlib.machinery
+import os
+
+import pytest
+
+from paper_2603_29010_amd import build
 from paper_2603_29010_amd.build import early_use_of_transpose_reads
 
 READ_A = ["ds_read_b64_tr_b16 v[10:11], v2", "ds_read_b64_tr_b16 v[12:13], v2 offset:1024"]
@@ -20,3 +26,20 @@ def test_a_wait_has_to_cover_the_transpose_read():
     assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0)"], MUL) is not None
     assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0) lgkmcnt(0)"], MUL) is None
     assert scan(READ_A, ["v_add_u32_e32 v12, 1, v4"], ["s_waitcnt lgkmcnt(0)"]) is not None        # overwritten in flight
+
+
+def test_the_extension_module_is_named_for_its_interpreter():
+    suffix = os.path.basename(build.CALLS)[len("_calls"):]
+    assert suffix == importlib.machinery.EXTENSION_SUFFIXES[0] and suffix != ".so"
+
+
+@pytest.mark.parametrize("cc", ["/nonexistent/cc", "false"])
+def test_without_a_compiler_the_build_goes_on(tmp_path, monkeypatch, cc):
+    module, untagged = tmp_path / "_calls.tag.so", tmp_path / "_calls.so"
+    module.write_bytes(b"of an earlier source")
+    untagged.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(build, "CALLS", str(module))
+    monkeypatch.setattr(build, "CC", cc)
+    with pytest.warns(UserWarning, match="ctypes"):
+        build._build_calls(True)
+    assert not module.exists() and not untagged.exists()
