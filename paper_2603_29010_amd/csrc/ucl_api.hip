@@ -560,8 +560,10 @@ bool few_rows_apply(const VariantDesc &v, const Launch &L) {
         if (v.stages != 1) return many && L.K >= (L.dt >= 2 ? 256 : 512);
         return L.K >= 1408 || (!many && L.K >= (L.dt >= 2 ? 128 : 256));
     }
-    // (64 rows: for half of them at least, which is what its row was fitted to; 26 x 12360 x 7680 bf16 46.0 us, 16x32 tiles 41.4 us)
-    if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256) && (v.tile_m < 64 || L.M > 32);
+    // (64 rows: for half of them at least, which is what its row was fitted to; 26 x 12360 x 7680 bf16 46.0 us, 16x32 tiles 41.4 us; and for half of
+    // the CUs: with fewer tiles each wave's one buffer keeps too little of B's way from memory in flight, 35 x 7304 x 8016 bf16 51.9 us, 32x64 tiles
+    // 40.3 us; over 3600 problems it is 1.04 to 1.7 times behind below 128 tiles, level from there on)
+    if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256) && (v.tile_m < 64 || (L.M > 32 && count_tiles(L, v.tile_m, v.tile_n) >= kNumCUs / 2));
     return L.K >= 320;
 }
 

@@ -1,0 +1,15 @@
+"""Which kernels and bands are chosen for problems around a tile per CU, as measured (host only): calls that a cost row or a line once sent to a slower kernel."""
+import pytest
+
+import paper_2603_29010_amd as ucl
+
+
+def chosen(M, N, K, dt, batch=0, out=None):
+    kw = dict(M=M, N=N, K=K, **({"batch": batch} if batch else {}))
+    return ucl.ucl_select_tuning("batched_gemm" if batch else "gemm", dt, out or ("bf16" if dt == "e4m3" else dt), **kw)
+
+
+@pytest.mark.parametrize("M,N,K,dt", [(35, 7304, 8016, "bf16"), (36, 8120, 5376, "f16"), (33, 7296, 7552, "bf16")])
+def test_64_rows_of_eight_waves_need_tiles_for_half_of_the_cus(M, N, K, dt):
+    # 52, 26 and 37 us on the 64x64 kernel of eight waves, 40, 20 and 28 us on the 32x64 one
+    assert chosen(M, N, K, dt)["tile_m"] == 32
