@@ -673,9 +673,14 @@ bool takes_gemm(const Launch &conv, const Launch &gemm, const ucl_tuning *tune) 
 }
 
 int default_raster(const VariantDesc &v, const Launch &L) {
-    // bands of ~1024 rows: an XCD's run of 32 consecutive tiles then covers a near-square block.  Tiles of 64 rows: bands of 512 for the same
-    // reason (1000 x 1000 x 512: 8.3 -> 7.1 us, 1000 x 1001 x 1992: 16.4 -> 16.0 us with bands of 8 instead of 16 tiles); a group's rows stay in one band.
-    if (v.tile_m == 64 && L.mode == 0) return 8;
+    // bands of ~1024 rows: an XCD's run of 32 consecutive tiles then covers a near-square block.  Tiles of 64 rows: even bands of up to ten tiles, for the
+    // same reason (2500 problems, against bands of 16: 11 to 16 rows of tiles 0.97 to 0.98 of the time, more 0.95 to 0.99; bands of eight tiles and
+    // a rest cost 1.02 to 1.03 where there are nine or ten rows of tiles, 610 x 2024 x 5408 fp16 42.7 instead of 33.3 us).  With k-tiles of 32 four
+    // workgroups share a CU, and bands of eight do as well as any from 17 rows of tiles on (0.99, even ones 1.01).  A group's rows stay in one band.
+    if (v.tile_m == 64 && L.mode == 0) {
+        const int64_t rows = (L.M + 63) / 64, bands = (rows + 9) / 10;
+        return v.tile_k == 32 && rows > 16 ? 8 : (int)((rows + bands - 1) / bands);
+    }
     int gm = 1024 / v.tile_m;
     return gm < 1 ? 1 : gm;
 }

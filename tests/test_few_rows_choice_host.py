@@ -13,3 +13,9 @@ def chosen(M, N, K, dt, batch=0, out=None):
 def test_64_rows_of_eight_waves_need_tiles_for_half_of_the_cus(M, N, K, dt):
     # 52, 26 and 37 us on the 64x64 kernel of eight waves, 40, 20 and 28 us on the 32x64 one
     assert chosen(M, N, K, dt)["tile_m"] == 32
+
+
+@pytest.mark.parametrize("M,N,K,dt,bands", [(610, 2024, 5408, "f16", 10), (591, 1776, 3104, "bf16", 10), (673, 1520, 4736, "bf16", 6), (863, 1248, 3088, "bf16", 7)])
+def test_bands_of_64_row_tiles_are_even(M, N, K, dt, bands):
+    t = chosen(M, N, K, dt)
+    assert t["tile_m"] == 64 and t["raster"] == bands
