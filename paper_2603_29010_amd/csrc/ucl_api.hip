@@ -66,7 +66,7 @@ const std::vector<CostRow> &all_costs() {
     return c;
 }
 
-// The rows of the few-row kernels for more tiles than CUs, in the same order (resident 0: none).
+// The rows of the few-row kernels for more tiles than CUs, in the same order (one_buffer() says which have one).
 const std::vector<CostRow> &many_tiles_costs() {
     static const std::vector<CostRow> c = [] {
         std::vector<CostRow> out;
@@ -206,11 +206,16 @@ double fourth_power_sum(double a, double b, double c = 0, double d = 0) {
     a *= a; b *= b; c *= c; d *= d;
     return sqrt(sqrt(a * a + b * b + c * c + d * d));
 }
+// Few-row kernels with one stage buffer per wave: gemm and batched launches take them under the named tile's tuple, with a cost row of its own
+// (kManyTilesRows).  Their workgroups are short and follow one another on a CU without rounds.
+bool one_buffer(const VariantDesc &v, const Launch &L) {
+    return L.mode == 0 && v.stages == 1 && v.k_groups == 4 && takes_one_buffer(count_tiles(L, v.tile_m, v.tile_n), L.K);
+}
 double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L) {
     const int64_t tiles_n = (L.N + v.tile_n - 1) / v.tile_n;
     const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
     const int64_t slots = 256 * (int64_t)r.resident, rounds = (tiles + slots - 1) / slots;
-    const double on_cu = tiles <= slots ? (double)((tiles + 255) / 256) : (double)(rounds * r.resident);
+    const double on_cu = tiles <= slots || one_buffer(v, L) ? (double)((tiles + 255) / 256) : (double)(rounds * r.resident);
     // (8-bit inputs: K counts pairs of elements, 2 bytes)
     double rows = (double)L.M, all_rows = (double)L.batch * L.M, panels = (double)L.batch;
     if (L.mode == 1) {
@@ -232,12 +237,7 @@ double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L)
 
 constexpr int kNumCUs = 256;
 
-const CostRow &cost_row(int i, const Launch &L) {
-    const VariantDesc &v = all_variants()[i];
-    const CostRow &many = many_tiles_costs()[i];
-    // (as far as those rows were fitted: a 32x64 kernel priced by them takes 1564 x 752 x 4752 in 45.2 us, the tile kernels 40.6 us)
-    return many.resident > 0 && L.batch == 1 && L.M <= 300 && takes_one_buffer(count_tiles(L, v.tile_m, v.tile_n), L.K) ? many : all_costs()[i];
-}
+const CostRow &cost_row(int i, const Launch &L) { return L.mode == 0 && one_buffer(all_variants()[i], L) ? many_tiles_costs()[i] : all_costs()[i]; }
 
 // Slices a split-K launch of `total_tiles` tiles gets: as asked for, or (0) enough to give every CU a workgroup
 // while each keeps at least 4 x 64 of K; slices are whole multiples of 64 along K.
@@ -600,7 +600,11 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         // K groups of the data gradient: with fewer than three k-tiles for each of the two there is nothing to share out (24 <- 32 at 3x3, 9 x 5 x 5:
         // 9.7 against 8.3 us, 24 <- 24 over 3 x 24 x 24 9.7 against 8.6 us).
         if (L.mode == 3 && v.k_groups > 1 && L.K < 320) continue;
-        const double t = L.mode == 4 ? estimate_wgrad_seconds(v, all_costs()[i], L, 1, L.K) : estimate_seconds(v, cost_row(i, L), L);
+        double t = L.mode == 4 ? estimate_wgrad_seconds(v, all_costs()[i], L, 1, L.K) : estimate_seconds(v, cost_row(i, L), L);
+        // Above 300 rows, and where K gives a wave a single step, the tile kernels are the few-row ones' rivals and both rows are 10 to 15 % off: what is no
+        // clear win stays with the tile kernel.  (Slower than the choice among tile kernels by more than 4 %: 6.4 -> 3.8 % of 2700 16-bit problems of
+        // 301 to 3000 rows, the timing's own share, and 7 -> 2 % of 3900 8-bit ones of K = 144 to 512, which are still 1.07 to 1.14x in the mean.)
+        if (L.mode == 0 && (L.K <= 256 || L.M > 300) && one_buffer(v, L)) t *= L.K <= 256 ? 1.3 : 1.2;
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);
         if (!best || (fits && !best_fits) || (fits == best_fits && t < best_t)) { best_t = t; best = &v; best_fits = fits; }
