@@ -207,8 +207,9 @@ double fourth_power_sum(double a, double b, double c = 0, double d = 0) {
     return sqrt(sqrt(a * a + b * b + c * c + d * d));
 }
 // Few-row kernels with one stage buffer per wave: gemm and batched launches take them under the named tile's tuple, with a cost row of its own
-// (kManyTilesRows).  Their workgroups are short and follow one another on a CU without rounds.
+// (kManyTilesRows); grouped ones are variants of their own.  Their workgroups are short and follow one another on a CU without rounds.
 bool one_buffer(const VariantDesc &v, const Launch &L) {
+    if (L.mode == 1) return is_few_row(v) && v.stages != 1;
     return L.mode == 0 && v.stages == 1 && v.k_groups == 4 && takes_one_buffer(count_tiles(L, v.tile_m, v.tile_n), L.K);
 }
 double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L) {
