@@ -208,15 +208,18 @@ double fourth_power_sum(double a, double b, double c = 0, double d = 0) {
 }
 // Few-row kernels with one stage buffer per wave: gemm and batched launches take them under the named tile's tuple, with a cost row of its own
 // (kManyTilesRows); grouped ones are variants of their own.  Their workgroups are short and follow one another on a CU without rounds.
-bool one_buffer(const VariantDesc &v, const Launch &L) {
+bool one_buffer(const VariantDesc &v, const Launch &L, int64_t tiles) {
     if (L.mode == 1) return is_few_row(v) && v.stages != 1;
-    return L.mode == 0 && v.stages == 1 && v.k_groups == 4 && takes_one_buffer(count_tiles(L, v.tile_m, v.tile_n), L.K);
+    return L.mode == 0 && v.stages == 1 && v.k_groups == 4 && takes_one_buffer(tiles, L.K);
 }
-double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L) {
+// (row, many: the variant's rows of all_costs() and many_tiles_costs(); *one: whether it runs with one stage buffer per wave)
+double estimate_seconds(const VariantDesc &v, const CostRow &row, const CostRow &many, const Launch &L, bool *one) {
     const int64_t tiles_n = (L.N + v.tile_n - 1) / v.tile_n;
     const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n);
+    *one = one_buffer(v, L, tiles);
+    const CostRow &r = L.mode == 0 && *one ? many : row;
     const int64_t slots = 256 * (int64_t)r.resident, rounds = (tiles + slots - 1) / slots;
-    const double on_cu = tiles <= slots || one_buffer(v, L) ? (double)((tiles + 255) / 256) : (double)(rounds * r.resident);
+    const double on_cu = tiles <= slots || *one ? (double)((tiles + 255) / 256) : (double)(rounds * r.resident);
     // (8-bit inputs: K counts pairs of elements, 2 bytes)
     double rows = (double)L.M, all_rows = (double)L.batch * L.M, panels = (double)L.batch;
     if (L.mode == 1) {
@@ -237,8 +240,6 @@ double estimate_seconds(const VariantDesc &v, const CostRow &r, const Launch &L)
 }
 
 constexpr int kNumCUs = 256;
-
-const CostRow &cost_row(int i, const Launch &L) { return L.mode == 0 && one_buffer(all_variants()[i], L) ? many_tiles_costs()[i] : all_costs()[i]; }
 
 // Slices a split-K launch of `total_tiles` tiles gets: as asked for, or (0) enough to give every CU a workgroup
 // while each keeps at least 4 x 64 of K; slices are whole multiples of 64 along K.
@@ -462,8 +463,9 @@ SplitChoice choose_split(const Launch &L, const ucl_tuning *tune) {
     // than always split, none slower.
     if (L.mode == 0) {
         const VariantDesc *v = select_variant(L, nullptr);
+        bool one = false;
         if (!best.v || (v && (L.K <= 8192 || count_tiles(L, v->tile_m, v->tile_n) >= 64) &&
-                        estimate_seconds(*v, cost_row((int)(v - all_variants().data()), L), L) < (L.K <= 8192 ? 0.9 : 0.8) * best_t)) {
+                        estimate_seconds(*v, all_costs()[v - all_variants().data()], many_tiles_costs()[v - all_variants().data()], L, &one) < (L.K <= 8192 ? 0.9 : 0.8) * best_t)) {
             best.v = v;
             best.slices = 1;
         }
@@ -476,8 +478,8 @@ int64_t split_bytes(const Launch &L, const SplitChoice &c) {
 }
 
 // Filter gradients whose slices are left to the library: wgrad_taps_kernel and its slices (0: the kernel and slices chosen above).
-// The constants of its launch time were fitted to 32000 launches (8000 geometries of 1 to 64 images, 3 to 62 pixels a side, 8 to 512 channels
-// and filters, up to ten choices of slices each; 5 % off in the mean near the best choice): microseconds of a launch, of a round of
+// The constants of its launch time were fitted to 16670 launches of 3992 of 17441 timed geometries (1 to 64 images, 3 to 62 pixels a side, 8 to 512
+// channels and filters, up to ten choices of slices each; 5 % off in the mean near the best choice): microseconds of a launch, of a round of
 // workgroups and of a k-tile in it, of the second launch, TB/s of partial sums, what a slice and a MB of the gradient add.
 struct TapsRow {
     double fixed, round, ktile, second, partial_tbs, slice, out;
@@ -495,7 +497,7 @@ TapsChoice choose_taps(const Launch &L, const VariantDesc &v, const SplitChoice 
     // What the tile kernel is expected to take.  Both models are off by some 5 %: a tie stays with it.
     double best_t = 0.94e6 * estimate_wgrad_seconds(v, all_costs()[&v - all_variants().data()], L, other.slices, other.slices > 1 ? other.k_per_slice : L.K);
     // An accumulator's roundings: one per MFMA (32 pixels) of its chain and one per slice; their squares weigh about alike in the error of the sum.
-    // fp32 results take no choice with more of them than the tile kernel's.
+    // fp32 results take no choice with more of them than the tile kernel's.  (16-bit ones may: their own rounding is hundreds of times a sum's error.)
     const int64_t roundings = (other.slices > 1 ? other.k_per_slice : L.K) / 32 + other.slices;
     // no split, and what gives 1/4 to all of the CUs a workgroup, or two
     const int fills[] = {1, 64, 96, 128, 160, 192, 224, 256, 384, 512};
@@ -570,6 +572,7 @@ bool few_rows_apply(const VariantDesc &v, const Launch &L) {
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
     const auto &vs = all_variants();
+    const auto &costs = all_costs(), &many = many_tiles_costs();
     const VariantDesc *best = nullptr;
     double best_t = 0;
     bool best_fits = false;
@@ -601,11 +604,12 @@ const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
         // K groups of the data gradient: with fewer than three k-tiles for each of the two there is nothing to share out (24 <- 32 at 3x3, 9 x 5 x 5:
         // 9.7 against 8.3 us, 24 <- 24 over 3 x 24 x 24 9.7 against 8.6 us).
         if (L.mode == 3 && v.k_groups > 1 && L.K < 320) continue;
-        double t = L.mode == 4 ? estimate_wgrad_seconds(v, all_costs()[i], L, 1, L.K) : estimate_seconds(v, cost_row(i, L), L);
+        bool one = false;
+        double t = L.mode == 4 ? estimate_wgrad_seconds(v, costs[i], L, 1, L.K) : estimate_seconds(v, costs[i], many[i], L, &one);
         // Above 300 rows, and where K gives a wave a single step, the tile kernels are the few-row ones' rivals and both rows are 10 to 15 % off: what is no
         // clear win stays with the tile kernel.  (Slower than the choice among tile kernels by more than 4 %: 6.4 -> 3.8 % of 2700 16-bit problems of
         // 301 to 3000 rows, the timing's own share, and 7 -> 2 % of 3900 8-bit ones of K = 144 to 512, which are still 1.07 to 1.14x in the mean.)
-        if (L.mode == 0 && (L.K <= 256 || L.M > 300) && one_buffer(v, L)) t *= L.K <= 256 ? 1.3 : 1.2;
+        if (L.mode == 0 && one && (L.K <= 256 || L.M > 300)) t *= L.K <= 256 ? 1.3 : 1.2;
         // (a large tile must not make a call fail that a smaller one serves)
         const bool fits = panels_fit(v, L);
         if (!best || (fits && !best_fits) || (fits == best_fits && t < best_t)) { best_t = t; best = &v; best_fits = fits; }
