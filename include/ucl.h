@@ -140,8 +140,13 @@ typedef enum ucl_conv_iterator {
  * all, on the caller's stream; two where the chain has the form act(alpha * acc + bias[n] +
  * beta * R[m,n]) -- any part may be missing, the empty chain included -- and the rows of D are
  * 16-byte aligned: the reduction kernel then runs the chain on the sums and stores D itself).
- * Both give bit-identical results.  With no tile named in the same
- * ucl_tuning, the tile is chosen for the split-K launch (not as for the unsplit problem). */
+ * With the same tile and slices both give bit-identical results.  With no tile named in the same
+ * ucl_tuning, the tile is chosen for the split-K launch (not as for the unsplit problem).
+ * conv2d_wgrad, PARALLEL, no tile and no slices named: 3x3 filters with pad 1, stride 1 or 2 (both
+ * ways), unit dilation, a chain of nothing or one SCALE and a 16-byte aligned dw may run on a kernel
+ * that no tile names (ucl_select_tuning() and ucl_variant() know the tile kernels only).  It cuts
+ * the output pixels into ranges of its own, so its fp32 sums round differently from SERIAL's or a
+ * named tile's: for fp32 results with no more roundings, for 16-bit ones possibly over longer ranges. */
 typedef enum ucl_split_k_mode { UCL_SPLIT_K_NONE = 0, UCL_SPLIT_K_SERIAL = 1, UCL_SPLIT_K_PARALLEL = 2 } ucl_split_k_mode;
 
 /* `.with_scheduler(tile=...)`.  DEFAULT: one workgroup per output tile, dealt out by the hardware as
@@ -375,7 +380,9 @@ ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out);
 
 /* Bytes of workspace a call on problem p with tuning `tune` needs (0 without a split):
  * UCL_WORKSPACE_COUNTER_BYTES + slices x tiles x tile_m x tile_n x 4.  *slices_out (may be NULL)
- * receives the number of K slices the call will use.  PARALLEL with split_k_slices 0 also covers what
+ * receives the number of K slices the call will use.  A filter gradient on the kernel that no tile
+ * names (see ucl_split_k_mode) needs UCL_WORKSPACE_COUNTER_BYTES + slices x Kout x 9 C x 4 (nothing with
+ * one slice), its slices are ranges of output pixels, and *bytes also covers the tile kernel.  PARALLEL with split_k_slices 0 also covers what
  * calls on p with other strides or chains may need; given less, or nothing, such a call splits as
  * far as that allows, by a simpler rule, and is rejected only where that rule needs more.  tune->workspace is
  * not looked at here.  With the STREAM_K scheduler:
@@ -416,9 +423,11 @@ typedef struct ucl_variant_info {
 int32_t ucl_num_variants(void);
 ucl_status ucl_variant(int32_t i, ucl_variant_info *out);
 int32_t ucl_variant_k_groups(int32_t i);   /* K groups variant i is built with (1: none; 0: no such variant) */
-/* ucl_variant() goes on behind ucl_num_variants() with the few-row kernels (stages 1; grouped also 4: one for each wavefront; tiles of 16 to 64 rows, every wavefront a K
- * group of its own), until it reports an invalid index.  The library chooses among them as among the others; they
- * can be named, but serve no split-K. */
+/* ucl_variant() goes on behind ucl_num_variants() with the few-row kernels (tiles of 16 to 64 rows, every wavefront a K
+ * group of its own; stages 1, grouped also 4: one buffer for each wavefront), until it reports an invalid index.  The
+ * library chooses among them as among the others; they can be named, but serve no split-K.  gemm / batched_gemm tiles of
+ * 16 or 32 rows are two kernels under one name: with more than 256 tiles and K up to 4096 (8-bit inputs 8192) a launch takes
+ * the one with a single stage buffer per wavefront, else the one whose lds_bytes ucl_variant() reports. */
 
 const char *ucl_status_string(ucl_status s);
 const char *ucl_last_error(void);   /* thread-local; valid until the next call on this thread */

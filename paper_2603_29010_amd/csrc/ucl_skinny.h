@@ -13,8 +13,9 @@
 // What the chain reads (bias, residual) is requested at the start: at the end it cost another trip to memory (0.3 us of 5).
 // 64x64 tiles have eight waves and one stage buffer each: a step's fragments go to registers, the buffer is refilled while they are
 // multiplied.  No barrier in the loop and half the LDS reads of 32x32 wave tiles; ahead of the tile kernel with two K groups where rows
-// are not whole 128-byte lines, which it feels more: 1000x1001x1992 fp16 16.0 -> 14.3 us (K = 1984: 13.2 -> 12.9 us).  64x64 tiles of four waves
-// with two stages, or with steps of 128, were slower (16.0 and 15.0 us).
+// are not whole 128-byte lines, which it feels more: 1000x1001x1992 fp16 16.0 -> 14.3 us by themselves (K = 1984: 13.2 -> 12.9 us), 13.0 us with the
+// chain's operands requested first and bands of 512 rows.  64x64 tiles of four waves with two stages, or with steps of 128, were slower (16.0
+// and 15.0 us).  Every wave has one step on its way: with tiles for fewer than half of the CUs that is too little from memory (few_rows_apply).
 // Measured, 64x64x64x4 tiles with two K groups -> here: 16x4096x4096 bf16 14.5 -> 8.5 us (18.2 before the K groups; the
 // weight's trip from memory is 6.8), 2x792x7744 21.5 -> 8.4 us, 185x584x6960 34.5 -> 12.3 us, 305x336x1984 10.0 -> 6.2 us.
 #pragma once
@@ -329,7 +330,9 @@ hipError_t launch_skinny(const KParams &p, const GroupTable *gt, int grid, hipSt
 // Two stage depths of one tile: with a workgroup per CU at most, what is in flight are the stages of its waves; with more, workgroups that
 // share a CU have as much in flight with one buffer each, and one's start and end hide under the others' copies.  (32 rows, 64 columns,
 // three stages -> one buffer: 64x16384x1024 bf16, 512 tiles 14.3 -> 10.3 us; 16x16: 16x4096x4096, 256 tiles 8.7 us with four stages, 10.5 us with one.
-// Over a deep K the stages stream better again: 26x12360x7680 bf16 42.4 and 46.2 us.)
+// 3000 problems of more tiles than CUs and K from 272 to 4096, decoding, batched or tall: 0.4 to 0.98 of the time with one buffer, least for short K and
+// many tiles; 16x16 tiles at K above 2048 the 0.98, so the line is drawn at 4096.  Beyond it, 3900 problems up to K = 16384: 16x16 tiles 0.96
+// to 1.09, the others 0.82 to 1.01; nothing prices them there.)
 template <class Deep, class One>
 hipError_t launch_skinny_pair(const KParams &p, const GroupTable *gt, int grid, hipStream_t stream) {
     return takes_one_buffer(grid, p.K) ? launch_skinny<One>(p, gt, grid, stream) : launch_skinny<Deep>(p, gt, grid, stream);

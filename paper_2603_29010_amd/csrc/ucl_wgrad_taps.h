@@ -11,9 +11,10 @@
 // The pixels pass through LDS in k-tiles of KT: dy in four stage buffers, x in a ring of four k-tiles (a k-tile's taps reach into its
 // neighbours).  Eight waves: two groups take half of each k-tile's pixels, in a group four waves hold 32 filters x 16 channels x
 // 9 taps each; the groups' sums meet in LDS.  Slices of the pixels go to different workgroups; their sums are added up by a second launch.
-// Bound by the MFMAs and, with VALU work for copies only, close to them: 0.67 us per 128 pixels (0.5 at full rate; 1.06 with ring addresses worked
-// out for every read and one set of fragments, 0.91 with two sets).  What is left is fixed: 6.9 us of launch, first copies and meeting, 3 us of second
-// launch, and the partial sums at 3 TB/s, which is why 64 x 32 and not more.  Gathering tile kernel -> here, both launches, fp32 gradient:
+// The loop is bound by the MFMAs and, with VALU work for copies only, close to them: 0.67 us per 128 pixels (0.5 at full rate; 1.06 with ring addresses worked
+// out for every read and one set of fragments, 0.91 with two sets).  But it is 5 of 17.8 us for 32 x 28 x 28 x 128 -> 128, whose MFMAs take 15 %
+// of the launch's clocks: the rest is 6.9 us of launch, first copies and meeting, and a second launch of some 3 us and the partial sums at 3 TB/s
+// (4.5 us here), which is why 64 x 32 and not more.  Gathering tile kernel -> here, both launches in a graph, fp32 gradient:
 // 32 x 28 x 28 x 128 -> 128 26.0 -> 17.8 us, 32 x 14 x 14 x 256 -> 256 31.4 -> 20.9 us, 32 x 7 x 7 x 512 -> 512 41.8 -> 19.4 us,
 // 32 x 56 x 56 x 64 -> 64 25.6 -> 20.5 us, 32 x 56 x 56 x 128 -> 128 at stride 2 25.5 -> 21.8 us.
 #pragma once
