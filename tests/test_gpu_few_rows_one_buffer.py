@@ -35,3 +35,22 @@ def test_grouped_choice(dt):
     assert (t["tile_m"], t["stages"], t["k_groups"]) == (32, 4, 4)
     parity.check_exact(spec, None, label=f"{dt} chosen")
     parity.check_exact(spec, Tuning(**t), label=f"{dt} named")
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16", "e4m3", "e5m2"])
+@pytest.mark.parametrize("batch,M,N,K", [(64, 16, 520, 336), (20, 25, 1000, 400), (9, 65, 700, 400)], ids=lambda v: str(v))
+def test_batches_and_more_rows_chosen(batch, M, N, K, dt):
+    # batches of more tiles than CUs, as the library chooses: exact, and a chain over them
+    unit = 2 if dt in ("e4m3", "e5m2") else 1
+    t = ucl.ucl_select_tuning("batched_gemm", dt, "f32", batch=batch, M=M, N=N, K=K * unit)
+    assert t["stages"] == 1 and t["k_groups"] == 4 and batch * -(-M // t["tile_m"]) * -(-N // t["tile_n"]) > 256
+    parity.check_exact(synth.batched_spec(batch, M, N, K * unit, dt_in=dt, dt_out="f32", epilogue=(), integer=True), None, label=f"{dt} chosen")
+    parity.check(synth.batched_spec(batch, M, N, K * unit, dt_in=dt, dt_out="f16" if dt == "f16" else "bf16", epilogue=("bias", "aux_load", "silu")), None, label=f"{dt} chain")
+
+
+@pytest.mark.parametrize("rows", [9, 10, 11, 17, 21])
+def test_even_bands(rows):
+    # rows of 64-row tiles in one, two and three bands, the last one shorter where they do not divide
+    spec = synth.gemm_spec(64 * rows - 7, 840, 1032, dt_in="bf16", dt_out="f32", epilogue=(), integer=True)
+    for tile in ((64, 64, 64, 4), (64, 64, 32, 4)):
+        parity.check_exact(spec, Tuning(*tile), label=f"{rows} rows of tiles {tile}")
