@@ -132,6 +132,8 @@ struct Launch {
     int64_t cN = 0, cH = 0, cW = 0, str_h = 1, str_w = 1;    // conv dgrad: images, extents of the activations, strides
     int taps_stride = 0;          // conv wgrad: stride of a problem that wgrad_taps_kernel serves (0: it does not)
     int64_t cP = 0, cQ = 0, cC = 0;
+    int held_stride = 0;          // conv fprop / dgrad: stride of a problem that conv_held_kernel serves (cN, cP, cQ, cC set; 0: it does not)
+    int64_t gathered = 0;         // ... and bytes of the pixels it gathers
     bool ndirect_ok = false;      // B contiguous along N and small enough for 32-bit byte offsets: direct-copy kernels apply
     bool mdirect_ok = false;      // the same for A contiguous along M
 };
@@ -157,6 +159,20 @@ void taps_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     const bool ok = R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == str_w && (str_h == 1 || str_h == 2) && dil_h == 1 && dil_w == 1 &&
                     Q <= 62 && P < (1 << 20) && L.M > 32 && L.dt < variants_wgrad_taps().n && N * (P + 1) * (Q + 1) < (1ll << 30) && N * P * Q * L.M * 2 < (1ll << 30) && N * H * W * C * 2 < (1ll << 30);
     L.taps_stride = ok ? (int)str_h : 0;
+}
+
+// Convolutions that conv_held_kernel serves: 3x3 with pad 1 at unit stride and dilation, as a forward pass up to the channels of one pass (further ones gain
+// nothing there: 0.7 of the tile kernels' speed), as a data gradient any.  n images of P x Q output pixels, C channels to multiply, L.N to write; the limits are
+// those of 32-bit offsets and of divisions by reciprocals.
+void held_launch(Launch &L, int64_t n_img, int64_t H, int64_t W, int64_t P, int64_t Q, int64_t C, int64_t R, int64_t S, int64_t pad_h, int64_t pad_w, int64_t str_h,
+                 int64_t str_w, int64_t dil_h, int64_t dil_w) {
+    L.cN = n_img; L.cP = P; L.cQ = Q; L.cC = C;
+    const bool ok = R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == str_w && (str_h == 1 || (str_h == 2 && L.mode == 2)) && dil_h == 1 && dil_w == 1 && L.dt < 2 &&
+                    (L.dt == 0 ? variants_conv_held_bf16() : variants_conv_held_f16()).n > 0 &&
+                    (L.mode == 3 || C <= 64 * kHeldMaxKG) && L.N % 8 == 0 && Q <= 1024 && P < (1 << 20) && n_img * (P + 1) * ((L.N + 31) / 32) < (1ll << 20) &&
+                    n_img * P * Q * L.N < (1ll << 30) && n_img * H * W * C < (1ll << 30) && C * 9 * L.N < (1ll << 30);
+    L.held_stride = ok ? (int)str_h : 0;
+    L.gathered = n_img * H * W * C * 2;
 }
 
 // Per-problem selection: of the variants built for this (mode, input type, operand layouts) the one with the smallest
@@ -240,6 +256,8 @@ double estimate_seconds(const VariantDesc &v, const CostRow &row, const CostRow 
 }
 
 constexpr int kNumCUs = 256;
+
+
 
 // Slices a split-K launch of `total_tiles` tiles gets: as asked for, or (0) enough to give every CU a workgroup
 // while each keeps at least 4 x 64 of K; slices are whole multiples of 64 along K.
@@ -568,6 +586,97 @@ bool few_rows_apply(const VariantDesc &v, const Launch &L) {
     // 40.3 us; over 3600 problems it is 1.04 to 1.7 times behind below 128 tiles, level from there on)
     if (L.mode == 0) return L.K > (L.dt >= 2 ? 64 : 256) && (v.tile_m < 64 || (L.M > 32 && count_tiles(L, v.tile_m, v.tile_n) >= kNumCUs / 2));
     return L.K >= 320;
+}
+
+// Seconds of a conv_held_kernel launch (constants in ucl_costs.h): the workgroups of a round have `pairs` pairs of rows per wave to
+// multiply and `pixels` bytes of pixels and their filters to copy, whose rate falls with the CUs that copy; or what all of them move.
+double held_seconds(const Launch &L, const HeldPlan &h, int pairs, int64_t pixels, bool residual) {
+    const HeldCosts &c = kHeldCosts;
+    const int k = h.kg == 1 ? 0 : h.kg == 2 ? 1 : 2, mg = 8 / (h.kg * h.ng), m = mg == 1 ? 0 : mg == 2 ? 1 : 2;
+    const double filter = h.kg * h.ng * 36.864e3, fixed = c.pass[k] + c.sharing[m] + c.pair[k] * pairs;
+    auto round = [&](double busy) { return h.passes * (fixed + filter * (c.filter * busy + c.filter_alone) + (double)pixels * (c.pixels * busy + c.pixels_alone)) + c.next_pass * (h.passes - 1); };
+    const int64_t wgs = (int64_t)h.bands * h.tiles_n, full = wgs / kNumCUs, rest = wgs % kNumCUs;
+    const double cus = c.launch + (double)full * round(1.0) + (rest ? round((double)rest / kNumCUs) : 0.0);
+    const double moved = (double)L.gathered + (double)(L.cN * L.cP * L.cQ) * (double)(L.N * (residual ? 2 : 1)) * 2.0;
+    return 1e-6 * fourth_power_sum(cus, c.memory + c.moved * moved + c.weights * (double)(9 * L.cC * L.N) * 2.0);
+}
+
+// How conv_held_kernel would cut up a problem: of the plans whose pixels fit into LDS, with as many rows per workgroup as one, two or three rounds
+// of workgroups take or as LDS holds, the one with the shortest estimate.
+HeldPlan choose_held(const Launch &L, bool residual) {
+    HeldPlan best;
+    if (!L.held_stride) return best;
+    HeldPlan h;
+    h.stride = L.held_stride;
+    h.kg = L.cC <= 64 ? 1 : L.cC <= 128 ? 2 : kHeldMaxKG;
+    h.passes = (int)((L.cC + 64 * h.kg - 1) / (64 * h.kg));
+    h.pair = L.cQ <= 7 ? 2 : 1;
+    h.pitch = (int)(L.cQ + 16) / 16 * 16;
+    h.strips = h.pair == 2 ? 1 : (int)(L.cQ + 15) / 16;
+    h.rows = (int)((L.cN + h.pair - 1) / h.pair * (L.cP + 1));
+    for (h.ng = 4; h.ng >= 1; h.ng /= 2) {
+        const int capacity = held_patch_capacity(h.kg, h.ng);
+        if (capacity == 0) continue;
+        h.tiles_n = (int)((L.N + 32 * h.ng - 1) / (32 * h.ng));
+        const int mg = 8 / (h.kg * h.ng);
+        for (h.strip_split = 1; h.strip_split <= mg; h.strip_split *= 2) {
+            const int groups = mg / h.strip_split, strips = (h.strips + h.strip_split - 1) / h.strip_split;
+            auto per_of = [&](int R) { return ((R + groups - 1) / groups + 1) & ~1; };
+            // (sums of earlier passes: one more pair, what the first pair's MFMAs find to finish)
+            auto keep_of = [&](int R) { return h.passes > 1 ? (per_of(R) * strips + 2) * 512 * (8 / h.kg) * 4 : 0; };
+            int most = ((capacity / h.kg / 128 - 8) / (h.stride * h.pitch) - 3 + h.stride) / h.stride;
+            while (most > 0 && held_plane_bytes(h.stride, most, h.pitch) * h.kg + keep_of(most) > capacity) --most;
+            for (int rounds = 1; rounds <= 4 && most > 0; ++rounds) {
+                const int bands = kNumCUs * rounds / h.tiles_n;
+                h.R = bands > 0 ? (h.rows + bands - 1) / bands : most + 1;
+                if (h.R > most) {
+                    if (rounds < 4) continue;
+                    h.R = most;
+                }
+                // (rows are multiplied in pairs and strips 16 columns at a time: what is read beyond the band's pixels has to be in LDS, too)
+                const int per = per_of(h.R), last = (h.R - 1) / per * per + per;
+                if (held_plane_bytes(h.stride, h.R, h.pitch) * (h.kg - 1) + ((int64_t)(h.stride * (last - 1) + 3) * h.stride * h.pitch + 16 * h.strip_split + 32) * 128 > kLdsBytesPerCU) continue;
+                h.bands = (h.rows + h.R - 1) / h.R;
+                h.keep_bytes = keep_of(h.R);
+                h.seconds = held_seconds(L, h, per / 2 * strips, held_plane_bytes(h.stride, h.R, h.pitch) * h.kg, residual);
+                if (best.R == 0 || h.seconds < best.seconds) best = h;
+                if (h.R == most || h.R == 1) break;
+            }
+        }
+    }
+    return best;
+}
+
+// Seconds of the kernel that a convolution would get instead.  kCostRows price the resident-patch kernels as if they gathered every tap from memory,
+// which serves among tile kernels but is up to 1.8 times what they take where there are more tiles than slots.  (Gathering forward kernels
+// take 1.05 of what their rows say in the mean, the few-row ones 0.95.)
+double tile_kernel_seconds(const VariantDesc &v, const Launch &L, bool residual) {
+    if (v.la == 3) {
+        for (const PatchRow &r : kPatchRows) {
+            if (r.mode != v.mode || r.tile_m != v.tile_m || r.tile_n != v.tile_n || r.patch_c != v.patch_c) continue;
+            const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n), rounds = (tiles + 2 * kNumCUs - 1) / (2 * kNumCUs);
+            const double on_cu = tiles <= 2 * kNumCUs ? (double)((tiles + kNumCUs - 1) / kNumCUs) : 2.0 * (double)rounds, K = (double)L.K;
+            const double copies = on_cu * (v.tile_m + (double)(L.N < v.tile_n ? L.N : v.tile_n)) * K * 2.0 / (r.gbs * 1e3);
+            const double math = on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6);
+            const double chain = (double)rounds * (double)((L.K + 31) / 32) * r.step, memory = ((double)L.M + (double)L.N) * K * 2.0 / 9.0 / 5.3e6;
+            const double out = (double)L.M * (double)L.N * 2.0 / 4.6e6 * r.out * (L.mode == 2 && !residual ? 0.5 : 1.0);      // (fitted to forward passes with a residual)
+            return 1e-6 * (r.fixed + r.round * (double)rounds + fourth_power_sum(fourth_power_sum(copies, math, chain, memory), out * r.hidden) + out * (1.0 - r.hidden));
+        }
+    }
+    const size_t i = (size_t)(&v - all_variants().data());
+    bool one = false;
+    return estimate_seconds(v, all_costs()[i], many_tiles_costs()[i], L, &one) * (L.mode != 2 || v.la != 2 ? 1.0 : is_few_row(v) ? 0.95 : 1.05);
+}
+
+// The plan of a convolution that runs on conv_held_kernel, R = 0 for one that does not: calls that name nothing, with the chains of the usual layers (scale,
+// bias, residual, ReLU) and outputs of the inputs' type, where the estimate is shorter than that of the kernel `v` the call would get.
+HeldPlan plan_held(const Launch &L, const KParams &kp, const ucl_tuning *tune, const VariantDesc &v) {
+    if (!L.held_stride || (tune && (names_tile(tune) || tune->raster || tune->iterator || tune->scheduler || tune->split_k_mode))) return HeldPlan();
+    const int type = L.dt == 1 ? UCL_F16 : UCL_BF16;
+    const FusedEpi &f = kp.fused;
+    if (!f.enabled || (f.act && f.act != UCL_EPI_RELU) || L.dtD != type || !kp.d_vec || (f.has_res && (f.res_dt != (type | 0x100) || f.res_ld != L.N))) return HeldPlan();
+    const HeldPlan h = choose_held(L, f.has_res != 0);
+    return h.R > 0 && h.seconds < tile_kernel_seconds(v, L, f.has_res != 0) ? h : HeldPlan();
 }
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {
@@ -1164,6 +1273,14 @@ ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool
         if (taps.slices == 1 || (taps.slices > 1 && tune->workspace && aligned16(tune->workspace) && taps_bytes(L, taps) <= tune->workspace_bytes))
             return run_taps(L, kp, taps, tune->workspace, stream);
     }
+    if (L.held_stride) {
+        const HeldPlan h = plan_held(L, kp, tune, *v);
+        if (h.R > 0) {
+            const hipError_t e = (L.dt == 0 ? variants_conv_held_bf16() : variants_conv_held_f16()).v->launch_held(L.mode, h, kp, (hipStream_t)stream);
+            if (e != hipSuccess) return fail(UCL_ERR_LAUNCH, "kernel launch failed: %s", hipGetErrorString(e));
+            return UCL_OK;
+        }
+    }
     if (total == 0) return UCL_OK;     // grouped with every M_g == 0: nothing to do
     const GroupTable *gtp = L.mode == 1 ? &gt : nullptr;
     hipError_t e;
@@ -1548,6 +1665,7 @@ ucl_status ucl_conv2d_fprop(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     Launch L;
     L.mode = 2; L.M = M; L.N = Kout; L.K = Kg; L.la = 2; L.lb = 0; L.dt = dt_code(dtX); L.dtD = dtY;
     L.patch_c = conv_patch_channels(W, C, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
+    held_launch(L, N, H, W, P, Q, C, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
     KParams kp;
     memset(&kp, 0, sizeof(kp));
     if (ucl_status st = check_epilogue(epi, L, kp)) return st;
@@ -1603,6 +1721,7 @@ ucl_status ucl_conv2d_dgrad(int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     L.mode = 3; L.M = M; L.N = C; L.K = Kg; L.la = 2; L.lb = 1; L.ndirect_ok = true; L.dt = dt_code(dtDy); L.dtD = dtDx;
     L.patch_c = conv_patch_channels(W, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
     dgrad_launch(L, N, H, W, stride_h, stride_w);
+    held_launch(L, N, P, Q, H, W, Kout, R, S, pad_h, pad_w, stride_h, stride_w, dil_h, dil_w);
     KParams kp;
     memset(&kp, 0, sizeof(kp));
     // (the tiles that take longest start first)

@@ -155,4 +155,28 @@ static const SplitCostRow kWgradSplitRows[] = {
     {64, 64, 64, 4,  0.00f, 2.41f},
 };
 
+// Resident-patch kernels of two workgroups per CU, for the choice between them and conv_held_kernel (tile_kernel_seconds): fitted to the 2270 of 12000
+// geometries that kCostRows give to them, 3 to 5 % off where those rows are 10 to 15 %.
+struct PatchRow {
+    short mode, tile_m, tile_n, patch_c;
+    float fixed, round, gbs, tflops, step, out, hidden;
+};
+static const PatchRow kPatchRows[] = {
+    {3, 128, 64, 128,  3.97f, 3.57f, 803.0f, 5.45f, 0.094f, 5.20f, 0.85f},
+    {3, 256, 64, 64,  7.14f, 0.00f, 181.0f, 5.15f, 0.080f, 1.47f, 0.30f},
+    {2, 128, 64, 128,  4.26f, 1.22f, 126.9f, 9.98f, 0.160f, 2.63f, 0.00f},
+    {2, 256, 128, 64,  10.66f, 0.00f, 203.1f, 6.21f, 0.092f, 1.44f, 0.38f},
+};
+
+// Launches of conv_held_kernel, microseconds (per byte; by wave groups over channels 1, 2, 4 and by waves that share a filter 1, 2, 4): fitted to 66000 launches
+// of 12000 geometries (1 to 64 images of 5 to 80 pixels a side, 16 to 1024 channels), 7 % off; the plan chosen with them is 1.6 % behind the best of
+// six measured ones on 12000 others.
+struct HeldCosts {
+    double launch, pass[3], sharing[3], pair[3], next_pass;              // pair: a wave's two rows of 16 pixels
+    double filter, filter_alone, pixels, pixels_alone;                   // bytes that a workgroup copies, by the share of busy CUs and by themselves
+    double memory, moved, weights;                                       // bytes that all of them move
+};
+static const HeldCosts kHeldCosts = {2.933, {1.864, 2.100, 2.098}, {0.178, 0.389, 0.137}, {1.320, 1.482, 1.512}, 1.565,
+                                     3.83e-6, 0.14e-6, 11.4e-6, 19.7e-6, 2.357, 0.260e-6, 1.46e-6};
+
 }  // namespace ucl

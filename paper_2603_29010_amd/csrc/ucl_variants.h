@@ -4,6 +4,29 @@
 
 namespace ucl {
 
+// 3x3 convolutions with the filter in registers (conv_held_kernel): how a launch is cut up.  Not among the variants that a tile names.
+struct HeldPlan {
+    int stride = 1;
+    int kg = 0, ng = 0;            // wave groups over channels (64 each) and filters (32 each) of a workgroup; 0: not served
+    int R = 0;                     // padded output rows per workgroup
+    int strip_split = 1;           // of the waves that kg and ng leave, as many share out strips, the others rows
+    int pair = 1, pitch = 0, strips = 0, rows = 0, bands = 0, tiles_n = 0, passes = 1, keep_bytes = 0;
+    double seconds = 0;
+};
+constexpr int kHeldMaxKG = 4;
+// LDS of a workgroup: one tap of its filters (KG x NG x 4 KB), several on their way; where KG > 1 its waves' sums of four output rows meet in their
+// place; 1 KB for the bias.  The rest is its pixels' (0: wave groups that no kernel is built for).
+constexpr int held_slots(int kg, int ng) { return kg * ng == 8 ? 3 : kg * ng == 4 ? 4 : 9; }
+constexpr int held_filter_bytes(int kg, int ng) {
+    const int filter = held_slots(kg, ng) * kg * ng * 4096, meet = kg == 1 ? 0 : 4 * 8 * 2048;
+    return filter > meet ? filter : meet;
+}
+constexpr int held_patch_capacity(int kg, int ng) {
+    return kg * ng <= 8 && (kg == 2 || ng == 2 || kg * ng == 4) ? kLdsBytesPerCU - held_filter_bytes(kg, ng) - 1024 : 0;
+}
+// ... which are, for R output rows at a pitch: the image rows their taps reach and eight zeros behind them, per plane of 64 channels
+constexpr int64_t held_plane_bytes(int64_t stride, int64_t R, int64_t pitch) { return ((stride * R + 3 - stride) * stride * pitch + 8) * 128; }
+
 struct VariantDesc {
     int tile_m, tile_n, tile_k, stages;
     int dt;             // inputs: 0 bf16, 1 fp16, 2 fp8 e4m3, 3 fp8 e5m2 (8-bit inputs are handled as pairs: K, strides in 16-bit units)
@@ -18,6 +41,7 @@ struct VariantDesc {
     int patch_c;        // resident-patch kernels: channels per pixel of the tensor the patch holds (64 or 128), else 0
     hipError_t (*launch)(const KParams &p, const GroupTable *gt, int grid, hipStream_t stream);
     int (*resident)();          // workgroups one CU holds at a time (queried from the runtime)
+    hipError_t (*launch_held)(int mode, const HeldPlan &h, const KParams &p, hipStream_t stream);      // variants_conv_held_* only
 };
 
 // Few-row kernels of four waves: with more tiles than this, one per CU, those with one stage buffer per wave serve (gemm and batched calls: the
@@ -70,5 +94,9 @@ VariantList variants_kgroups_conv_grad();
 // conv2d_wgrad with all taps of a pixel in one workgroup, by input type (not among the variants that a tile names; split_k and k_per_slice of
 // its arguments are slices and padded pixels per slice)
 VariantList variants_wgrad_taps();
+
+// 3x3 convolutions and data gradients with the filter in registers, by input type (chosen only, by their launch_held)
+VariantList variants_conv_held_bf16();
+VariantList variants_conv_held_f16();
 
 }  // namespace ucl

@@ -5,7 +5,7 @@ import os
 import pytest
 
 from paper_2603_29010_amd import build
-from paper_2603_29010_amd.build import early_use_of_transpose_reads
+from paper_2603_29010_amd.build import early_use_of_transpose_reads, overwritten_store
 
 READ_A = ["ds_read_b64_tr_b16 v[10:11], v2", "ds_read_b64_tr_b16 v[12:13], v2 offset:1024"]
 READ_B = ["ds_read_b128 v[20:23], v3", "ds_read_b128 v[24:27], v3 offset:2048"]
@@ -26,6 +26,15 @@ def test_a_wait_has_to_cover_the_transpose_read():
     assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0)"], MUL) is not None
     assert scan(READ_A, READ_B, ["s_waitcnt vmcnt(0) lgkmcnt(0)"], MUL) is None
     assert scan(READ_A, ["v_add_u32_e32 v12, 1, v4"], ["s_waitcnt lgkmcnt(0)"]) is not None        # overwritten in flight
+
+
+def test_the_data_of_a_wide_store_stay_for_an_instruction():
+    store = "buffer_store_dwordx4 v[172:175], v215, s[28:31], s59 offen"
+    assert overwritten_store([store, "v_mov_b32_e32 v172, v192"]) == (2, "v_mov_b32_e32 v172, v192")
+    assert overwritten_store(["global_store_dwordx4 v[2:3], v[4:7], off", "v_add_u32_e32 v6, 1, v9"]) == (2, "v_add_u32_e32 v6, 1, v9")
+    for between in ("s_nop 0", "v_mov_b32_e32 v215, v192", "v_mov_b32_e32 v171, v192"):
+        assert overwritten_store([store, between, "v_mov_b32_e32 v172, v192"]) is None
+    assert overwritten_store([store.replace("x4 v[172:175]", "x2 v[172:173]"), "v_mov_b32_e32 v172, v192"]) is None
 
 
 def test_the_extension_module_is_named_for_its_interpreter():
