@@ -590,7 +590,7 @@ bool few_rows_apply(const VariantDesc &v, const Launch &L) {
 
 // Seconds of a conv_held_kernel launch (constants in ucl_costs.h): the workgroups of a round have `pairs` pairs of rows per wave to
 // multiply and `pixels` bytes of pixels and their filters to copy, whose rate falls with the CUs that copy; or what all of them move.
-double held_seconds(const Launch &L, const HeldPlan &h, int pairs, int64_t pixels, bool residual) {
+double held_seconds(const Launch &L, const HeldPlan &h, double pairs, int64_t pixels, bool residual) {
     const HeldCosts &c = kHeldCosts;
     const int k = h.kg == 1 ? 0 : h.kg == 2 ? 1 : 2, mg = 8 / (h.kg * h.ng), m = mg == 1 ? 0 : mg == 2 ? 1 : 2;
     const double filter = h.kg * h.ng * 36.864e3, fixed = c.pass[k] + c.sharing[m] + c.pair[k] * pairs;
@@ -621,7 +621,7 @@ HeldPlan choose_held(const Launch &L, bool residual) {
         const int mg = 8 / (h.kg * h.ng);
         for (h.strip_split = 1; h.strip_split <= mg; h.strip_split *= 2) {
             const int groups = mg / h.strip_split, strips = (h.strips + h.strip_split - 1) / h.strip_split;
-            auto per_of = [&](int R) { return ((R + groups - 1) / groups + 1) & ~1; };
+            auto per_of = [&](int R) { return held_rows_of_wave(R, groups, h.kg, h.passes > 1); };
             // (sums of earlier passes: one more pair, what the first pair's MFMAs find to finish)
             auto keep_of = [&](int R) { return h.passes > 1 ? (per_of(R) * strips + 2) * 512 * (8 / h.kg) * 4 : 0; };
             int most = ((capacity / h.kg / 128 - 8) / (h.stride * h.pitch) - 3 + h.stride) / h.stride;
@@ -638,7 +638,7 @@ HeldPlan choose_held(const Launch &L, bool residual) {
                 if (held_plane_bytes(h.stride, h.R, h.pitch) * (h.kg - 1) + ((int64_t)(h.stride * (last - 1) + 3) * h.stride * h.pitch + 16 * h.strip_split + 32) * 128 > kLdsBytesPerCU) continue;
                 h.bands = (h.rows + h.R - 1) / h.R;
                 h.keep_bytes = keep_of(h.R);
-                h.seconds = held_seconds(L, h, per / 2 * strips, held_plane_bytes(h.stride, h.R, h.pitch) * h.kg, residual);
+                h.seconds = held_seconds(L, h, (per / 2 + (per & 1 ? 0.55 : 0.0)) * strips, held_plane_bytes(h.stride, h.R, h.pitch) * h.kg, residual);
                 if (best.R == 0 || h.seconds < best.seconds) best = h;
                 if (h.R == most || h.R == 1) break;
             }

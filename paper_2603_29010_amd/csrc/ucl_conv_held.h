@@ -15,6 +15,8 @@
 // 295 KB of filters per CU stretch to 4 us where all CUs copy (15 TB/s from L2).  Measured on the steps to it, 4 images of 56 x 56 x 64 <- 64, us per
 // pair: rows one by one with a branch per tap row 2.3, pairs 1.95, addresses kept and conversions packed 1.55, sums stored from the MFMA's layout 1.3.
 // Stores with the non-temporal bit and residual loads without it (a wave reads half lines): 32 x 56 x 56 x 64 -> 128 22.7 -> 20.8 us.
+// A last single row with half of the MFMAs (KG > 1; 0.55 of a pair) instead of a pair with one row missing: 1.02 on average over 300 drawn forward
+// passes and data gradients of 128 and 256 channels, up to 1.09 (44 x 32 x 32 x 128 -> 128); launches of even rows as before.
 // Tile kernels -> here, us in a graph: forward with bias, residual and ReLU 32 x 56 x 56 x 64 -> 128 27.8 -> 20.2, 32 x 56 x 56 x 64 -> 64 24.2 -> 12.3,
 // 32 x 28 x 28 x 128 -> 128 16.3 -> 12.9, 4 x 14 x 14 x 256 -> 256 11.1 -> 7.9; data gradients 32 x 28 x 28 x 128 14.9 -> 12.6, 32 x 14 x 14 x 256
 // 27.5 -> 18.9, 4 x 14 x 14 x 256 17.0 -> 8.1, 1 x 56 x 56 x 64 10.5 -> 6.3.
@@ -237,9 +239,10 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
     // ---- the wave's part of the band: strips of 16 columns, two output rows at a time -----------------------------------
     const int sgroups = a.strip_split, rgroups = MG / sgroups;
     const int ms = mg & (sgroups - 1), mr = mg / sgroups;
-    const int per = ((R + rgroups - 1) / rgroups + 1) & ~1, first = mr * per;        // output rows of the wave, and where they start
+    const int per = held_rows_of_wave(R, rgroups, KG, Cfg::MULTI), first = mr * per;    // output rows of the wave, and where they start
     if (KG == 1 && first >= R) return;
     const int img0 = divide(row0 + first, a.rcp_rows), p0 = row0 + first - img0 * Pp;
+    const int own_rows = R - first < per ? R - first : per;
     const int rows_left = R - first < a.rows - row0 - first ? R - first : a.rows - row0 - first;
     const int strip_rounds = (a.strips + sgroups - 1) / sgroups;
     const int own = lane_again(), l = own & 15, g = own >> 4;
@@ -357,7 +360,10 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
     };
     // Input rows ST o .. ST o + 2 meet output row o, ST rows on those of row o + 1.  Loads of the residual and stores
     // are issued for every row, out of range where there is nothing to do: waits then count them.
-    auto rows = [&](auto par_) __attribute__((always_inline)) {
+    // (ONE: the pair's second row is not the wave's: half of the MFMAs.  Where KG = 1 the body's own finishing does not fit into the registers,
+    // nor with several passes: those count their rows in pairs.)
+    auto rows = [&](auto par_, auto one_) __attribute__((always_inline)) {
+        constexpr bool ONE = decltype(one_)::value;
         using Par = std::integral_constant<int, decltype(par_)::value>;
         using Other = std::integral_constant<int, 1 - decltype(par_)::value>;
         uint32_t off[2], row[2];
@@ -368,15 +374,15 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
             if constexpr (Cfg::RES) load(Par{}, k, off[k], row[k]);
         });
         // the first row after this pair (stride 1: one up from its last, stride 2: its last again), or the wave's next strip
-        const int back = o + 2 < per ? (ST - 2) * line * 128 : sr + 1 < strip_rounds ? (sgroups * 16 - (ST * (per - 1) + 2) * line) * 128 : 0;
-        constexpr int ROWS = ST + 3;
+        const int back = o + 2 < per ? (ONE ? 2 * ST - 2 : ST - 2) * line * 128 : sr + 1 < strip_rounds ? (sgroups * 16 - (ST * (ONE ? o : per - 1) + 2) * line) * 128 : 0;
+        constexpr int ROWS = ONE ? 3 : ST + 3;
         static_for<ROWS>([&](auto j_) {
             constexpr int j = decltype(j_)::value;
             static_for<3>([&](auto s) { at[s] += j == ROWS - 1 ? back : line * 128; });
             static_for<6>([&](auto f_) {
                 constexpr int f = decltype(f_)::value, s = f >> 1, ks = f & 1;
                 if constexpr (j <= 2) static_for<2>([&](auto nb) { mfma_held<DT, j == 0 && f == 0>(acc[0][nb], wf[j * 3 + s][ks][nb], fr[f]); });
-                if constexpr (j >= ST) static_for<2>([&](auto nb) { mfma_held<DT, j == ST && f == 0>(acc[1][nb], wf[(j - ST) * 3 + s][ks][nb], fr[f]); });
+                if constexpr (j >= ST && !ONE) static_for<2>([&](auto nb) { mfma_held<DT, j == ST && f == 0>(acc[1][nb], wf[(j - ST) * 3 + s][ks][nb], fr[f]); });
                 fetch(f_);
                 // (four MFMAs have been issued since the last one of the sums that are read here)
                 if constexpr (KG == 1) {
@@ -402,6 +408,10 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
+        if constexpr (ONE) {
+            sums_ready(acc[0]);
+            put(Par{}, I0{});
+        }
         static_for<2>([&](auto k) {
             late_off[k] = off[k];
             late_row[k] = row[k];
@@ -409,9 +419,12 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
     };
     // true behind the last pair
     auto step = [&](auto par) __attribute__((always_inline)) {
-        rows(par);
+        if constexpr (KG > 1 && !Cfg::MULTI) {
+            if (o + 1 < own_rows) rows(par, std::false_type{});
+            else rows(par, std::true_type{});
+        } else rows(par, std::false_type{});
         o += 2;
-        if (o == per) {
+        if (o >= per) {
             o = 0;
             if (++sr < strip_rounds) strip_start();
         }

@@ -26,6 +26,11 @@ constexpr int held_patch_capacity(int kg, int ng) {
 }
 // ... which are, for R output rows at a pitch: the image rows their taps reach and eight zeros behind them, per plane of 64 channels
 constexpr int64_t held_plane_bytes(int64_t stride, int64_t R, int64_t pitch) { return ((stride * R + 3 - stride) * stride * pitch + 8) * 128; }
+// Rows of one of `groups` waves that share R: in pairs, and a last single one where the registers hold its own body
+constexpr int held_rows_of_wave(int R, int groups, int kg, bool multi) {
+    const int rows = (R + groups - 1) / groups;
+    return kg == 1 || multi ? (rows + 1) & ~1 : rows;
+}
 
 struct VariantDesc {
     int tile_m, tile_n, tile_k, stages;
