@@ -15,8 +15,8 @@
 // 295 KB of filters per CU stretch to 4 us where all CUs copy (15 TB/s from L2).  Measured on the steps to it, 4 images of 56 x 56 x 64 <- 64, us per
 // pair: rows one by one with a branch per tap row 2.3, pairs 1.95, addresses kept and conversions packed 1.55, sums stored from the MFMA's layout 1.3.
 // Stores with the non-temporal bit and residual loads without it (a wave reads half lines): 32 x 56 x 56 x 64 -> 128 22.7 -> 20.8 us.
-// A last single row with half of the MFMAs (KG > 1; 0.55 of a pair) instead of a pair with one row missing: 1.02 on average over 300 drawn forward
-// passes and data gradients of 128 and 256 channels, up to 1.09 (44 x 32 x 32 x 128 -> 128); launches of even rows as before.
+// A last single row with half of the MFMAs (KG > 1; 0.55 of a pair) instead of a pair with one row missing: 1.03 on average over 120 drawn forward
+// passes of 128 and 256 channels, up to 1.14 (12 x 11 x 11 x 256 -> 512), 1.014 with data and filter gradient together; launches of even rows as before.
 // Tile kernels -> here, us in a graph: forward with bias, residual and ReLU 32 x 56 x 56 x 64 -> 128 27.8 -> 20.2, 32 x 56 x 56 x 64 -> 64 24.2 -> 12.3,
 // 32 x 28 x 28 x 128 -> 128 16.3 -> 12.9, 4 x 14 x 14 x 256 -> 256 11.1 -> 7.9; data gradients 32 x 28 x 28 x 128 14.9 -> 12.6, 32 x 14 x 14 x 256
 // 27.5 -> 18.9, 4 x 14 x 14 x 256 17.0 -> 8.1, 1 x 56 x 56 x 64 10.5 -> 6.3.
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(512, 2) void conv_held_kernel(const ConvHeld a) {
     if (KG == 1 && first >= R) return;
     const int img0 = divide(row0 + first, a.rcp_rows), p0 = row0 + first - img0 * Pp;
     const int own_rows = R - first < per ? R - first : per;
-    const int rows_left = R - first < a.rows - row0 - first ? R - first : a.rows - row0 - first;
+    const int rows_left = own_rows < a.rows - row0 - first ? own_rows : a.rows - row0 - first;
     const int strip_rounds = (a.strips + sgroups - 1) / sgroups;
     const int own = lane_again(), l = own & 15, g = own >> 4;
     // fragment addresses: shift s, chunk g (the other half of the channels: ^ 64)

@@ -42,16 +42,16 @@ def check_rounded(spec):
 
 
 # (channels of one pass: 64, 128 and 256 in one, two and four wave groups; filters in tiles of 32, 64 and 128; images of up to 7 columns in pairs,
-# the last one without a partner; one, three and five rows per workgroup; rows of more than one strip, and of a strip and one column; one-pixel and one-row images)
+# the last one without a partner; one, three and five rows per workgroup, by one or more waves; rows of more than one strip, and of a strip and one column; one-pixel and one-row images)
 FPROP = [geom(5, 28, 28, 64, 128), geom(2, 56, 56, 64, 72), geom(3, 13, 17, 40, 136), geom(6, 28, 28, 128, 128), geom(4, 9, 33, 104, 40),
          geom(9, 14, 14, 256, 72), geom(2, 15, 16, 136, 264), geom(31, 7, 7, 256, 64), geom(3, 5, 7, 64, 32), geom(7, 1, 1, 64, 64), geom(2, 1, 60, 32, 64),
          geom(40, 6, 3, 128, 24),
          geom(4, 56, 56, 64, 128, 2), geom(3, 27, 33, 40, 72, 2), geom(2, 30, 28, 128, 64, 2), geom(5, 28, 27, 256, 72, 2), geom(9, 14, 13, 128, 264, 2),
-         geom(40, 14, 14, 256, 64), geom(70, 9, 17, 128, 64), geom(14, 18, 18, 128, 256, 2), geom(90, 7, 7, 256, 128),
+         geom(40, 14, 14, 256, 64), geom(70, 9, 17, 128, 64), geom(14, 18, 18, 128, 256, 2), geom(90, 7, 7, 256, 128), geom(85, 14, 14, 128, 64),
          geom(7, 15, 2, 104, 40, 2), geom(3, 1, 30, 64, 64, 2), geom(2, 32, 63, 64, 48, 2), geom(33, 14, 14, 256, 64, 2), geom(6, 27, 25, 104, 128, 2)]
 DGRAD = [geom(5, 28, 28, 128, 64), geom(2, 56, 56, 72, 64), geom(3, 13, 17, 136, 40), geom(6, 28, 28, 128, 128), geom(4, 9, 33, 32, 104),
          geom(9, 14, 14, 72, 256), geom(5, 15, 16, 264, 136), geom(31, 7, 7, 64, 256), geom(3, 5, 7, 32, 64), geom(2, 14, 14, 64, 512), geom(9, 7, 7, 136, 520),
-         geom(2, 8, 8, 72, 1024), geom(40, 14, 14, 64, 256), geom(90, 9, 17, 64, 128), geom(42, 29, 29, 64, 256)]
+         geom(2, 8, 8, 72, 1024), geom(40, 14, 14, 64, 256), geom(90, 9, 17, 64, 128), geom(42, 29, 29, 64, 256), geom(43, 14, 14, 64, 128)]
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
