@@ -43,9 +43,9 @@ SPIN_UP_SECONDS = 0.5
 # HBM bytes moved per launch (read + written) as counted by rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE,
 # each scaled by what the same counter reads for a plain 256 MiB device copy (2.000 and 1.000).
 # Counters cannot be read from inside this process: these are the figures RECORDED in
-# profiles/ucl_tile_kernel_*.txt (with the commands that produced them) for the kernels the selection
+# profiles/*_kernel_*.txt (with the commands that produced them) for the kernels the selection
 # table picks, not measurements of the run that prints them.
-RECORDED_TRAFFIC_BYTES = {1: 1160248, 2: 235364923, 3: 84280114, 4: 525456226, 5: 66147739}
+RECORDED_TRAFFIC_BYTES = {1: 1160248, 2: 235364923, 3: 84280114, 4: 525456226, 5: 71409268}
 # The same for the rows of --widening (profiles/ucl_tile_kernel_widening_rows.txt; all launches of a step added up).
 WIDENING_TRAFFIC_BYTES = {
     "gemm_4096x4096x4096_fp8_e4m3_rowcol_bias_gelu_tanh_bf16out": 134654126,
