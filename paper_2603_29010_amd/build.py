@@ -72,20 +72,44 @@ def _check_asm(obj):
             raise RuntimeError(f"{asm}: line {bad[0]}: `{bad[1]}` touches the result of a transpose read that may still be in flight")
 
 
+STORE_WAIT_STATES = 2             # between a store of more than 64 bits and a write to its data (what the compiler keeps for stores without a scalar offset)
+
+
 def overwritten_store(lines):
-    """The first (line number, instruction) that overwrites the data of a store of more than 64 bits right behind it, or None: the store may still be
-    reading them, also where its offset is in a scalar register and the compiler expects no hazard."""
-    data = set()
+    """The first (line number, instruction) that overwrites the data of a store of more than 64 bits within STORE_WAIT_STATES behind it, or None: the
+    store may still be reading them, also where its offset is in a scalar register and the compiler expects no hazard.  An instruction is one
+    wait state, `s_nop n` n + 1; branches are followed to their labels."""
+    code, labels = [], {}                             # (line number, instruction, op), and where labels point in it
     for number, line in enumerate(lines, 1):
         ins = line.split(";")[0].strip()
-        if not ins or ins.startswith(".") or ins.endswith(":"):
-            continue
-        op = ins.split()[0]
-        operands = ins[len(op):].split(",")
-        if data and op.startswith("v_") and _vregs(operands[0]) & data:
-            return number, ins
+        if ins.endswith(":"):
+            labels[ins[:-1]] = len(code)
+        elif ins and not ins.startswith("."):
+            code.append((number, ins, ins.split()[0]))
+
+    def behind(at, data, left):
+        """The same for one store, from instruction `at` with `left` wait states to go."""
+        while at < len(code) and left > 0:
+            number, ins, op = code[at]
+            operands = ins[len(op):].split(",")
+            if op.startswith("v_") and _vregs(",".join(operands[:2 if op.startswith("v_swap") else 1])) & data:
+                return number, ins
+            left -= int(operands[0], 0) + 1 if op == "s_nop" else 1
+            if op == "s_branch" or op.startswith("s_cbranch"):
+                bad = behind(labels.get(operands[0].strip(), len(code)), data, left)
+                if bad:
+                    return bad
+            if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                return None
+            at += 1
+        return None
+
+    for at, (_, ins, op) in enumerate(code):
         m = re.match(r"(buffer|global|flat)_store_dwordx[34]", op)
-        data = _vregs(operands[0 if m.group(1) == "buffer" else 1]) if m else set()
+        if m:
+            bad = behind(at + 1, _vregs(ins[len(op):].split(",")[0 if m.group(1) == "buffer" else 1]), STORE_WAIT_STATES)
+            if bad:
+                return bad
     return None
 
 

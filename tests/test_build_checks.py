@@ -28,13 +28,27 @@ def test_a_wait_has_to_cover_the_transpose_read():
     assert scan(READ_A, ["v_add_u32_e32 v12, 1, v4"], ["s_waitcnt lgkmcnt(0)"]) is not None        # overwritten in flight
 
 
-def test_the_data_of_a_wide_store_stay_for_an_instruction():
-    store = "buffer_store_dwordx4 v[172:175], v215, s[28:31], s59 offen"
-    assert overwritten_store([store, "v_mov_b32_e32 v172, v192"]) == (2, "v_mov_b32_e32 v172, v192")
+def test_the_data_of_a_wide_store_stay_for_two_wait_states():
+    store, write = "buffer_store_dwordx4 v[172:175], v215, s[28:31], s59 offen", "v_mov_b32_e32 v172, v192"
+    assert overwritten_store([store, write]) == (2, write)
     assert overwritten_store(["global_store_dwordx4 v[2:3], v[4:7], off", "v_add_u32_e32 v6, 1, v9"]) == (2, "v_add_u32_e32 v6, 1, v9")
-    for between in ("s_nop 0", "v_mov_b32_e32 v215, v192", "v_mov_b32_e32 v171, v192"):
-        assert overwritten_store([store, between, "v_mov_b32_e32 v172, v192"]) is None
-    assert overwritten_store([store.replace("x4 v[172:175]", "x2 v[172:173]"), "v_mov_b32_e32 v172, v192"]) is None
+    for between in ("s_nop 0", "v_mov_b32_e32 v215, v192", "v_mov_b32_e32 v171, v192", "s_waitcnt vmcnt(0)"):
+        assert overwritten_store([store, between, write]) == (3, write)
+        assert overwritten_store([store, between, between, write]) is None
+    assert overwritten_store([store, "s_nop 1", write]) is None
+    assert overwritten_store([store, "s_nop 0", "v_swap_b32 v1, v174"]) is not None
+    assert overwritten_store([store.replace("x4 v[172:175]", "x2 v[172:173]"), write]) is None
+
+
+def test_the_data_of_a_wide_store_across_branches():
+    store, write = "buffer_store_dwordx4 v[172:175], v215, s[28:31], 0 offen", "v_mov_b32_e32 v172, v192"
+    # a loop's head, behind its back edge; the fall-through of a conditional branch; either side of one
+    assert overwritten_store([".LBB0_1:", write, "s_nop 3", store, "s_cbranch_scc1 .LBB0_1", "s_endpgm"]) == (2, write)
+    assert overwritten_store([store, "s_cbranch_scc1 .LBB0_2", write, ".LBB0_2:", "s_endpgm"]) == (3, write)
+    assert overwritten_store([".LBB0_1:", write, "s_nop 3", store, "s_nop 0", "s_cbranch_scc1 .LBB0_1", "s_endpgm"]) is None
+    # what stands behind an unconditional branch is not what runs
+    assert overwritten_store([store, "s_branch .LBB0_2", ".LBB0_1:", write, ".LBB0_2:", "s_endpgm"]) is None
+    assert overwritten_store([store, "s_endpgm", "_Z4nextv:", write]) is None
 
 
 def test_the_extension_module_is_named_for_its_interpreter():
