@@ -204,7 +204,7 @@ def time_workload(cfg, steps, warmup, replays, copies=None, use_graph=True):
         "workload": WORKLOAD_NAMES[cfg], "ms_per_step": ms, "ms_per_step_sustained": timing["sustained"],
         "ms_per_step_min": min(per_step), "ms_per_step_max": max(per_step), "tflops": tflops, "gbps": gbps, "flops": sol["flops"], "bytes": sol["bytes"],
         "t_sol_us": sol["t_sol"] * 1e6, "frac_of_sol": sol["t_sol"] / t,
-        "buffer_sets": copies, "launch": launch, "kernel": probe.selected(),
+        "buffer_sets": copies, "launch": launch, "kernel": probe.kernel(),
         "roofline": {
             "bound": "mfma" if mfma else "hbm", "achieved": tflops if mfma else gbps,
             "peak": PEAK_MFMA_TFLOPS if mfma else PEAK_HBM_GBPS, "unit": "TFLOP/s" if mfma else "GB/s",
@@ -395,6 +395,10 @@ def bench_widening(args):
                      w.selected() if tune is None or tune.c.split_k_mode else
                      dict(tune.as_dict(), scheduler=("default", "persistent", "stream_k")[tune.c.scheduler]),
                      "launch": launch, "sclk_mhz_under_load": sclk}
+        if tune is None or tune.c.split_k_mode:
+            runs_on = w.kernel(tune)
+            if "unnamed" in runs_on:
+                out[name]["kernel"] = runs_on
         if tune is not None and tune.c.split_k_mode:
             kw = w._problem_kwargs()
             out[name]["split_k"] = dict(zip(("workspace_bytes", "slices"),

@@ -122,7 +122,8 @@ typedef struct ucl_epilogue {
  * every geometry.  FIXED_STRIDE_DILATION (3x3 filter, unit stride and dilation, pad 1,
  * W <= 58; fprop: C = 64 or 128, dgrad: Kout = 64 or 128) copies the pixels a tile needs into LDS
  * once and reads all nine taps from there.  DEFAULT: the table takes the second where it
- * applies; 1x1 filters at unit stride without padding run on the GEMM kernels (a named tile on the GEMM kernel of that
+ * applies, and with nothing else named in ucl_tuning (or no ucl_tuning) 3x3 layers may run on the
+ * kernel of UCL_UNNAMED_CONV_HELD below instead of either; 1x1 filters at unit stride without padding run on the GEMM kernels (a named tile on the GEMM kernel of that
  * shape if one is built, else on the gathering one).  conv2d_wgrad accepts any valid value and ignores it. */
 typedef enum ucl_conv_iterator {
     UCL_ITER_DEFAULT = 0,
@@ -144,7 +145,7 @@ typedef enum ucl_conv_iterator {
  * ucl_tuning, the tile is chosen for the split-K launch (not as for the unsplit problem).
  * conv2d_wgrad, PARALLEL, no tile and no slices named: 3x3 filters with pad 1, stride 1 or 2 (both
  * ways), unit dilation, a chain of nothing or one SCALE and a 16-byte aligned dw may run on a kernel
- * that no tile names (ucl_select_tuning() and ucl_variant() know the tile kernels only).  It cuts
+ * that no tile names (UCL_UNNAMED_WGRAD_TAPS).  It cuts
  * the output pixels into ranges of its own, so its fp32 sums round differently from SERIAL's or a
  * named tile's: for fp32 results with no more roundings, for 16-bit ones possibly over longer ranges. */
 typedef enum ucl_split_k_mode { UCL_SPLIT_K_NONE = 0, UCL_SPLIT_K_SERIAL = 1, UCL_SPLIT_K_PARALLEL = 2 } ucl_split_k_mode;
@@ -371,12 +372,31 @@ ucl_status ucl_sol_bound(const ucl_problem *p, const ucl_hw *hw, ucl_sol_report 
 
 /* ---- Introspection (HOST only; used by tests and the benchmark) ------------ */
 
-/* The tuning the selection table would pick for a problem: the launch path with
- * tune == NULL applies the same function to the same description (packed
+/* The tuning the selection table would pick for a problem: of the tile kernels, the launch path with
+ * tune == NULL takes the one that the same function picks for the same description (packed
  * operands assumed: leading strides equal to the contiguous extents).  A launch
  * that asks for split-K without naming a tile chooses its tile for the split
- * launch instead; ucl_workspace_size() follows that choice. */
+ * launch instead; ucl_workspace_size() follows that choice.  Some launches run on a kernel that no
+ * tile names: ucl_unnamed_kernel().  Passing the answer of this query back in selects the tile
+ * kernel for those, which adds its fp32 sums in another order and takes longer than the open call. */
 ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out);
+
+/* The kernels that no tile names (ucl_select_tuning() and ucl_variant() know the tile kernels only). */
+typedef enum ucl_unnamed_kernel_id {
+    UCL_UNNAMED_NONE = 0,
+    /* conv2d_fprop with stride 1 or 2 (both ways) and up to 256 channels, conv2d_dgrad with stride 1: 3x3 filters
+     * with pad 1 and unit dilation, results of the inputs' type, a chain of any of SCALE, BIAS, AUX_LOAD (of the
+     * same type, ld = its extent) and RELU in this order, 16-byte aligned rows, and no tile, raster, iterator,
+     * scheduler or split named: where its estimated time is the shorter one. */
+    UCL_UNNAMED_CONV_HELD = 1,
+    /* conv2d_wgrad under UCL_SPLIT_K_PARALLEL, see ucl_split_k_mode */
+    UCL_UNNAMED_WGRAD_TAPS = 2
+} ucl_unnamed_kernel_id;
+
+/* Which of them a launch on problem p with `tune` (may be NULL) runs on, p->epi being its chain (NULL pointers
+ * in it and the result count as 16-byte aligned, an ld of 0 as packed).  As for ucl_workspace_size(),
+ * tune->workspace is not looked at: it is taken to be as large as that query asks. */
+ucl_status ucl_unnamed_kernel(const ucl_problem *p, const ucl_tuning *tune, int32_t *kernel);
 
 /* Bytes of workspace a call on problem p with tuning `tune` needs (0 without a split):
  * UCL_WORKSPACE_COUNTER_BYTES + slices x tiles x tile_m x tile_n x 4.  *slices_out (may be NULL)

@@ -126,6 +126,8 @@ def _load():
         lib.ucl_sol_bound.argtypes = [C.POINTER(_Problem), C.POINTER(_Hw), C.POINTER(_SolReport)]
         lib.ucl_select_tuning.restype = C.c_int
         lib.ucl_select_tuning.argtypes = [C.POINTER(_Problem), C.POINTER(_Tuning)]
+        lib.ucl_unnamed_kernel.restype = C.c_int
+        lib.ucl_unnamed_kernel.argtypes = [C.POINTER(_Problem), C.POINTER(_Tuning), C.POINTER(i32)]
         lib.ucl_workspace_size.restype = C.c_int
         lib.ucl_workspace_size.argtypes = [C.POINTER(_Problem), C.POINTER(_Tuning), C.POINTER(i64), C.POINTER(i32)]
         lib.ucl_workspace_init.restype = C.c_int
@@ -322,6 +324,14 @@ def ucl_select_tuning(op, dt_in, dt_out, **kw):
     t = Tuning()
     _check(_load().ucl_select_tuning(C.byref(p), t.ref()))
     return t.as_dict()
+
+
+def ucl_unnamed_kernel(op, dt_in, dt_out, tune=None, **kw):
+    """The kernel that no tile names which a call on this problem runs on ("conv_held", "wgrad_taps"), or None."""
+    p, keep = _problem(op, dt_in, dt_out, **kw)
+    kernel = C.c_int32()
+    _check(_load().ucl_unnamed_kernel(C.byref(p), _opt(tune), C.byref(kernel)))
+    return (None, "conv_held", "wgrad_taps")[kernel.value]
 
 
 def ucl_workspace_size(op, dt_in, dt_out, tune=None, **kw):

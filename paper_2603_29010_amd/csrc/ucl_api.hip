@@ -537,6 +537,9 @@ TapsChoice choose_taps(const Launch &L, const VariantDesc &v, const SplitChoice 
     return best;
 }
 bool takes_taps(const Launch &L, const ucl_tuning *tune) { return L.taps_stride > 0 && split_left_open(L, tune) && !names_tile(tune); }
+bool serves_taps(const Launch &L, const KParams &kp, const ucl_tuning *tune) {
+    return L.mode == 4 && takes_taps(L, tune) && kp.fused.enabled && !kp.fused.has_bias && !kp.fused.has_res && !kp.fused.act;
+}
 int64_t taps_bytes(const Launch &L, const TapsChoice &c) { return c.slices > 1 ? UCL_WORKSPACE_COUNTER_BYTES + (int64_t)c.slices * L.M * L.N * 4 : 0; }
 
 // Kernels that the general rule chooses among.  Split-K has kernels without K groups only.  And the slices an open call gets are what
@@ -1268,7 +1271,7 @@ ucl_status run(Launch L, KParams &kp, const ucl_tuning *tune, void *stream, bool
     if (v->lb == 0 && !panel_fits(v->tile_n, kp.ldb, L.K))
         return fail(UCL_ERR_UNSUPPORTED, "B leading stride %lld too large: a %d-row panel must span less than 2 GiB", (long long)kp.ldb, v->tile_n);
     kp.total_tiles = (int32_t)total;
-    if (L.mode == 4 && takes_taps(L, tune) && kp.fused.enabled && !kp.fused.has_bias && !kp.fused.has_res && !kp.fused.act && aligned16(kp.D)) {
+    if (serves_taps(L, kp, tune) && aligned16(kp.D)) {
         const TapsChoice taps = choose_taps(L, *v, choice);
         if (taps.slices == 1 || (taps.slices > 1 && tune->workspace && aligned16(tune->workspace) && taps_bytes(L, taps) <= tune->workspace_bytes))
             return run_taps(L, kp, taps, tune->workspace, stream);
@@ -1545,6 +1548,12 @@ ucl_status launch_from_problem(const ucl_problem *p, Launch &L) {
     if (L.mode == 3) {
         L.patch_c = conv_patch_channels(p->cW, p->cKout, p->cR, p->cS, p->pad_h, p->pad_w, p->stride_h, p->stride_w, p->dil_h, p->dil_w);
         dgrad_launch(L, p->cN, p->cH, p->cW, p->stride_h, p->stride_w);
+    }
+    if (L.mode == 2 || L.mode == 3) {
+        const int64_t P = conv_out(p->cH, p->pad_h, p->dil_h, p->cR, p->stride_h), Q = conv_out(p->cW, p->pad_w, p->dil_w, p->cS, p->stride_w);
+        const bool fwd = L.mode == 2;
+        held_launch(L, p->cN, fwd ? p->cH : P, fwd ? p->cW : Q, fwd ? P : p->cH, fwd ? Q : p->cW, fwd ? p->cC : p->cKout, p->cR, p->cS, p->pad_h, p->pad_w,
+                    p->stride_h, p->stride_w, p->dil_h, p->dil_w);
     }
     if (L.mode == 1)
         for (int g = 0; g < L.groups; ++g) L.sum_Mg += L.M_g[g];
@@ -1827,6 +1836,32 @@ ucl_status ucl_select_tuning(const ucl_problem *p, ucl_tuning *out) {
     out->raster = default_raster(*v, L);
     out->k_groups = v->k_groups;
     out->iterator = v->la == 3 ? UCL_ITER_FIXED_STRIDE_DILATION : v->la == 2 ? UCL_ITER_ANALYTIC : UCL_ITER_DEFAULT;
+    return UCL_OK;
+}
+
+ucl_status ucl_unnamed_kernel(const ucl_problem *p, const ucl_tuning *tune, int32_t *kernel) {
+    g_err[0] = 0;
+    if (!kernel) return fail(UCL_ERR_INVALID_ARG, "output pointer is NULL");
+    *kernel = UCL_UNNAMED_NONE;
+    Launch L;
+    if (ucl_status st = launch_from_problem(p, L)) return st;
+    if (!L.held_stride && !L.taps_stride) return UCL_OK;
+    SplitChoice choice;
+    const VariantDesc *v = select_with_split(L, tune, choice, /*sizing=*/true);
+    if (!v) return fail(UCL_ERR_UNSUPPORTED, "no kernel built for this problem and tuning; see ucl_variant()");
+    ucl_epilogue epi;
+    memset(&epi, 0, sizeof(epi));
+    if (p->epi) epi = *p->epi;
+    for (int i = 0; i < epi.n_steps && i < UCL_MAX_EPI_STEPS; ++i) {
+        if (!epi.steps[i].ptr) epi.steps[i].ptr = (const void *)(uintptr_t)16;      // (looked at for its alignment only)
+        if (!epi.steps[i].ld) epi.steps[i].ld = L.N;
+    }
+    KParams kp;
+    memset(&kp, 0, sizeof(kp));
+    if (ucl_status st = check_epilogue(&epi, L, kp)) return st;
+    kp.d_vec = L.N % (16 / elem_size(L.dtD)) == 0;
+    if (plan_held(L, kp, tune, *v).R > 0) *kernel = UCL_UNNAMED_CONV_HELD;
+    if (serves_taps(L, kp, tune) && choose_taps(L, *v, choice).slices > 0) *kernel = UCL_UNNAMED_WGRAD_TAPS;
     return UCL_OK;
 }
 

@@ -175,9 +175,15 @@ class DeviceWorkload:
         return kw
 
     def selected(self):
-        """The kernel the selection table picks for this workload (what run(tune=None) launches)."""
+        """The tile kernel the selection table picks for this workload."""
         s = self.spec
         return ucl.ucl_select_tuning(self.op, s["dt_in"], s["dt_out"], **self._problem_kwargs())
+
+    def kernel(self, tune=None):
+        """What run(tune) launches where `tune` names no tile: {"unnamed": ...} for a kernel that no tile names, else selected()."""
+        s = self.spec
+        unnamed = ucl.ucl_unnamed_kernel(self.op, s["dt_in"], s["dt_out"], tune=tune, epi=self.epi, **self._problem_kwargs())
+        return {"unnamed": unnamed} if unnamed else self.selected()
 
     def sol(self, hw=None):
         s = self.spec

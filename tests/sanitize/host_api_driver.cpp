@@ -48,6 +48,10 @@ int main() {
         int64_t bytes = -1;
         int32_t slices = -1;
         (void)ucl_workspace_size(&p, nullptr, &bytes, &slices);
+        int32_t kernel = -1;
+        p.stride_h = 1;
+        (void)ucl_unnamed_kernel(&p, nullptr, &kernel);
+        EXPECT(kernel == UCL_UNNAMED_NONE && ucl_unnamed_kernel(&p, nullptr, nullptr) == UCL_ERR_INVALID_ARG);
     }
     EXPECT(ucl_sol_bound(nullptr, nullptr, nullptr) == UCL_ERR_INVALID_ARG);
     {

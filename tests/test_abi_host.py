@@ -140,6 +140,31 @@ def _err(fn, *a, **k):
     return e.value
 
 
+def test_kernels_that_no_tile_names_are_reported():
+    def runs_on(op, conv, out="bf16", epi=(), tune=None):
+        return ucl.ucl_unnamed_kernel(op, "bf16", out, tune=tune, conv=conv, epi=ucl.Epilogue(epi))
+
+    conv = (32, 56, 56, 64, 128, 3, 3, 1, 1, 1, 1, 1, 1)
+    chain = [("scale", 0.5), ("bias", 0, "f32"), ("aux_load", 0, "bf16", 0, 0, 1.0), ("relu",)]
+    assert runs_on("conv2d_fprop", conv) == runs_on("conv2d_fprop", conv, epi=chain) == "conv_held"
+    assert runs_on("conv2d_dgrad", (32, 28, 28, 128, 128) + conv[5:]) == "conv_held"
+    # other chains and results, a residual of another type or pitch, anything named in the tuning: the tile kernel of ucl_select_tuning
+    for epi in ([("silu",)], [("relu",), ("bias", 0, "bf16")], [("aux_load", 0, "f32", 0, 0, 1.0)], [("aux_load", 0, "bf16", 136, 0, 1.0)], [("aux_load", 8, "bf16", 0, 0, 1.0)]):
+        assert runs_on("conv2d_fprop", conv, epi=epi) is None
+    assert runs_on("conv2d_fprop", conv, out="f32") is None
+    for tune in (ucl.Tuning(iterator=2), ucl.Tuning(raster=4), ucl.Tuning(**ucl.ucl_select_tuning("conv2d_fprop", "bf16", "bf16", conv=conv))):
+        assert runs_on("conv2d_fprop", conv, tune=tune) is None
+    # 1x1 and 5x5 filters, dilated ones, strided data gradients, other operations
+    for other in ((32, 56, 56, 64, 128, 1, 1, 0, 0, 1, 1, 1, 1), (32, 56, 56, 64, 128, 5, 5, 1, 1, 1, 1, 1, 1), (32, 56, 56, 64, 128, 3, 3, 1, 1, 1, 1, 2, 2)):
+        assert runs_on("conv2d_fprop", other) is None
+    assert runs_on("conv2d_dgrad", conv[:9] + (2, 2, 1, 1)) is None
+    assert ucl.ucl_unnamed_kernel("gemm", "bf16", "bf16", M=64, N=64, K=64) is None
+    split = ucl.Tuning(split_k="parallel")
+    wgrad = (32, 28, 28, 128, 128) + conv[5:]
+    assert runs_on("conv2d_wgrad", wgrad, out="f32", tune=split) == "wgrad_taps"
+    assert runs_on("conv2d_wgrad", wgrad, out="f32") is None and runs_on("conv2d_wgrad", wgrad, out="f32", tune=split, epi=[("relu",)]) is None
+
+
 def test_validation_rejects_before_any_launch():
     P = 4096  # a 16-byte aligned fake address: validation must fail before it is ever dereferenced
     ok = dict(A=P, dtA="bf16", a_rs=64, a_cs=1, B=P, dtB="bf16", b_rs=1, b_cs=64, D=P, dtD="bf16", d_rs=64, d_cs=1)

@@ -34,6 +34,7 @@ def kernels_of(spec, tune=None):
 
 def check_rounded(spec):
     """Whole numbers: the sums are exact in fp32, so the results are theirs rounded once."""
+    assert DeviceWorkload(spec).kernel() == {"unnamed": "conv_held"}
     assert any("conv_held_kernel" in k for k in kernels_of(spec)), kernels_of(spec)
     got, _ = parity.gpu_result(spec)
     want = oracle.round_to(orc_run.run(spec), spec["dt_out"])
@@ -74,6 +75,7 @@ def test_parts_of_the_chain(chain):
 
 def test_other_chains_and_named_kernels_stay_where_they_were():
     g = geom(3, 14, 14, 128, 64)
+    assert "unnamed" not in DeviceWorkload(synth.conv_spec(integer=True, epilogue=("silu",), **g)).kernel(), "what is reported runs"
     assert not any("held" in k for k in kernels_of(synth.conv_spec(integer=True, epilogue=("silu",), **g)))
     assert not any("held" in k for k in kernels_of(synth.conv_spec(integer=True, dt_out="f32", **g)))
     for tune in (Tuning(tile_m=64, tile_n=64, tile_k=64, stages=4), Tuning(raster=4), Tuning(iterator=1)):

@@ -159,5 +159,5 @@ def test_conv_pick_is_near_the_fastest_built_variant(name):
     if t_pick > 1.15 * times[best]:
         t_pick = min(t_pick, time_us(w, None))
         times[best] = max(times[best], time_us(w, Tuning(*best[:4], iterator=1 if best[4] == "gather" else 2)))
-    assert t_pick <= 1.15 * times[best], (f"{name}: the table's choice {w.selected()} runs {t_pick:.1f} us, {best} runs {times[best]:.1f} us; all: " +
+    assert t_pick <= 1.15 * times[best], (f"{name}: the library's choice {w.kernel()} runs {t_pick:.1f} us, {best} runs {times[best]:.1f} us; all: " +
                                           ", ".join(f"{k}: {v:.1f}" for k, v in sorted(times.items(), key=lambda kv: kv[1])))
