@@ -257,8 +257,6 @@ double estimate_seconds(const VariantDesc &v, const CostRow &row, const CostRow 
 
 constexpr int kNumCUs = 256;
 
-
-
 // Slices a split-K launch of `total_tiles` tiles gets: as asked for, or (0) enough to give every CU a workgroup
 // while each keeps at least 4 x 64 of K; slices are whole multiples of 64 along K.
 // The weight gradient in parallel mode gets two workgroups per CU where the variant fits twice: its gathered operand
@@ -650,25 +648,24 @@ HeldPlan choose_held(const Launch &L, bool residual) {
     return best;
 }
 
-// Seconds of the kernel that a convolution would get instead.  kCostRows price the resident-patch kernels as if they gathered every tap from memory,
-// which serves among tile kernels but is up to 1.8 times what they take where there are more tiles than slots.  (Gathering forward kernels
-// take 1.05 of what their rows say in the mean, the few-row ones 0.95.)
+// Seconds of the tile kernel that a 3x3 convolution would get instead (kConvRows), 0 for one without a row.
 double tile_kernel_seconds(const VariantDesc &v, const Launch &L, bool residual) {
-    if (v.la == 3) {
-        for (const PatchRow &r : kPatchRows) {
-            if (r.mode != v.mode || r.tile_m != v.tile_m || r.tile_n != v.tile_n || r.patch_c != v.patch_c) continue;
-            const int64_t tiles = count_tiles(L, v.tile_m, v.tile_n), rounds = (tiles + 2 * kNumCUs - 1) / (2 * kNumCUs);
-            const double on_cu = tiles <= 2 * kNumCUs ? (double)((tiles + kNumCUs - 1) / kNumCUs) : 2.0 * (double)rounds, K = (double)L.K;
-            const double copies = on_cu * (v.tile_m + (double)(L.N < v.tile_n ? L.N : v.tile_n)) * K * 2.0 / (r.gbs * 1e3);
-            const double math = on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6);
-            const double chain = (double)rounds * (double)((L.K + 31) / 32) * r.step, memory = ((double)L.M + (double)L.N) * K * 2.0 / 9.0 / 5.3e6;
-            const double out = (double)L.M * (double)L.N * 2.0 / 4.6e6 * r.out * (L.mode == 2 && !residual ? 0.5 : 1.0);      // (fitted to forward passes with a residual)
-            return 1e-6 * (r.fixed + r.round * (double)rounds + fourth_power_sum(fourth_power_sum(copies, math, chain, memory), out * r.hidden) + out * (1.0 - r.hidden));
-        }
+    for (const ConvRow &r : kConvRows) {
+        if (r.mode != v.mode || r.tile_m != v.tile_m || r.tile_n != v.tile_n || r.tile_k != v.tile_k || r.stages != v.stages || r.k_groups != v.k_groups || r.patch_c != v.patch_c) continue;
+        const int64_t tiles_n = (L.N + v.tile_n - 1) / v.tile_n, tiles = count_tiles(L, v.tile_m, v.tile_n), slots = kNumCUs * r.resident, rounds = (tiles + slots - 1) / slots;
+        const double on_cu = tiles <= slots ? (double)((tiles + kNumCUs - 1) / kNumCUs) : (double)(rounds * r.resident), K = (double)L.K, N = (double)L.N;
+        const double lines = (double)((L.cC + 63) / 64 * 64) / (double)L.cC - 1.0;
+        const double rows = v.tile_m * (1.0 + r.lines * lines + (L.held_stride == 2 ? r.stride2 : 0.0) + (L.cC % 64 ? r.odd_c : 0.0));
+        const double columns = (L.N < v.tile_n ? N : v.tile_n) + (L.N < 64 ? r.few_n * (64.0 - N) : 0.0);
+        const double copies = on_cu * (rows + columns) * K * 2.0 / (r.gbs * 1e3);
+        const double math = on_cu * 2.0 * v.tile_m * v.tile_n * K / (r.tflops * 1e6);
+        const int64_t step_k = (is_few_row(v) ? 64 : v.tile_k) * v.k_groups;
+        const double chain = (double)(rounds * ((L.K + step_k - 1) / step_k)) * r.step, memory = ((double)L.gathered + N * K * 2.0) / 5.3e6 * r.memory;
+        const double out = (double)L.M * N * 2.0 / 4.6e6 * (r.out + (residual ? r.residual : 0.0)) *
+                           (1.0 + (L.N % v.tile_n ? r.part / (double)tiles_n : 0.0) + (L.N % 64 ? r.half_line : 0.0));
+        return 1e-6 * (r.fixed + r.round * (double)rounds + fourth_power_sum(fourth_power_sum(copies, math, chain, memory), out * r.hidden) + out * (1.0 - r.hidden));
     }
-    const size_t i = (size_t)(&v - all_variants().data());
-    bool one = false;
-    return estimate_seconds(v, all_costs()[i], many_tiles_costs()[i], L, &one) * (L.mode != 2 || v.la != 2 ? 1.0 : is_few_row(v) ? 0.95 : 1.05);
+    return 0;
 }
 
 // The plan of a convolution that runs on conv_held_kernel, R = 0 for one that does not: calls that name nothing, with the chains of the usual layers (scale,
@@ -678,8 +675,9 @@ HeldPlan plan_held(const Launch &L, const KParams &kp, const ucl_tuning *tune, c
     const int type = L.dt == 1 ? UCL_F16 : UCL_BF16;
     const FusedEpi &f = kp.fused;
     if (!f.enabled || (f.act && f.act != UCL_EPI_RELU) || L.dtD != type || !kp.d_vec || (f.has_res && (f.res_dt != (type | 0x100) || f.res_ld != L.N))) return HeldPlan();
+    const double tile_seconds = tile_kernel_seconds(v, L, f.has_res != 0);
     const HeldPlan h = choose_held(L, f.has_res != 0);
-    return h.R > 0 && h.seconds < tile_kernel_seconds(v, L, f.has_res != 0) ? h : HeldPlan();
+    return h.R > 0 && h.seconds < tile_seconds ? h : HeldPlan();
 }
 
 const VariantDesc *select_variant(const Launch &L, const ucl_tuning *tune) {

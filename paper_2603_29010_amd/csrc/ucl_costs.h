@@ -155,28 +155,51 @@ static const SplitCostRow kWgradSplitRows[] = {
     {64, 64, 64, 4,  0.00f, 2.41f},
 };
 
-// Resident-patch kernels of two workgroups per CU, for the choice between them and conv_held_kernel (tile_kernel_seconds): fitted to the 2270 of 12000
-// geometries that kCostRows give to them, 3 to 5 % off where those rows are 10 to 15 %.
-struct PatchRow {
-    short mode, tile_m, tile_n, patch_c;
-    float fixed, round, gbs, tflops, step, out, hidden;
+// Tile kernels of 3x3 convolutions (forward at stride 1 and 2, data gradients at stride 1; rows of all that such a layer can get), for the choice between
+// them and conv_held_kernel (tile_kernel_seconds).  kCostRows rank them among one another, but know neither the residual nor columns that
+// fill no tile nor pixels of less than a line: 14 to 35 % off as times for the 128x128, 256x128 and 32-deep kernels, and the choice made with them
+// took layers to conv_held_kernel that ran up to 1.6 times as fast here (17 x 56 x 56 x 128 -> 128 without a residual 21.8 us, there 33.3).
+// Fitted to 79000 layers (1 to 64 images of 3 to 400 rows and 3 to 1024 columns, 8 to 1024 channels), 2 to 7 % off:
+//   fixed, round, gbs, tflops, step   as in CostRow
+//   out, residual, hidden             weight of the output's bytes at 4.6 TB/s, of the residual's, and the share that the loop hides
+//   part, half_line                   what they take longer in a column of tiles that is not full, and where a row is not whole lines of 128 bytes
+//   lines, few_n, stride2, odd_c      pixels copied beyond their bytes: whole lines where C < 64, filters of fewer than 64 columns, stride 2, C no multiple of 64
+//   memory                            weight of the operands' trip from memory at 5.3 TB/s
+struct ConvRow {
+    short mode, tile_m, tile_n, tile_k, stages, k_groups, patch_c, resident;
+    float fixed, round, gbs, tflops, step, out, residual, hidden, part, half_line, lines, few_n, stride2, odd_c, memory;
 };
-static const PatchRow kPatchRows[] = {
-    {3, 128, 64, 128,  3.97f, 3.57f, 803.0f, 5.45f, 0.094f, 5.20f, 0.85f},
-    {3, 256, 64, 64,  7.14f, 0.00f, 181.0f, 5.15f, 0.080f, 1.47f, 0.30f},
-    {2, 128, 64, 128,  4.26f, 1.22f, 126.9f, 9.98f, 0.160f, 2.63f, 0.00f},
-    {2, 256, 128, 64,  10.66f, 0.00f, 203.1f, 6.21f, 0.092f, 1.44f, 0.38f},
+static const ConvRow kConvRows[] = {
+    {2, 256, 128, 32, 3, 1,   0, 2,  6.24f, 2.31f, 175.4f, 7.76f, 0.786f,  0.66f, 0.84f, 0.00f, 0.49f, 0.91f,  0.71f, 30.00f, 1.45f, 0.00f, 1.32f},
+    {2, 256, 128, 32, 4, 1,  64, 6,  2.33f, 1.12f, 62.6f, 5.59f, 0.597f,  0.42f, 0.83f, 0.03f, 0.71f, 1.70f,  0.68f, 6.40f, 0.00f, 0.00f, 4.55f},
+    {2, 128, 128, 64, 2, 1,   0, 2,  4.75f, 1.31f, 178.6f, 8.77f, 0.665f,  1.18f, 1.13f, 0.02f, 0.53f, 0.41f,  0.00f, 7.16f, 0.68f, 1.41f, 1.31f},
+    {2, 128, 128, 64, 2, 2,   0, 1,  4.10f, 3.72f, 124.9f, 4.84f, 0.007f,  0.65f, 1.03f, 0.08f, 0.80f, 1.24f,  0.00f, 3.03f, 0.87f, 1.45f, 1.67f},
+    {2, 128, 128, 32, 3, 1,   0, 1,  4.95f, 0.05f, 276.0f, 30.00f, 0.239f,  1.04f, 1.19f, 0.00f, 0.22f, 0.48f,  3.00f, 19.12f, 2.53f, 0.57f, 1.51f},
+    {2, 128,  64, 64, 3, 2,   0, 1,  3.64f, 2.17f, 173.0f, 2.96f, 0.008f,  1.27f, 1.53f, 0.03f, 0.16f, 0.94f,  0.00f, 1.46f, 1.68f, 1.16f, 1.88f},
+    {2, 128,  64, 32, 4, 1, 128, 2,  4.80f, 0.00f, 242.1f, 5.40f, 0.146f,  1.98f, 1.37f, 0.03f, 1.20f, 0.22f,  1.14f, 6.37f, 0.00f, 0.00f, 0.00f},
+    {2,  64,  64, 64, 4, 2,   0, 1,  4.58f, 1.64f, 135.8f, 30.00f, 0.251f,  0.85f, 2.05f, 0.02f, 0.05f, 0.57f,  0.46f, 1.47f, 0.32f, 0.43f, 0.82f},
+    {2,  64,  64, 32, 3, 1,   0, 5,  5.24f, 0.39f, 333.9f, 2.59f, 0.138f,  0.99f, 0.84f, 0.03f, 0.00f, 0.28f,  3.00f, 5.50f, 0.00f, 0.00f, 1.72f},
+    {2,  16,  32, 64, 1, 4,   0, 1,  5.26f, 1.98f, 166.5f, 30.00f, 0.177f,  4.62f, 6.51f, 0.07f, 0.00f, 0.00f,  0.00f, 0.00f, 0.20f, 0.00f, 0.01f},
+    {3, 256, 128, 32, 4, 1,  64, 1,  6.82f, 6.77f, 900.0f, 30.00f, 0.000f,  0.32f, 0.71f, 0.00f, 0.72f, 1.46f,  2.29f, 0.30f, 0.00f, 0.00f, 1.60f},
+    {3, 128, 128, 32, 4, 1,   0, 2,  6.44f, 5.44f, 277.8f, 4.97f, 0.000f,  0.71f, 0.82f, 0.00f, 0.69f, 0.41f,  1.79f, 17.65f, 1.37f, 3.00f, 4.08f},
+    {3, 256,  64, 32, 4, 1,   0, 1,  5.25f, 3.01f, 301.5f, 4.54f, 0.337f,  0.18f, 0.79f, 0.00f, 0.00f, 0.89f,  1.78f, 0.47f, 1.04f, 3.00f, 7.95f},
+    {3, 256,  64, 32, 4, 1,  64, 2,  6.74f, 0.00f, 581.0f, 4.65f, 0.246f,  0.40f, 1.26f, 0.00f, 0.09f, 1.90f,  1.43f, 30.00f, 0.00f, 0.00f, 2.38f},
+    {3, 128,  64, 32, 4, 1,   0, 3,  7.41f, 0.00f, 222.3f, 3.77f, 0.265f,  1.76f, 0.81f, 0.02f, 0.00f, 0.41f,  1.87f, 8.03f, 1.05f, 1.21f, 3.51f},
+    {3, 128,  64, 32, 4, 1, 128, 2,  5.14f, 1.07f, 900.0f, 4.87f, 0.144f,  1.11f, 1.25f, 0.04f, 0.11f, 0.71f,  1.97f, 24.53f, 0.00f, 0.00f, 2.65f},
+    {3,  64,  64, 64, 4, 2,   0, 1,  2.64f, 6.27f, 82.7f, 30.00f, 0.393f,  1.34f, 2.17f, 0.01f, 0.27f, 0.26f,  0.65f, 1.05f, 2.93f, 0.08f, 3.03f},
+    {3,  64,  64, 32, 3, 1,   0, 4,  5.91f, 0.95f, 64.7f, 2.66f, 0.231f,  0.33f, 0.66f, 0.06f, 0.05f, 1.15f,  1.18f, 1.00f, 0.27f, 0.00f, 6.19f},
 };
 
 // Launches of conv_held_kernel, microseconds (per byte; by wave groups over channels 1, 2, 4 and by waves that share a filter 1, 2, 4): fitted to 66000 launches
 // of 12000 geometries (1 to 64 images of 5 to 80 pixels a side, 16 to 1024 channels), 7 % off; the plan chosen with them is 1.6 % behind the best of
-// six measured ones on 12000 others.
+// six measured ones on 12000 others.  On the 79000 layers of kConvRows, up to 1024 columns wide, the chosen plan's estimate is 6 % off, with the
+// weights of the bytes that all move (the last three) fitted to them: 1 x 14 x 14 x 256 -> 1024 at stride 2 was priced 10.4 us and takes 7.4.
 struct HeldCosts {
     double launch, pass[3], sharing[3], pair[3], next_pass;              // pair: a wave's two rows of 16 pixels
     double filter, filter_alone, pixels, pixels_alone;                   // bytes that a workgroup copies, by the share of busy CUs and by themselves
     double memory, moved, weights;                                       // bytes that all of them move
 };
 static const HeldCosts kHeldCosts = {2.933, {1.864, 2.100, 2.098}, {0.178, 0.389, 0.137}, {1.320, 1.482, 1.512}, 1.565,
-                                     3.83e-6, 0.14e-6, 11.4e-6, 19.7e-6, 2.357, 0.260e-6, 1.46e-6};
+                                     3.83e-6, 0.14e-6, 11.4e-6, 19.7e-6, 0.764, 0.283e-6, 0.317e-6};
 
 }  // namespace ucl
