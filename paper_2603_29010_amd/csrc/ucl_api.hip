@@ -161,8 +161,8 @@ void taps_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
     L.taps_stride = ok ? (int)str_h : 0;
 }
 
-// Convolutions that conv_held_kernel serves: 3x3 with pad 1 at unit stride and dilation, as a forward pass up to the channels of one pass (further ones gain
-// nothing there: 0.7 of the tile kernels' speed), as a data gradient any.  n images of P x Q output pixels, C channels to multiply, L.N to write; the limits are
+// Convolutions that conv_held_kernel serves: 3x3 with pad 1 and unit dilation, as a forward pass at stride 1 or 2 and up to the channels of one pass (further
+// ones gain nothing there: 0.7 of the tile kernels' speed), as a data gradient at stride 1 and of any channels.  n images of P x Q output pixels, C channels to multiply, L.N to write; the limits are
 // those of 32-bit offsets and of divisions by reciprocals.
 void held_launch(Launch &L, int64_t n_img, int64_t H, int64_t W, int64_t P, int64_t Q, int64_t C, int64_t R, int64_t S, int64_t pad_h, int64_t pad_w, int64_t str_h,
                  int64_t str_w, int64_t dil_h, int64_t dil_w) {
@@ -589,21 +589,20 @@ bool few_rows_apply(const VariantDesc &v, const Launch &L) {
     return L.K >= 320;
 }
 
-// Seconds of a conv_held_kernel launch (constants in ucl_costs.h): the workgroups of a round have `pairs` pairs of rows per wave to
-// multiply and `pixels` bytes of pixels and their filters to copy, whose rate falls with the CUs that copy; or what all of them move.
-double held_seconds(const Launch &L, const HeldPlan &h, double pairs, int64_t pixels, bool residual) {
+// Microseconds that the CUs take for a conv_held_kernel launch (constants in ucl_costs.h): the workgroups of a round have `pairs` pairs of rows per
+// wave to multiply and `pixels` bytes of pixels and their filters to copy, whose rate falls with the CUs that copy.
+double held_microseconds(const HeldPlan &h, double pairs, int64_t pixels) {
     const HeldCosts &c = kHeldCosts;
     const int k = h.kg == 1 ? 0 : h.kg == 2 ? 1 : 2, mg = 8 / (h.kg * h.ng), m = mg == 1 ? 0 : mg == 2 ? 1 : 2;
     const double filter = h.kg * h.ng * 36.864e3, fixed = c.pass[k] + c.sharing[m] + c.pair[k] * pairs;
     auto round = [&](double busy) { return h.passes * (fixed + filter * (c.filter * busy + c.filter_alone) + (double)pixels * (c.pixels * busy + c.pixels_alone)) + c.next_pass * (h.passes - 1); };
-    const int64_t wgs = (int64_t)h.bands * h.tiles_n, full = wgs / kNumCUs, rest = wgs % kNumCUs;
-    const double cus = c.launch + (double)full * round(1.0) + (rest ? round((double)rest / kNumCUs) : 0.0);
-    const double moved = (double)L.gathered + (double)(L.cN * L.cP * L.cQ) * (double)(L.N * (residual ? 2 : 1)) * 2.0;
-    return 1e-6 * fourth_power_sum(cus, c.memory + c.moved * moved + c.weights * (double)(9 * L.cC * L.N) * 2.0);
+    const int wgs = h.bands * h.tiles_n, full = wgs / kNumCUs, rest = wgs % kNumCUs;
+    return c.launch + (double)full * round(1.0) + (rest ? round((double)rest / kNumCUs) : 0.0);
 }
 
-// How conv_held_kernel would cut up a problem: of the plans whose pixels fit into LDS, with as many rows per workgroup as one, two or three rounds
-// of workgroups take or as LDS holds, the one with the shortest estimate.
+// How conv_held_kernel would cut up a problem: of the plans whose pixels fit into LDS, with as many rows per workgroup as one to four rounds
+// of workgroups take, or as LDS holds where that is fewer, the one with the shortest estimate.  (Every call that may be served asks: 32-bit
+// numbers, what all plans move left to the end, and no strips shared out among more waves than there are strips.)
 HeldPlan choose_held(const Launch &L, bool residual) {
     HeldPlan best;
     if (!L.held_stride) return best;
@@ -615,36 +614,43 @@ HeldPlan choose_held(const Launch &L, bool residual) {
     h.pitch = (int)(L.cQ + 16) / 16 * 16;
     h.strips = h.pair == 2 ? 1 : (int)(L.cQ + 15) / 16;
     h.rows = (int)((L.cN + h.pair - 1) / h.pair * (L.cP + 1));
+    double best_us = 0;
     for (h.ng = 4; h.ng >= 1; h.ng /= 2) {
         const int capacity = held_patch_capacity(h.kg, h.ng);
         if (capacity == 0) continue;
-        h.tiles_n = (int)((L.N + 32 * h.ng - 1) / (32 * h.ng));
+        h.tiles_n = ((int)L.N + 32 * h.ng - 1) / (32 * h.ng);
         const int mg = 8 / (h.kg * h.ng);
-        for (h.strip_split = 1; h.strip_split <= mg; h.strip_split *= 2) {
+        for (h.strip_split = 1; h.strip_split <= mg && (h.strip_split == 1 || h.strip_split / 2 < h.strips); h.strip_split *= 2) {
             const int groups = mg / h.strip_split, strips = (h.strips + h.strip_split - 1) / h.strip_split;
             auto per_of = [&](int R) { return held_rows_of_wave(R, groups, h.kg, h.passes > 1); };
             // (sums of earlier passes: one more pair, what the first pair's MFMAs find to finish)
             auto keep_of = [&](int R) { return h.passes > 1 ? (per_of(R) * strips + 2) * 512 * (8 / h.kg) * 4 : 0; };
             int most = ((capacity / h.kg / 128 - 8) / (h.stride * h.pitch) - 3 + h.stride) / h.stride;
             while (most > 0 && held_plane_bytes(h.stride, most, h.pitch) * h.kg + keep_of(most) > capacity) --most;
-            for (int rounds = 1; rounds <= 4 && most > 0; ++rounds) {
+            for (int rounds = 1, tried = 0; rounds <= 4 && most > 0; ++rounds) {
                 const int bands = kNumCUs * rounds / h.tiles_n;
                 h.R = bands > 0 ? (h.rows + bands - 1) / bands : most + 1;
                 if (h.R > most) {
                     if (rounds < 4) continue;
                     h.R = most;
                 }
+                if (h.R == tried) continue;
+                tried = h.R;
                 // (rows are multiplied in pairs and strips 16 columns at a time: what is read beyond the band's pixels has to be in LDS, too)
                 const int per = per_of(h.R), last = (h.R - 1) / per * per + per;
-                if (held_plane_bytes(h.stride, h.R, h.pitch) * (h.kg - 1) + ((int64_t)(h.stride * (last - 1) + 3) * h.stride * h.pitch + 16 * h.strip_split + 32) * 128 > kLdsBytesPerCU) continue;
+                const int64_t plane = held_plane_bytes(h.stride, h.R, h.pitch);
+                if (plane * (h.kg - 1) + ((int64_t)(h.stride * (last - 1) + 3) * h.stride * h.pitch + 16 * h.strip_split + 32) * 128 > kLdsBytesPerCU) continue;
                 h.bands = (h.rows + h.R - 1) / h.R;
                 h.keep_bytes = keep_of(h.R);
-                h.seconds = held_seconds(L, h, (per / 2 + (per & 1 ? 0.55 : 0.0)) * strips, held_plane_bytes(h.stride, h.R, h.pitch) * h.kg, residual);
-                if (best.R == 0 || h.seconds < best.seconds) best = h;
+                const double us = held_microseconds(h, (per / 2 + (per & 1 ? 0.55 : 0.0)) * strips, plane * h.kg);
+                if (best.R == 0 || us < best_us) { best = h; best_us = us; }
                 if (h.R == most || h.R == 1) break;
             }
         }
     }
+    const HeldCosts &c = kHeldCosts;
+    const double moved = (double)L.gathered + (double)(L.cN * L.cP * L.cQ) * (double)(L.N * (residual ? 2 : 1)) * 2.0;
+    best.seconds = 1e-6 * fourth_power_sum(best_us, c.memory + c.moved * moved + c.weights * (double)(9 * L.cC * L.N) * 2.0);
     return best;
 }
 
