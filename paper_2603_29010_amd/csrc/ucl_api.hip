@@ -167,10 +167,14 @@ void taps_launch(Launch &L, int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
 void held_launch(Launch &L, int64_t n_img, int64_t H, int64_t W, int64_t P, int64_t Q, int64_t C, int64_t R, int64_t S, int64_t pad_h, int64_t pad_w, int64_t str_h,
                  int64_t str_w, int64_t dil_h, int64_t dil_w) {
     L.cN = n_img; L.cP = P; L.cQ = Q; L.cC = C;
+    // (rows whose offsets a launch works out: also those of a missing partner of the last image of up to seven columns, and those that the last band and its
+    // waves have beyond the images, fewer than 64 padded ones.  With 2 GiB or more of them the offset of a row and the one that keeps a lane from
+    // storing could add up to an address inside the result.)
+    const int64_t named_rows = (n_img + (Q <= 7)) * P + 128;
     const bool ok = R == 3 && S == 3 && pad_h == 1 && pad_w == 1 && str_h == str_w && (str_h == 1 || (str_h == 2 && L.mode == 2)) && dil_h == 1 && dil_w == 1 && L.dt < 2 &&
                     (L.dt == 0 ? variants_conv_held_bf16() : variants_conv_held_f16()).n > 0 &&
                     (L.mode == 3 || C <= 64 * kHeldMaxKG) && L.N % 8 == 0 && Q <= 1024 && P < (1 << 20) && n_img * (P + 1) * ((L.N + 31) / 32) < (1ll << 20) &&
-                    n_img * P * Q * L.N < (1ll << 30) && n_img * H * W * C < (1ll << 30) && C * 9 * L.N < (1ll << 30);
+                    named_rows * Q * L.N < (1ll << 30) && n_img * H * W * C < (1ll << 30) && C * 9 * L.N < (1ll << 30);
     L.held_stride = ok ? (int)str_h : 0;
     L.gathered = n_img * H * W * C * 2;
 }
